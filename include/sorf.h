@@ -179,10 +179,11 @@ size_t sorf_projection_fit_workspace_bytes(int32_t d_rep);
 /* Fit of one element's projection matrix (SORF subsection: the SVD Z~_e = U_e S_e V_e^T of
  * the matrix whose columns are sampled representations of element e; U_e^{N_PCA} is its
  * first N_PCA columns). Computed as the eigenvectors of Z~_e Z~_e^T = sum_rows rho^T rho,
- * formed in FP64, by the cyclic Jacobi method in FP64 (at most 15 sweeps).
+ * formed in FP64: Householder tridiagonalisation, bisection for the n_pca largest
+ * eigenvalues and inverse iteration for their vectors, all in FP64.
  *   sample: [n_samples][d_rep] FP32 rows (any alignment).
  *   U: [d_rep][n_pca] row-major FP32 out; column r is the left singular vector of the
- *     r-th largest singular value (equal values: lower eigenvector index first), its sign
+ *     r-th largest singular value (equal values: an orthonormal basis of their space), its sign
  *     chosen so that its entry of largest magnitude (ties: lowest row) is positive. Writing
  *     element e's result at U_all + e * d_rep * d with n_pca = d builds the [E][d_rep][d]
  *     array sorf_project takes.
@@ -191,7 +192,7 @@ size_t sorf_projection_fit_workspace_bytes(int32_t d_rep);
  *   determined only for distinct, nonzero singular values: the sample needs rank >= n_pca
  *   (columns past its rank are arbitrary unit vectors of the null space).
  *   workspace: at least sorf_projection_fit_workspace_bytes(d_rep), 256-byte aligned.
- *   About 15 (d_rep + 1) kernel launches; deterministic. */
+ *   About d_rep + 15 kernel launches; deterministic. */
 sorf_status sorf_projection_fit(int64_t n_samples, int32_t d_rep, const float* sample,
                                 int32_t n_pca, float* U, double* singular_values,
                                 void* workspace, size_t workspace_bytes, sorf_stream_t stream);

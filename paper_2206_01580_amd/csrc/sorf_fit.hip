@@ -1,0 +1,601 @@
+// Fit of one element's projection (arXiv 2206.01580, Theory section, SORF
+// subsection: Z~_e = U_e S_e V_e^T over sampled representations, U_e^{N_PCA}
+// its first N_PCA columns). The left singular vectors of Z~_e are the
+// eigenvectors of G = Z~_e Z~_e^T = sum over the sampled rows of rho^T rho
+// (n x n, n = d_rep), and the singular values the square roots of its
+// eigenvalues. G is formed in FP64 by the FP64 Gram kernel; only its n_pca
+// largest eigenpairs are computed, all in FP64:
+//
+//   tridiagonal  Householder reduction Q^T G Q = T, one launch per column. A
+//                launch applies the previous column's rank-two update to its
+//                rows and multiplies the updated rows by the new reflector in
+//                the same pass, so a column costs one read and one write of
+//                the trailing matrix (L2-resident) and one launch;
+//   bisect       one workgroup per wanted eigenvalue of T: every thread counts
+//                the eigenvalues below its own shift (Sturm sequence), so a pass
+//                narrows the interval 257-fold and seven or eight passes reach
+//                the rounding of T;
+//   vectors      inverse iteration on T (LU with partial pivoting), one wave
+//                per vector;
+//   clusters     eigenvalues closer than kFitCluster ||T|| share a workgroup
+//                that orthonormalises their vectors in order; their inverse
+//                iteration is repeated from the orthonormal vectors;
+//   back         the reflectors are applied to the wanted vectors only.
+//
+// What bounds it: the chain of n dependent columns, each a launch of about six
+// microseconds (launch, two workgroup sums, one pass over L2; the arithmetic is
+// under 2 % of that). At n = 720, n_pca = 128 (1000 samples) the call takes
+// 5.5 ms: columns 4.2, vectors 0.54, back 0.46, bisection 0.29, Gram 0.13. The
+// cyclic Jacobi method that stood here before took 112 ms (15 sweeps of 719
+// launches, all n eigenvectors rotated at every one of them; with blocks of 16
+// indices it needs as many sweeps, so fewer launches alone would not do).
+#include "sorf_internal.h"
+
+namespace sorf {
+
+constexpr int kFitThreads = 256;
+constexpr int kFitLdsN = 1600;           // largest n whose LU factors stay in LDS (40 n bytes)
+constexpr int kFitPasses = 10;           // 257^8 = 2^64: the interval is at rounding size by then
+constexpr double kFitEps = 2.220446049250313e-16;
+// Vectors of eigenvalues further apart than this (relative to ||T||) are
+// orthogonal to eps / kFitCluster = 2e-8 by themselves, below the rounding of
+// the FP32 output.
+constexpr double kFitCluster = 1e-8;
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, false);
+  return v + __hiloint2double(hi, lo);
+}
+
+// Sum over a wave, the same value in every lane: butterflies inside each row
+// of 16 lanes (no LDS round trip: this is on the chain of every column and
+// every reflector), then the four row sums.
+__device__ __forceinline__ double wave_sum(double v) {
+  v = dpp_add<0xB1>(v);    // lane ^ 1
+  v = dpp_add<0x4E>(v);    // lane ^ 2
+  v = dpp_add<0x141>(v);   // mirrored half rows: the other quad
+  v = dpp_add<0x140>(v);   // mirrored rows: the other half
+  auto row = [&](int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                            __builtin_amdgcn_readlane(__double2loint(v), l));
+  };
+  return (row(0) + row(16)) + (row(32) + row(48));
+}
+
+// Sum over the workgroup's four waves, the same value in every thread.
+__device__ __forceinline__ double block_sum(double v, double* red) {
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = (red[0] + red[1]) + (red[2] + red[3]);
+  __syncthreads();
+  return v;
+}
+
+// A (n x n, full) = the symmetric matrix whose lower triangle is G.
+__global__ __launch_bounds__(256) void fit_init_kernel(const double* __restrict__ G, int n,
+                                                       double* __restrict__ A) {
+  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (t >= int64_t(n) * n) return;
+  const int i = int(t / n), j = int(t % n);
+  A[t] = i >= j ? G[t] : G[int64_t(j) * n + i];
+}
+
+// Column k of the reduction. In: A with the updates of columns < k - 1, the
+// reflector v of column k - 1 (H = I - tau v v^T, entries >= k), tau and
+// p = A v. Every workgroup forms, from row k of A and these vectors,
+//   w = tau p - (tau^2 / 2) (v . p) v,   column k of A - v w^T - w v^T,
+// the diagonal entry, the subdiagonal entry and the next reflector; then it
+// updates its own rows i > k and multiplies them by the new reflector. Row k
+// itself is read by all and written by none.
+template <int NMAX>
+__global__ __launch_bounds__(kFitThreads) void fit_column_kernel(
+    double* __restrict__ A, int n, int k, const double* __restrict__ p_in,
+    double* __restrict__ p_out, double* __restrict__ Vh, double* __restrict__ tau,
+    double* __restrict__ diag, double* __restrict__ sub) {
+  __shared__ double sv[NMAX], sw[NMAX], sn[NMAX];   // old reflector, w, new reflector
+  __shared__ double red[4];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int i = k + 1 + ((int(blockIdx.x) * kFitThreads + tid) >> 6);   // this wave's row
+  double* __restrict__ Ai = A + int64_t(i < n ? i : n - 1) * n;
+  // the row is requested first, to arrive while the reflector is formed
+  constexpr int EPT = NMAX / 64;
+  constexpr bool HELD = EPT <= 16;
+  double ai[HELD ? EPT : 1];
+  if constexpr (HELD) {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      const int j = e * 64 + lane;
+      ai[e] = j > k && j < n ? Ai[j] : 0.0;
+    }
+  }
+  const double tau0 = k > 0 ? tau[k - 1] : 0.0;
+  const double* __restrict__ row = A + int64_t(k) * n;
+  const double* __restrict__ v0 = Vh + int64_t(k > 0 ? k - 1 : 0) * n;
+  double vp = 0.0;
+  for (int j = k + tid; j < n; j += kFitThreads) {
+    const double v = k > 0 ? v0[j] : 0.0;
+    const double p = k > 0 ? p_in[j] : 0.0;
+    sv[j] = v;
+    sw[j] = p;
+    vp = fma(v, p, vp);
+  }
+  vp = block_sum(vp, red);
+  const double half = 0.5 * tau0 * tau0 * vp;
+  for (int j = k + tid; j < n; j += kFitThreads) sw[j] = tau0 * sw[j] - half * sv[j];
+  __syncthreads();
+  const double vk = sv[k], wk = sw[k];
+  double x2 = 0.0;   // squared norm of the column below the subdiagonal entry
+  for (int j = k + tid; j < n; j += kFitThreads) {
+    const double c = row[j] - (sv[j] * wk + sw[j] * vk);
+    sn[j] = c;
+    if (j > k + 1) x2 = fma(c, c, x2);
+  }
+  x2 = block_sum(x2, red);
+  const double dk = sn[k];
+  const double x0 = k + 1 < n ? sn[k + 1] : 0.0;
+  double t = 0.0, alpha = x0;
+  if (x2 > 0.0) {
+    const double norm = sqrt(fma(x0, x0, x2));
+    alpha = x0 > 0.0 ? -norm : norm;
+    const double head = x0 - alpha;             // v = (head, x_1, ...), |head| >= norm
+    t = 2.0 / fma(head, head, x2);
+    __syncthreads();                            // x0 has been read by every thread
+    if (tid == 0) sn[k + 1] = head;
+  } else if (x2 != x2) {
+    t = x2;                                     // not a number: carried into the result
+  }
+  __syncthreads();
+  if (blockIdx.x == 0) {
+    for (int j = k + 1 + tid; j < n; j += kFitThreads) Vh[int64_t(k) * n + j] = sn[j];
+    if (tid == 0) {
+      tau[k] = t;
+      diag[k] = dk;
+      sub[k] = alpha;
+    }
+  }
+  if (i >= n) return;   // whole waves
+  const double vi = sv[i], wi = sw[i];
+  double s = 0.0;
+  if constexpr (HELD) {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      const int j = e * 64 + lane;
+      if (j > k && j < n) {
+        const double a = ai[e] - (vi * sw[j] + wi * sv[j]);
+        Ai[j] = a;
+        s = fma(a, sn[j], s);
+      }
+    }
+  } else {
+    for (int j = k + 1 + lane; j < n; j += 64) {
+      const double a = Ai[j] - (vi * sw[j] + wi * sv[j]);
+      Ai[j] = a;
+      s = fma(a, sn[j], s);
+    }
+  }
+  s = wave_sum(s);
+  if (lane == 0) p_out[i] = s;
+}
+
+// 1 / q to rounding (the hardware's approximation, two Newton steps).
+__device__ __forceinline__ double fit_rcp(double q) {
+  double r = __builtin_amdgcn_rcp(q);
+  r = fma(r, fma(-q, r, 1.0), r);
+  return fma(r, fma(-q, r, 1.0), r);
+}
+
+// lam[r] = the r-th largest eigenvalue of T; norm[0] = a bound on ||T||. One
+// workgroup per eigenvalue, every thread with a shift of its own.
+template <int NMAX>
+__global__ __launch_bounds__(kFitThreads) void fit_bisect_kernel(
+    const double* __restrict__ diag, const double* __restrict__ sub, int n, int n_pca,
+    double* __restrict__ lam, double* __restrict__ norm) {
+  __shared__ double sd[NMAX], se2[NMAX];
+  __shared__ double red[3][4];
+  __shared__ int redi[4];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  double lo = 1e308, hi = -1e308, big = 0.0;
+  for (int i = tid; i < n; i += kFitThreads) {
+    const double d = diag[i];
+    const double el = i > 0 ? fabs(sub[i - 1]) : 0.0, er = i + 1 < n ? fabs(sub[i]) : 0.0;
+    sd[i] = d;
+    se2[i] = el * el;
+    lo = fmin(lo, d - (el + er));
+    hi = fmax(hi, d + (el + er));
+    big = fmax(big, el * el);
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    lo = fmin(lo, __shfl_xor(lo, o));
+    hi = fmax(hi, __shfl_xor(hi, o));
+    big = fmax(big, __shfl_xor(big, o));
+  }
+  if (lane == 0) {
+    red[0][wv] = lo;
+    red[1][wv] = hi;
+    red[2][wv] = big;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    lo = fmin(lo, red[0][w]);
+    hi = fmax(hi, red[1][w]);
+    big = fmax(big, red[2][w]);
+  }
+  const double bound = fmax(fabs(lo), fabs(hi));
+  const double pivmin = 2.2250738585072014e-308 * fmax(1.0, big);
+  const double slack = 4.0 * kFitEps * bound * n + 2.0 * pivmin;
+  const int r = blockIdx.x;
+  if (r == 0 && tid == 0) norm[0] = bound;
+  const int below = n - 1 - r;   // eigenvalues smaller than the wanted one
+  double a = lo - slack, b = hi + slack;
+  for (int pass = 0; pass < kFitPasses; ++pass) {
+    const double w = b - a;   // the same in every thread
+    if (!(w > 2.0 * kFitEps * fmax(fabs(a), fabs(b)) + 2.0 * pivmin)) break;
+    const double h = w * (1.0 / (kFitThreads + 1));
+    const double x = a + h * double(tid + 1);
+    int count = 0;
+    double q = sd[0] - x;
+    if (fabs(q) <= pivmin) q = -pivmin;
+    count += q < 0.0;
+    for (int i = 1; i < n; ++i) {
+      q = (sd[i] - x) - se2[i] * fit_rcp(q);
+      if (fabs(q) <= pivmin) q = -pivmin;
+      count += q < 0.0;
+    }
+    // shifts with count <= below lie at or under the eigenvalue
+    const unsigned long long under = __ballot(count <= below);
+    if (lane == 0) redi[wv] = __popcll(under);
+    __syncthreads();
+    const int m = (redi[0] + redi[1]) + (redi[2] + redi[3]);   // count rises with the shift
+    __syncthreads();
+    const double na = a + h * double(m);
+    if (m < kFitThreads) b = a + h * double(m + 1);
+    a = m > 0 ? na : a;
+  }
+  if (tid == 0) lam[r] = 0.5 * (a + b);
+}
+
+// start[r] = the first index of r's cluster of close eigenvalues.
+__global__ __launch_bounds__(256) void fit_clusters_kernel(const double* __restrict__ lam,
+                                                           const double* __restrict__ norm,
+                                                           int n_pca, int32_t* __restrict__ start) {
+  __shared__ int32_t s[256];
+  const double tol = kFitCluster * norm[0];
+  int first = 0;
+  for (int r0 = 0; r0 < n_pca; r0 += 256) {
+    const int r = r0 + int(threadIdx.x);
+    s[threadIdx.x] = r < n_pca && r > 0 && lam[r - 1] - lam[r] > tol;
+    __syncthreads();
+    if (threadIdx.x == 0)
+      for (int t = 0; t < 256 && r0 + t < n_pca; ++t) {
+        if (s[t]) first = r0 + t;
+        start[r0 + t] = first;
+      }
+    __syncthreads();
+  }
+}
+
+// A number in [-1, 1) from two indices.
+__device__ __forceinline__ double fit_noise(uint32_t i, uint32_t r) {
+  uint32_t h = i * 0x9E3779B1u ^ (r + 1u) * 0x85EBCA77u;
+  h = (h ^ (h >> 15)) * 0x2C1B3C6Du;
+  h = (h ^ (h >> 12)) * 0x297A2D39u;
+  h ^= h >> 15;
+  return double(int32_t(h)) * (1.0 / 2147483648.0);
+}
+
+// Inverse iteration: row r of Z = the unit eigenvector of T for lam[r]. With
+// `again` it starts from the row that is there and leaves vectors alone in
+// their cluster as they are. The factors of T - x I (multiplier, the three
+// diagonals of U with the main one inverted, the row swaps) and the iterate
+// are in LDS, or for large n in this workgroup's 6 n doubles of `scratch`; one
+// lane runs the recurrences.
+template <bool LDS>
+__global__ __launch_bounds__(64) void fit_vectors_kernel(
+    const double* __restrict__ diag, const double* __restrict__ sub, int n, int n_pca,
+    const double* __restrict__ lam, const double* __restrict__ norm,
+    const int32_t* __restrict__ start, int again, double* __restrict__ scratch,
+    double* __restrict__ Z) {
+  __shared__ double lds[LDS ? 5 * kFitLdsN : 1];
+  __shared__ uint8_t lds_swap[LDS ? kFitLdsN : 1];
+  const int lane = threadIdx.x;
+  double* base = LDS ? lds : scratch + int64_t(blockIdx.x) * 6 * n;
+  double* u0 = base;
+  double* u1 = base + n;
+  double* u2 = base + 2 * n;
+  double* ml = base + 3 * n;
+  double* y = base + 4 * n;
+  uint8_t* swapped = LDS ? lds_swap : reinterpret_cast<uint8_t*>(base + 5 * n);
+  const double tiny = fmax(kFitEps * norm[0], 1e-280);
+  for (int r = blockIdx.x; r < n_pca; r += gridDim.x) {
+    const int first = start[r];
+    const bool alone = first == r && (r + 1 >= n_pca || start[r + 1] != first);
+    if (again && alone) continue;   // whole workgroups
+    // equal eigenvalues of a cluster are told apart by a few roundings of T
+    const double x = lam[r] - double(r - first) * kFitEps * norm[0];
+    for (int i = lane; i < n; i += 64)
+      y[i] = again ? Z[int64_t(r) * n + i] : fit_noise(uint32_t(i), uint32_t(r));
+    if (lane == 0) {
+      // (a, b, 0) is row i as the elimination left it, (c, d, e) row i + 1
+      double a = diag[0] - x, b = n > 1 ? sub[0] : 0.0;
+      for (int i = 0; i + 1 < n; ++i) {
+        const double c = sub[i], d = diag[i + 1] - x, e = i + 2 < n ? sub[i + 1] : 0.0;
+        const bool sw = fabs(c) > fabs(a);
+        double piv = sw ? c : a;
+        if (fabs(piv) < tiny) piv = piv < 0.0 ? -tiny : tiny;
+        const double inv = fit_rcp(piv), m = (sw ? a : c) * inv;
+        const double up = sw ? d : b;
+        u0[i] = inv;
+        u1[i] = up;
+        u2[i] = sw ? e : 0.0;
+        ml[i] = m;
+        swapped[i] = sw;
+        a = (sw ? b : d) - m * up;
+        b = sw ? -m * e : e;
+      }
+      if (fabs(a) < tiny) a = a < 0.0 ? -tiny : tiny;
+      u0[n - 1] = fit_rcp(a);
+      u1[n - 1] = 0.0;
+      u2[n - 1] = 0.0;
+    }
+    __syncthreads();
+    for (int it = 0; it < (again ? 2 : 3); ++it) {
+      if (lane == 0) {
+        double cur = y[0];
+        for (int i = 0; i + 1 < n; ++i) {
+          const double next = y[i + 1];
+          const bool sw = swapped[i] != 0;
+          const double top = sw ? next : cur;
+          y[i] = top;
+          cur = (sw ? cur : next) - ml[i] * top;
+        }
+        double y1 = cur * u0[n - 1], y2 = 0.0;
+        y[n - 1] = y1;
+        for (int i = n - 2; i >= 0; --i) {
+          const double v = (y[i] - u2[i] * y2 - u1[i] * y1) * u0[i];
+          y[i] = v;
+          y2 = y1;
+          y1 = v;
+        }
+      }
+      __syncthreads();
+      double big = 0.0;
+      for (int i = lane; i < n; i += 64) big = fmax(big, fabs(y[i]));
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o));
+      const double s = 1.0 / big;   // keeps the squares in range
+      double n2 = 0.0;
+      for (int i = lane; i < n; i += 64) n2 = fma(y[i] * s, y[i] * s, n2);
+      const double scale = s / sqrt(wave_sum(n2));
+      for (int i = lane; i < n; i += 64) y[i] *= scale;
+      __syncthreads();
+    }
+    for (int i = lane; i < n; i += 64) Z[int64_t(r) * n + i] = y[i];
+    __syncthreads();
+  }
+}
+
+// Orthonormalises the rows of Z of every cluster of two or more, in order:
+// each is freed of the earlier ones twice (the second time removes what
+// rounding left of the first) and scaled to length one. One workgroup per
+// cluster.
+__global__ __launch_bounds__(kFitThreads) void fit_orthogonal_kernel(
+    double* __restrict__ Z, int n, int n_pca, const int32_t* __restrict__ start) {
+  __shared__ double y[4096], coef[4096];
+  __shared__ double red[4];
+  const int first = blockIdx.x;
+  if (start[first] != first) return;
+  int last = first;
+  while (last + 1 < n_pca && start[last + 1] == first) ++last;
+  if (last == first) return;
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  for (int j = first; j <= last; ++j) {
+    double* __restrict__ zj = Z + int64_t(j) * n;
+    for (int i = tid; i < n; i += kFitThreads) y[i] = zj[i];
+    __syncthreads();
+    for (int pass = 0; pass < 2; ++pass) {
+      for (int q = first + wv; q < j; q += kFitThreads / 64) {
+        const double* zq = Z + int64_t(q) * n;
+        double s = 0.0;
+        for (int i = lane; i < n; i += 64) s = fma(zq[i], y[i], s);
+        s = wave_sum(s);
+        if (lane == 0) coef[q - first] = s;
+      }
+      __syncthreads();
+      for (int i = tid; i < n; i += kFitThreads) {
+        double v = y[i];
+        for (int q = first; q < j; ++q) v = fma(-coef[q - first], Z[int64_t(q) * n + i], v);
+        y[i] = v;
+      }
+      __syncthreads();
+    }
+    double n2 = 0.0;
+    for (int i = tid; i < n; i += kFitThreads) n2 = fma(y[i], y[i], n2);
+    const double scale = 1.0 / sqrt(block_sum(n2, red));
+    for (int i = tid; i < n; i += kFitThreads) zj[i] = y[i] * scale;
+    __syncthreads();
+  }
+}
+
+// Column r of U = H_0 H_1 ... H_{n-2} applied to row r of Z, its sign fixed by
+// its entry of largest magnitude (ties: lowest row). One workgroup of WAVES
+// waves per vector, 16 entries per lane in registers; the next reflector is
+// loaded while the current one is applied.
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void fit_back_kernel(
+    const double* __restrict__ Z, const double* __restrict__ Vh, const double* __restrict__ tau,
+    const double* __restrict__ lam, int n, int n_pca, float* __restrict__ U,
+    double* __restrict__ sv) {
+  constexpr int NT = 64 * WAVES, EPT = 16;
+  __shared__ double red[2][WAVES];
+  __shared__ int redi[WAVES];
+  const int r = blockIdx.x, tid = threadIdx.x;
+  double y[EPT], v[EPT], vn[EPT];
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) y[e] = e * NT + tid < n ? Z[int64_t(r) * n + e * NT + tid] : 0.0;
+  auto load = [&](double (&w)[EPT], int k) {
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      const int j = e * NT + tid;
+      w[e] = j > k && j < n ? Vh[int64_t(k) * n + j] : 0.0;
+    }
+  };
+  load(v, n - 1);
+  for (int k = n - 1; k >= 0; --k) {
+    if (k > 0) load(vn, k - 1);
+    double s = 0.0;
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) s = fma(v[e], y[e], s);
+    s = wave_sum(s);
+    if constexpr (WAVES > 1) {
+      if ((tid & 63) == 0) red[k & 1][tid >> 6] = s;
+      __syncthreads();
+      s = 0.0;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) s += red[k & 1][w];
+    }
+    s *= tau[k];
+#pragma unroll
+    for (int e = 0; e < EPT; ++e) {
+      y[e] = fma(-s, v[e], y[e]);
+      v[e] = vn[e];
+    }
+  }
+  double best = -1.0, val = 0.0;
+  int at = 0x7FFFFFFF;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    const int j = e * NT + tid;
+    if (j < n && fabs(y[e]) > best) {
+      best = fabs(y[e]);
+      val = y[e];
+      at = j;
+    }
+  }
+  auto take = [&](double b, double w, int a) {
+    if (b > best || (b == best && a < at)) {
+      best = b;
+      val = w;
+      at = a;
+    }
+  };
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const double b = __shfl_xor(best, o), w = __shfl_xor(val, o);
+    take(b, w, __shfl_xor(at, o));
+  }
+  if constexpr (WAVES > 1) {
+    __syncthreads();
+    if ((tid & 63) == 0) {
+      red[0][tid >> 6] = best;
+      red[1][tid >> 6] = val;
+      redi[tid >> 6] = at;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) take(red[0][w], red[1][w], redi[w]);
+  }
+  const double sgn = val < 0.0 ? -1.0 : 1.0;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) {
+    const int j = e * NT + tid;
+    if (j < n) U[int64_t(j) * n_pca + r] = float(sgn * y[e]);
+  }
+  if (sv != nullptr && tid == 0) sv[r] = sqrt(lam[r] > 0.0 ? lam[r] : 0.0);
+}
+
+}  // namespace sorf
+
+using namespace sorf;
+
+// Four n x n matrices (G, later the scratch of the inverse iteration; A; the
+// reflectors; the vectors of T) and a few vectors.
+static size_t fit_align(size_t b) { return (b + 255) & ~size_t(255); }
+
+constexpr int kFitScratchGroups = 64;   // workgroups of the inverse iteration outside LDS
+
+static size_t fit_g_bytes(size_t n) {
+  const size_t g = 8 * n * n, s = 8 * 6 * n * kFitScratchGroups;
+  return fit_align(int(n) > kFitLdsN && s > g ? s : g);
+}
+
+size_t sorf_fit_ws_bytes(int32_t d_rep) {
+  const size_t n = size_t(d_rep);
+  return fit_g_bytes(n) + 3 * fit_align(8 * n * n) + 6 * fit_align(8 * n) + fit_align(8) +
+         fit_align(4 * n);
+}
+
+hipError_t sorf_launch_projection_fit(int64_t n_samples, int32_t d_rep, const float* sample,
+                                      int32_t n_pca, float* U, double* sv, void* ws,
+                                      hipStream_t st) {
+  const int n = d_rep;
+  char* p = static_cast<char*>(ws);
+  auto part = [&](size_t bytes) {
+    char* q = p;
+    p += fit_align(bytes);
+    return q;
+  };
+  const size_t mat = 8 * size_t(n) * n, vec = 8 * size_t(n);
+  double* G = reinterpret_cast<double*>(part(fit_g_bytes(size_t(n))));
+  double* A = reinterpret_cast<double*>(part(mat));
+  double* Vh = reinterpret_cast<double*>(part(mat));
+  double* Z = reinterpret_cast<double*>(part(mat));
+  double* pv[2];
+  pv[0] = reinterpret_cast<double*>(part(vec));
+  pv[1] = reinterpret_cast<double*>(part(vec));
+  double* tau = reinterpret_cast<double*>(part(vec));
+  double* diag = reinterpret_cast<double*>(part(vec));
+  double* sub = reinterpret_cast<double*>(part(vec));
+  double* lam = reinterpret_cast<double*>(part(vec));
+  double* norm = reinterpret_cast<double*>(part(8));
+  int32_t* start = reinterpret_cast<int32_t*>(part(4 * size_t(n)));
+
+  hipError_t err = sorf_launch_fill(reinterpret_cast<float*>(G), 2 * int64_t(n) * n, 0.0f, st);
+  if (err != hipSuccess) return err;
+  err = sorf_launch_gram_f64(n_samples, n, sample, nullptr, G, nullptr, st);
+  if (err != hipSuccess) return err;
+  const int64_t nn = int64_t(n) * n;
+  hipLaunchKernelGGL(fit_init_kernel, dim3(unsigned((nn + 255) / 256)), dim3(256), 0, st, G, n, A);
+  constexpr int rows = kFitThreads / 64;   // one per wave
+  for (int k = 0; k < n; ++k) {
+    const int left = n - 1 - k;
+    const dim3 grid(unsigned(left > 0 ? (left + rows - 1) / rows : 1));
+    if (n <= 1024)
+      hipLaunchKernelGGL(fit_column_kernel<1024>, grid, dim3(kFitThreads), 0, st, A, n, k,
+                         pv[k & 1], pv[(k + 1) & 1], Vh, tau, diag, sub);
+    else
+      hipLaunchKernelGGL(fit_column_kernel<4096>, grid, dim3(kFitThreads), 0, st, A, n, k,
+                         pv[k & 1], pv[(k + 1) & 1], Vh, tau, diag, sub);
+  }
+  const dim3 each{unsigned(n_pca)};
+  if (n <= 1024)
+    hipLaunchKernelGGL(fit_bisect_kernel<1024>, each, dim3(kFitThreads), 0, st, diag, sub, n,
+                       n_pca, lam, norm);
+  else
+    hipLaunchKernelGGL(fit_bisect_kernel<4096>, each, dim3(kFitThreads), 0, st, diag, sub, n,
+                       n_pca, lam, norm);
+  hipLaunchKernelGGL(fit_clusters_kernel, dim3(1), dim3(256), 0, st, lam, norm, n_pca, start);
+  // once for every vector, twice more for the vectors of clusters
+  for (int round = 0; round < 3; ++round) {
+    if (n <= kFitLdsN)
+      hipLaunchKernelGGL(fit_vectors_kernel<true>, each, dim3(64), 0, st, diag, sub, n, n_pca,
+                         lam, norm, start, int(round > 0), G, Z);
+    else
+      hipLaunchKernelGGL(fit_vectors_kernel<false>,
+                         dim3(unsigned(n_pca < kFitScratchGroups ? n_pca : kFitScratchGroups)),
+                         dim3(64), 0, st, diag, sub, n, n_pca, lam, norm, start, int(round > 0),
+                         G, Z);
+    hipLaunchKernelGGL(fit_orthogonal_kernel, each, dim3(kFitThreads), 0, st, Z, n, n_pca, start);
+  }
+  if (n <= 1024)
+    hipLaunchKernelGGL(fit_back_kernel<1>, each, dim3(64), 0, st, Z, Vh, tau, lam, n, n_pca, U, sv);
+  else
+    hipLaunchKernelGGL(fit_back_kernel<4>, each, dim3(256), 0, st, Z, Vh, tau, lam, n, n_pca, U,
+                       sv);
+  return hipGetLastError();
+}

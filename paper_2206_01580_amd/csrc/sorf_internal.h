@@ -302,7 +302,7 @@ size_t sorf_project_ws_bytes(int64_t n_atoms, int32_t n_elements);
 hipError_t sorf_launch_project(int64_t n_atoms, int32_t d_rep, const float* rho,
                                const int32_t* element, int32_t n_elements, const float* U,
                                int32_t d, float* x, void* ws, hipStream_t s);
-// Fit of one element's projection: top n_pca eigenvectors of sum rho^T rho (FP64 Jacobi).
+// Fit of one element's projection: top n_pca eigenpairs of sum rho^T rho (FP64).
 size_t sorf_fit_ws_bytes(int32_t d_rep);
 hipError_t sorf_launch_projection_fit(int64_t n_samples, int32_t d_rep, const float* sample,
                                       int32_t n_pca, float* U, double* sv, void* ws, hipStream_t s);

@@ -205,157 +205,6 @@ __global__ __launch_bounds__(256) void proj_gemm_kernel(
     }
 }
 
-// ---------------------------------------------------------------------------
-// Fit of one element's projection (SORF subsection: Z~_e = U_e S_e V_e^T over
-// sampled representations, U_e^{N_PCA} its first N_PCA columns). The left
-// singular vectors of Z~_e are the eigenvectors of G = Z~_e Z~_e^T = sum over
-// the sampled rows of rho^T rho (d_rep x d_rep), and the singular values the
-// square roots of its eigenvalues. G is formed in FP64 by the FP64 Gram kernel;
-// its eigenvectors come from the cyclic Jacobi method in FP64 with the
-// round-robin ordering, which rotates m / 2 disjoint index pairs at a time
-// (m = d_rep rounded up to even; a padded zero row and column is never
-// rotated). A step computes every pair's rotation from the diagonal 2 x 2
-// blocks of A and applies all of them at once: the (a, b) block of the new
-// A is R_a^T A_ab R_b, so one thread per block needs nothing from the others
-// (A is double-buffered), and V = V R in place. After each sweep (m - 1 steps)
-// one block sums the squared off-diagonal entries directly (not as a
-// difference of totals, which cancels) and stops the iteration once they are
-// below 1e-30 of the total, or after kFitMaxSweeps sweeps.
-// ---------------------------------------------------------------------------
-constexpr int kFitMaxSweeps = 15;
-
-__device__ __forceinline__ void fit_pair(int a, int k, int m, int& p, int& q) {
-  // slot 0 keeps player 0; the other players rotate by one slot per step
-  auto player = [&](int slot) { return slot == 0 ? 0 : 1 + (slot - 1 + k) % (m - 1); };
-  const int u = player(a), v = player(m - 1 - a);
-  p = u < v ? u : v;
-  q = u < v ? v : u;
-}
-
-// rotation (c, s) with J = [[c, s], [-s, c]] on (p, q) that zeroes (J^T A J)_pq
-__device__ __forceinline__ void fit_rotation(const double* __restrict__ A, int m, int p, int q,
-                                             double& c, double& s) {
-  const double apq = A[int64_t(p) * m + q];
-  if (apq == 0.0) {
-    c = 1.0;
-    s = 0.0;
-    return;
-  }
-  const double tau = (A[int64_t(q) * m + q] - A[int64_t(p) * m + p]) / (2.0 * apq);
-  const double t = (tau >= 0.0 ? 1.0 : -1.0) / (fabs(tau) + sqrt(1.0 + tau * tau));
-  c = 1.0 / sqrt(1.0 + t * t);
-  s = t * c;
-}
-
-// A (m x m) = the symmetric matrix whose lower triangle is G (n x n), zero-padded;
-// V = I; done = 0
-__global__ __launch_bounds__(256) void fit_init_kernel(const double* __restrict__ G, int n, int m,
-                                                       double* __restrict__ A,
-                                                       double* __restrict__ V,
-                                                       int32_t* __restrict__ done) {
-  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (t >= int64_t(m) * m) return;
-  const int i = int(t / m), j = int(t % m);
-  double v = 0.0;
-  if (i < n && j < n) v = i >= j ? G[int64_t(i) * n + j] : G[int64_t(j) * n + i];
-  A[t] = v;
-  V[t] = i == j ? 1.0 : 0.0;
-  if (t == 0) *done = 0;
-}
-
-__global__ __launch_bounds__(256) void fit_step_kernel(const double* __restrict__ Ain,
-                                                       double* __restrict__ Aout,
-                                                       double* __restrict__ V, int m, int k,
-                                                       const int32_t* __restrict__ done) {
-  if (*done) return;
-  const int h = m / 2;
-  const int64_t t = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  const int64_t nblk = int64_t(h) * h;
-  if (t < nblk) {
-    const int a = int(t / h), b = int(t % h);
-    int pa, qa, pb, qb;
-    fit_pair(a, k, m, pa, qa);
-    fit_pair(b, k, m, pb, qb);
-    double ca, sa, cb, sb;
-    fit_rotation(Ain, m, pa, qa, ca, sa);
-    fit_rotation(Ain, m, pb, qb, cb, sb);
-    const double x = Ain[int64_t(pa) * m + pb], y = Ain[int64_t(pa) * m + qb];
-    const double z = Ain[int64_t(qa) * m + pb], w = Ain[int64_t(qa) * m + qb];
-    const double x1 = x * cb - y * sb, y1 = x * sb + y * cb;
-    const double z1 = z * cb - w * sb, w1 = z * sb + w * cb;
-    Aout[int64_t(pa) * m + pb] = ca * x1 - sa * z1;
-    Aout[int64_t(pa) * m + qb] = ca * y1 - sa * w1;
-    Aout[int64_t(qa) * m + pb] = sa * x1 + ca * z1;
-    Aout[int64_t(qa) * m + qb] = sa * y1 + ca * w1;
-  } else if (t < nblk + int64_t(m) * h) {
-    const int64_t u = t - nblk;
-    const int i = int(u / h), a = int(u % h);
-    int p, q;
-    fit_pair(a, k, m, p, q);
-    double c, s;
-    fit_rotation(Ain, m, p, q, c, s);
-    const double vp = V[int64_t(i) * m + p], vq = V[int64_t(i) * m + q];
-    V[int64_t(i) * m + p] = vp * c - vq * s;
-    V[int64_t(i) * m + q] = vp * s + vq * c;
-  }
-}
-
-// end of a sweep: stop when the off-diagonal mass is negligible (or on the last sweep)
-__global__ __launch_bounds__(1024) void fit_check_kernel(const double* __restrict__ A, int m,
-                                                         int last, int32_t* __restrict__ done,
-                                                         double* __restrict__ lam) {
-  __shared__ double so[1024], st[1024];
-  if (*done) return;
-  double off = 0.0, tot = 0.0;
-  for (int64_t t = threadIdx.x; t < int64_t(m) * m; t += 1024) {
-    const double v = A[t];
-    tot += v * v;
-    if (t / m != t % m) off += v * v;
-  }
-  so[threadIdx.x] = off;
-  st[threadIdx.x] = tot;
-  __syncthreads();
-  for (int w = 512; w > 0; w >>= 1) {
-    if (int(threadIdx.x) < w) {
-      so[threadIdx.x] += so[threadIdx.x + w];
-      st[threadIdx.x] += st[threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  const bool stop = last || so[0] <= 1e-30 * st[0];
-  if (stop) {
-    for (int i = threadIdx.x; i < m; i += 1024) lam[i] = A[int64_t(i) * m + i];
-  }
-  __syncthreads();
-  if (stop && threadIdx.x == 0) *done = 1;
-}
-
-// column r of U = eigenvector of the r-th largest eigenvalue (ties: lower index
-// first), sign fixed by its largest-magnitude entry (ties: lower row first)
-__global__ __launch_bounds__(256) void fit_select_kernel(const double* __restrict__ lam,
-                                                         const double* __restrict__ V, int n,
-                                                         int m, int n_pca, float* __restrict__ U,
-                                                         double* __restrict__ sv) {
-  const int i = int(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const double li = lam[i];
-  int rank = 0;
-  for (int j = 0; j < n; ++j) rank += (lam[j] > li || (lam[j] == li && j < i)) ? 1 : 0;
-  if (rank >= n_pca) return;
-  int piv = 0;
-  double best = -1.0;
-  for (int r = 0; r < n; ++r) {
-    const double a = fabs(V[int64_t(r) * m + i]);
-    if (a > best) {
-      best = a;
-      piv = r;
-    }
-  }
-  const double sgn = V[int64_t(piv) * m + i] < 0.0 ? -1.0 : 1.0;
-  for (int r = 0; r < n; ++r) U[int64_t(r) * n_pca + rank] = float(sgn * V[int64_t(r) * m + i]);
-  if (sv != nullptr) sv[rank] = sqrt(li > 0.0 ? li : 0.0);
-}
-
 }  // namespace sorf
 
 using namespace sorf;
@@ -404,55 +253,5 @@ hipError_t sorf_launch_project(int64_t n_atoms, int32_t d_rep, const float* rho,
   else
     hipLaunchKernelGGL(proj_gemm_kernel<false>, grid, dim3(256), 0, st, rho, d_rep, U, d, E, off,
                        tiles, perm, x);
-  return hipGetLastError();
-}
-
-size_t sorf_fit_ws_bytes(int32_t d_rep) {
-  auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
-  const size_t n = size_t(d_rep), m = n + (n & 1);
-  return al(8 * n * n) + 3 * al(8 * m * m) + al(8 * m) + al(4);
-}
-
-hipError_t sorf_launch_projection_fit(int64_t n_samples, int32_t d_rep, const float* sample,
-                                      int32_t n_pca, float* U, double* sv, void* ws,
-                                      hipStream_t st) {
-  auto al = [](size_t b) { return (b + 255) & ~size_t(255); };
-  const int n = d_rep, m = d_rep + (d_rep & 1);
-  char* p = static_cast<char*>(ws);
-  double* G = reinterpret_cast<double*>(p);
-  p += al(8 * size_t(n) * n);
-  double* A[2];
-  A[0] = reinterpret_cast<double*>(p);
-  p += al(8 * size_t(m) * m);
-  A[1] = reinterpret_cast<double*>(p);
-  p += al(8 * size_t(m) * m);
-  double* V = reinterpret_cast<double*>(p);
-  p += al(8 * size_t(m) * m);
-  double* lam = reinterpret_cast<double*>(p);
-  p += al(8 * size_t(m));
-  int32_t* done = reinterpret_cast<int32_t*>(p);
-
-  hipError_t err = sorf_launch_fill(reinterpret_cast<float*>(G), 2 * int64_t(n) * n, 0.0f, st);
-  if (err != hipSuccess) return err;
-  err = sorf_launch_gram_f64(n_samples, n, sample, nullptr, G, nullptr, st);
-  if (err != hipSuccess) return err;
-  const int64_t mm = int64_t(m) * m;
-  hipLaunchKernelGGL(fit_init_kernel, dim3(unsigned((mm + 255) / 256)), dim3(256), 0, st, G, n,
-                     m, A[0], V, done);
-  const int h = m / 2;
-  const int64_t threads = int64_t(h) * h + int64_t(m) * h;
-  const dim3 sgrid(unsigned((threads + 255) / 256));
-  int cur = 0;
-  for (int sweep = 0; sweep < kFitMaxSweeps; ++sweep) {
-    for (int k = 0; k < m - 1; ++k) {
-      hipLaunchKernelGGL(fit_step_kernel, sgrid, dim3(256), 0, st, A[cur], A[cur ^ 1], V, m, k,
-                         done);
-      cur ^= 1;
-    }
-    hipLaunchKernelGGL(fit_check_kernel, dim3(1), dim3(1024), 0, st, A[cur], m,
-                       int(sweep == kFitMaxSweeps - 1), done, lam);
-  }
-  hipLaunchKernelGGL(fit_select_kernel, dim3(unsigned((n + 255) / 256)), dim3(256), 0, st, lam, V,
-                     n, m, n_pca, U, sv);
   return hipGetLastError();
 }
