@@ -62,7 +62,9 @@ typedef enum {
 } sorf_status;
 
 typedef enum {
-  SORF_GRAM_FP32 = 0,        /* FP32 operands, FP32 MFMA, FP32 accumulation */
+  SORF_GRAM_FP32 = 0,        /* FP32 operands, FP32 accumulation; the products on the FP32
+                                matrix cores, or for large systems as six bf16 products of
+                                the operands' exact three-part splits (same accuracy) */
   SORF_GRAM_BF16 = 1,        /* one bf16 product hi^T hi, FP32 accumulation */
   SORF_GRAM_FP16 = 2,        /* one fp16 product hi^T hi, FP32 accumulation */
   SORF_GRAM_BF16_HILO = 3,   /* (hi + lo)^T (hi + lo), four bf16 products, hi = bf16(z),
@@ -253,9 +255,11 @@ sorf_status sorf_fchl19_backward(const float* R, const int32_t* element, const i
                                  sorf_stream_t stream);
 
 /* Bytes of workspace sorf_gram_accumulate needs for n_rows rows of D features in the given
- * precision (host-only query): the FP32 mode needs only the Z^T y partials (D * 8 bytes per
- * 1024 rows); the 16-bit modes also hold Z packed once in matrix-core fragment order
- * (2 bytes per entry per part, rows padded to 32 and columns to 256). 0 for invalid sizes. */
+ * precision (host-only query): the Z^T y partials (D * 8 bytes per 1024 rows) and the partial
+ * tiles of row slices; the 16-bit modes also hold Z packed once in matrix-core fragment order
+ * (2 bytes per entry per part, rows padded to 64 and columns to 256), and the FP32 mode three
+ * bf16 parts of up to 2 GB of it at a time when there are at least 512 rows and 1024 columns.
+ * 0 for invalid sizes. */
 size_t sorf_gram_workspace_bytes(int64_t n_rows, int32_t D, sorf_gram_precision precision);
 
 /* Normal-equation accumulation (RFF subsection, regularised normal equation):

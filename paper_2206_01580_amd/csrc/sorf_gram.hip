@@ -54,8 +54,9 @@ typedef int i32x16 __attribute__((ext_vector_type(16)));
 // Modes 0..5 are the public precisions. The split mode (FP64 output) runs two
 // internal ones: kSplitHead, the integer head products on int8 matrix cores,
 // and kSplitCross, the three fp16 products that involve the tail.
+// kFP32Parts is the FP32 mode on the bf16 matrix cores (gram_parts_kernel).
 enum GramMode { kFP32 = 0, kBF16 = 1, kFP16 = 2, kBF16HiLo = 3, kFP16HiLo = 4, kFP32Kahan = 5,
-                kSplitCross = 6, kSplitHead = 7 };
+                kSplitCross = 6, kSplitHead = 7, kFP32Parts = 8 };
 
 constexpr int KB = 16;                 // rows per fragment / FP32 stage
 constexpr int TM = 256, TN = 128;      // workgroup tile
@@ -70,7 +71,9 @@ constexpr int kFP32StageRows = 32;
 __host__ __device__ constexpr bool is_hilo(int mode) {
   return mode == kBF16HiLo || mode == kFP16HiLo || mode == kSplitCross;
 }
-__host__ __device__ constexpr bool is_bf(int mode) { return mode == kBF16 || mode == kBF16HiLo; }
+__host__ __device__ constexpr bool is_bf(int mode) {
+  return mode == kBF16 || mode == kBF16HiLo || mode == kFP32Parts;
+}
 
 // round-to-nearest-even conversions, returned as raw 16-bit patterns
 __device__ __forceinline__ unsigned short to_bf16_bits(float f) {
@@ -93,6 +96,23 @@ __device__ __forceinline__ void split(float z, unsigned short& hi, unsigned shor
     hi = __builtin_bit_cast(unsigned short, h);
     lo = __builtin_bit_cast(unsigned short, l);
   }
+}
+
+// z = hi + mid + low in bf16, exactly: each part takes the next eight bits of
+// the significand (rounded to nearest, so the rest has at most 24 - 8 and then
+// 24 - 16 bits left). Holds for entries inside outside_parts' range.
+__device__ __forceinline__ void split3(float z, unsigned short& hi, unsigned short& mid,
+                                       unsigned short& low) {
+  hi = to_bf16_bits(z);
+  const float r = z - from_bf16_bits(hi);
+  mid = to_bf16_bits(r);
+  low = to_bf16_bits(r - from_bf16_bits(mid));
+}
+// Entries whose parts would overflow or lose bits to underflow, infinities and
+// NaN: |z| >= 2^126 or 0 < |z| < 2^-100.
+__device__ __forceinline__ bool outside_parts(float z) {
+  const uint32_t a = __float_as_uint(z) & 0x7FFFFFFFu;
+  return a >= 0x7E800000u || (a != 0u && a < 0x0D800000u);
 }
 
 template <int MODE>
@@ -127,12 +147,15 @@ __host__ __device__ inline int64_t gram_super_tiles(int64_t D) {
   return nS * (nS + 1) / 2;
 }
 
-__device__ __forceinline__ bool super_tile(int64_t b, int64_t D, int64_t nI, int64_t nJ,
+// Super-tile of block b in this dealing.
+__host__ __device__ inline int64_t block_super(int64_t b) {
+  return (b / 8 / (SR_T * SC_T)) * 8 + b % 8;
+}
+
+// Tile (I, J) at position pos of super-tile G.
+__device__ __forceinline__ bool super_tile(int64_t G, int pos, int64_t D, int64_t nI, int64_t nJ,
                                            int64_t& I, int64_t& J) {
   const int64_t nS = (D + SR_T * TM - 1) / (SR_T * TM);
-  const int64_t q = b / 8;
-  const int64_t G = (q / (SR_T * SC_T)) * 8 + b % 8;
-  const int pos = int(q % (SR_T * SC_T));
   const int64_t off = nS * (nS - 1) / 2;
   int64_t R, C;
   if (G < off) {
@@ -154,19 +177,32 @@ __device__ __forceinline__ bool super_tile(int64_t b, int64_t D, int64_t nI, int
 // Row slices of the 256 x 128 tile kernels. One workgroup fills a compute
 // unit, so a launch of n_tiles tiles runs in ceil(n_tiles / 256) rounds; at
 // D = 8192 (1056 tiles) the fifth round holds 32 tiles and a fifth of the
-// launch leaves most of the chip idle. Splitting the rows of every tile into
-// n_split slices makes n_split * n_tiles shorter items (8448 at D = 8192, 33
-// whole rounds). Slice sp covers rows [sp * rows_per, (sp + 1) * rows_per) and
-// is dealt blocks [sp * grid1, (sp + 1) * grid1), each slice in the super-tile
-// order, so the slices run one after another and neighbouring tiles of one
-// slice share their panels in an XCD's L2. With n_split > 1 each item writes
-// its 256 x 128 sum to a partial tile and gram_slices_combine_kernel adds the
-// n_split partials of every entry into G in slice order (deterministic).
+// launch leaves most of the chip idle, and below D = 4096 there are fewer
+// tiles than compute units (and fewer super-tiles than XCDs). Splitting the
+// rows of every tile into n_split slices makes n_split * n_tiles shorter
+// items. Slice sp covers rows [sp * rows_per, (sp + 1) * rows_per). The
+// super-tiles of all slices are dealt to the XCDs in one sequence, slice by
+// slice, so every XCD gets its share of each and neighbouring tiles of one
+// slice still share their panels in an XCD's L2. With n_split > 1 each item
+// writes its 256 x 128 sum to a partial tile and gram_slices_combine_kernel
+// adds the n_split partials of every entry into G in slice order
+// (deterministic).
 struct SlicePlan {
   int32_t n_split;    // row slices per tile (1: items add into G themselves)
   int64_t rows_per;   // rows per slice, a multiple of the flush block
-  int64_t grid1;      // blocks per slice
+  int64_t n_super;    // super-tiles per slice
 };
+__host__ inline unsigned slice_grid(const SlicePlan& p) {
+  return unsigned((p.n_split * p.n_super + 7) / 8 * 8 * SR_T * SC_T);
+}
+// Slice and tile of block b; false for slots without a tile.
+__device__ __forceinline__ bool sliced_tile(int64_t b, const SlicePlan& plan, int64_t D, int64_t nI,
+                                            int64_t nJ, int64_t& sp, int64_t& I, int64_t& J) {
+  const int64_t g = block_super(b);
+  sp = g / plan.n_super;
+  return sp < plan.n_split &&
+         super_tile(g - sp * plan.n_super, int((b / 8) % (SR_T * SC_T)), D, nI, nJ, I, J);
+}
 
 // Index of lower-triangle tile (I, J) of 256 x 128 tiles: row I holds
 // J = 0 .. 2 I + 1, so the rows before it hold I (I + 1) tiles.
@@ -189,7 +225,9 @@ __global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ Z, 
                                                    float zscale, u16x8* __restrict__ hi,
                                                    u16x8* __restrict__ lo,
                                                    const float* __restrict__ y,
-                                                   double* __restrict__ zpart) {
+                                                   double* __restrict__ zpart,
+                                                   u16x8* __restrict__ low = nullptr,
+                                                   int32_t* __restrict__ wide = nullptr) {
   __shared__ float tile[64][kPackLds];
   __shared__ double red[8][128];
   const int tid = threadIdx.x;
@@ -249,7 +287,24 @@ __global__ __launch_bounds__(256) void pack_kernel(const float* __restrict__ Z, 
 #pragma unroll
           for (int j = 0; j < 8; ++j) zacc[cb] += double(v[j]) * double(yv[j]);
         }
-        if constexpr (MODE != kFP32) {
+        if constexpr (MODE == kFP32Parts) {
+          u16x8 h, m, l;
+          bool out = false;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            unsigned short a, b, c;
+            split3(v[j], a, b, c);
+            h[j] = a;
+            m[j] = b;
+            l[j] = c;
+            out |= outside_parts(v[j]);
+          }
+          const int64_t idx = (slab * ncb + blockIdx.x * 4 + cb) * 64 + lane;
+          hi[idx] = h;
+          lo[idx] = m;
+          low[idx] = l;
+          if (out) *wide = 1;
+        } else if constexpr (MODE != kFP32) {
           u16x8 h, l;
 #pragma unroll
           for (int j = 0; j < 8; ++j) {
@@ -493,7 +548,8 @@ void gram_packed_kernel(const u16x8* __restrict__ hi, const u16x8* __restrict__ 
   __shared__ u16x8 ring[NS][NP][NF][64];
 
   int64_t I, J;
-  if (!super_tile(blockIdx.x, D, nI, nJ, I, J)) return;
+  if (!super_tile(block_super(blockIdx.x), int((blockIdx.x / 8) % (SR_T * SC_T)), D, nI, nJ, I, J))
+    return;
   (void)n_tiles;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -641,6 +697,199 @@ void gram_packed_kernel(const u16x8* __restrict__ hi, const u16x8* __restrict__ 
           else
             G[gi * D + gj] += S[a][b][r] * gscale;
         }
+      }
+}
+
+// ------------------------------------------------ FP32 mode on bf16 matrix cores
+// Every FP32 entry is the exact sum of three bf16 parts, z = h + m + l (split3),
+// |m| <= 2^-8 |z| and |l| <= 2^-16 |z|. G takes the six products h h, h m, m h,
+// m m, h l and l h; the three left out are below 2^-23 |z z'| together, one FP32
+// rounding of the product. The sums are the FP32 mode's: 256 rows in a fresh
+// matrix-core accumulator, block sums added in FP32, row slices combined in
+// order. Against FP64 the result is closer than the FP32 matrix cores' (relative
+// Frobenius error at 700 x 1024 1.08e-7 against 1.38e-7, at 3000 x 2048 6.7e-8
+// against 8.8e-8): a bf16 instruction rounds its accumulator once per 16 rows
+// and product, the FP32 one once per 2 rows.
+// Six bf16 products cost 6/16 of one FP32 product at the datasheet rates (2.5 PF
+// against 157 TF), hence the detour; the parts' copies (6 bytes an entry
+// instead of 4) ride under the products. Work split, ring and software pipeline
+// are those of gram_packed_kernel, with 2 stages of 32 rows (144 KB) and twelve
+// fragment reads for 24 products per half-stage. 20,000 x 8192 takes 7.3 ms
+// (kernel 6.9, 1.2 PF of bf16 products; pack 0.32) against 11.1 ms on the FP32
+// matrix cores with the same slices. What bounds it is the rate this chip
+// sustains in long bf16 products (the vendor's 8192^3 product: 1.15 PF): wave
+// priorities, other orders of the products and of the reads change it by 1 %.
+// If any entry is outside the parts' range, `wide` is set by the pack kernel:
+// then this kernel leaves G alone and gram_fp32_ring_kernel runs instead.
+__global__ __launch_bounds__(64 * kPackedWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void gram_parts_kernel(const u16x8* __restrict__ packed, int64_t part_stride, int64_t n_slabs,
+                       int32_t ncb, int32_t D, int64_t n_tiles, int64_t nI, int64_t nJ,
+                       float* __restrict__ G, SlicePlan plan, float* __restrict__ part,
+                       const int32_t* __restrict__ wide) {
+  constexpr int NP = 3;                       // parts per operand
+  constexpr int NW = kPackedWaves;
+  constexpr int AF = 2 * (TM / 32);           // A fragments per stage
+  constexpr int BF = 2 * (TN / 32);           // B fragments per stage
+  constexpr int NF = AF + BF;
+  constexpr int WR = TM / (NW / 2), WC = TN / 2;   // wave tile
+  constexpr int BA = WR / 32, BB = WC / 32;        // 32 x 32 blocks per wave
+  constexpr int NS = 2;                       // ring depth (stages)
+  constexpr int KC = kFlushRows / (2 * KB);   // stages per flush
+  static_assert(NW == 8 && AF == 16 && BF == 8 && BA == 2 && BB == 2, "copies, schedule");
+  __shared__ u16x8 ring[NS][NP][NF][64];
+
+  if (*wide) return;
+  int64_t I, J;
+  int64_t sp;
+  if (!sliced_tile(blockIdx.x, plan, D, nI, nJ, sp, I, J)) return;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wv = tid >> 6;
+  const int wy = wv >> 1, wx = wv & 1;
+  const bool active = I * TM + wy * WR + WR - 1 >= J * TN + wx * WC;
+
+  // Wave w copies, of every part, A fragment w of both slabs and B fragment w.
+  const int64_t srcA = (I * (TM / 32) + wv) * 64 + lane;
+  const int64_t srcB = (int64_t(wv >> 2) * ncb + J * (TN / 32) + (wv & 3)) * 64 + lane;
+  const int64_t slab_stride = int64_t(ncb) * 64;
+  // this item's stages [st0, st0 + n_st): rows_per is a multiple of 256
+  const int64_t all = n_slabs / 2;
+  const int64_t per = plan.n_split > 1 ? plan.rows_per / (2 * KB) : all;
+  const int64_t st0 = sp * per;
+  const int64_t n_st = st0 + per < all ? per : (all > st0 ? all - st0 : 0);
+  const u16x8* base = packed + st0 * 2 * slab_stride;
+  auto issue = [&](int64_t st, int slot) {
+    const u16x8* p = base + st * 2 * slab_stride;
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      dma16(p + srcA, &ring[slot][q][wv][0]);
+      dma16(p + srcA + slab_stride, &ring[slot][q][8 + wv][0]);
+      dma16(p + srcB, &ring[slot][q][AF + wv][0]);
+      p += part_stride;
+    }
+  };
+
+  f32x16 P[BA][BB], S[BA][BB];
+#pragma unroll
+  for (int a = 0; a < BA; ++a)
+#pragma unroll
+    for (int b = 0; b < BB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        P[a][b][r] = 0.0f;
+        S[a][b][r] = 0.0f;
+      }
+  // Fragments of part q for half-stage kk of a slot. The high parts are double
+  // buffered; the middle and low ones are re-read as soon as their last product
+  // of the half-stage has been issued, which keeps the wave in 256 registers.
+  u16x8 ah0[BA], bh0[BB], ah1[BA], bh1[BB], am[BA], bm[BB], al[BA], bl[BB];
+  auto read = [&](int sl, int kk, int q, u16x8 (&a)[BA], u16x8 (&b)[BB]) {
+#pragma unroll
+    for (int i = 0; i < BA; ++i) a[i] = ring[sl][q][kk * (TM / 32) + wy * BA + i][lane];
+#pragma unroll
+    for (int i = 0; i < BB; ++i) b[i] = ring[sl][q][AF + kk * (TN / 32) + wx * BB + i][lane];
+  };
+  auto mma = [&](const u16x8 (&a)[BA], const u16x8 (&b)[BB]) {
+#pragma unroll
+    for (int i = 0; i < BA; ++i)
+#pragma unroll
+      for (int j = 0; j < BB; ++j) P[i][j] = mma16<kFP32Parts>(a[i], b[j], P[i][j]);
+  };
+  // The products of one half-stage (small ones first), and the reads of the
+  // next one (half-stage kk of slot sl) among them.
+  auto half = [&](const u16x8 (&ah)[BA], const u16x8 (&bh)[BB], int sl, int kk,
+                  u16x8 (&an)[BA], u16x8 (&bn)[BB]) {
+    read(sl, kk, 0, an, bn);
+    mma(ah, bl);
+    mma(al, bh);
+    read(sl, kk, 2, al, bl);
+    mma(am, bm);
+    mma(am, bh);
+    mma(ah, bm);
+    read(sl, kk, 1, am, bm);
+    mma(ah, bh);
+    auto both = [] {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+    };
+    both();
+    __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+    both();
+    __builtin_amdgcn_sched_group_barrier(0x008, 8, 0);
+    both();
+  };
+  auto flush = [&] {
+#pragma unroll
+    for (int a = 0; a < BA; ++a)
+#pragma unroll
+      for (int b = 0; b < BB; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          S[a][b][r] += P[a][b][r];
+          P[a][b][r] = 0.0f;
+        }
+  };
+
+#pragma unroll
+  for (int j = 0; j < NS; ++j)
+    if (j < n_st) issue(j, j);
+  if (n_st > 0) {
+    wait_stage<3 * NP>(n_st - 1 < NS - 1 ? n_st - 1 : NS - 1);
+    stage_barrier();
+    read(0, 0, 0, ah0, bh0);
+    read(0, 0, 1, am, bm);
+    read(0, 0, 2, al, bl);
+  }
+  int slot = 0;
+  int64_t s = 0;
+  while (s < n_st) {
+    const int64_t g_end = s + KC < n_st ? s + KC : n_st;
+    for (; s < g_end; ++s) {
+      half(ah0, bh0, slot, 1, ah1, bh1);
+      const bool more = s + 1 < n_st;
+      const int nslot = more ? slot ^ 1 : slot;
+      if (more) {
+        // stage s + 1 has landed, and so have this wave's reads of stage s,
+        // whose slot is filled again
+        wait_vm<0>();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        stage_barrier();
+        if (s + NS < n_st) issue(s + NS, slot);
+      }
+      // after the last stage this re-reads a published slot with no copy in
+      // flight; the values are not used
+      half(ah1, bh1, nslot, 0, ah0, bh0);
+      slot = nslot;
+    }
+    flush();
+  }
+
+  if (!active) return;
+  auto rr = [](int r) { return 8 * (r >> 2) + (r & 3); };
+  if (sp > 0) {
+    float* out = part + ((sp - 1) * n_tiles + tile_index(I, J)) * (TM * TN) +
+                 (wy * WR + 4 * (lane >> 5)) * TN + wx * WC + (lane & 31);
+#pragma unroll
+    for (int a = 0; a < BA; ++a)
+#pragma unroll
+      for (int b = 0; b < BB; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) out[(a * 32 + rr(r)) * TN + b * 32] = S[a][b][r];
+    return;
+  }
+  const int64_t i0 = I * TM + wy * WR + 4 * (lane >> 5), j0 = J * TN + wx * WC + (lane & 31);
+#pragma unroll
+  for (int a = 0; a < BA; ++a)
+#pragma unroll
+    for (int b = 0; b < BB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int64_t gi = i0 + a * 32 + rr(r);
+        const int64_t gj = j0 + b * 32;
+        if (gi < D && gj < D && gi >= gj) G[gi * D + gj] += S[a][b][r];
       }
 }
 
@@ -1081,7 +1330,9 @@ __global__ __launch_bounds__(64 * NW)
 __attribute__((amdgpu_waves_per_eu(HALF ? NW / 2 : NW / 4, HALF ? NW / 2 : NW / 4)))
 void gram_fp32_ring_kernel(const float* __restrict__ Z, int64_t M, int32_t D, int64_t n_tiles,
                            int64_t nI, int64_t nJ, const float* __restrict__ zeros,
-                           float* __restrict__ G, SlicePlan plan, float* __restrict__ part) {
+                           float* __restrict__ G, SlicePlan plan, float* __restrict__ part,
+                           const int32_t* __restrict__ wide) {
+  if (wide != nullptr && !*wide) return;   // gram_parts_kernel has done it
   static_assert(SR == 16 || SR == 32 || SR == 48, "stage rows");
   constexpr int TA = HALF ? TM / 2 : TM;      // A columns (rows of G) per workgroup
   // ring depth: 96, 144, 144 KB of LDS for whole tiles, 64 KB for half tiles
@@ -1102,8 +1353,8 @@ void gram_fp32_ring_kernel(const float* __restrict__ Z, int64_t M, int32_t D, in
   int64_t I, J;
   const int64_t hb = HALF ? (blockIdx.x / 8) & 1 : 0;
   const int64_t bid = HALF ? (blockIdx.x / 16) * 8 + blockIdx.x % 8 : blockIdx.x;
-  const int64_t sp = bid / plan.grid1;
-  if (!super_tile(bid % plan.grid1, D, nI, nJ, I, J)) return;
+  int64_t sp;
+  if (!sliced_tile(bid, plan, D, nI, nJ, sp, I, J)) return;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wv = tid >> 6;
@@ -1268,12 +1519,10 @@ void gram_fp32_ring_kernel(const float* __restrict__ Z, int64_t M, int32_t D, in
 }
 
 // G += the partial tiles of slices 1 .. n_split - 1 of every 256 x 128 tile
-// (slice 0 added its sum into G itself), summed in slice order; in the Kahan
-// mode G and the partials are summed with compensation, so that combining the
-// slices rounds once, as the unsliced kernel's final G += S does. One workgroup
-// per 4 rows of a tile, two columns per thread. Entries of waves above the
-// diagonal are never written to the partials; they are not read.
-template <bool KAHAN>
+// (slice 0 added its sum into G itself), summed in FP64 in slice order, so that
+// combining the slices rounds once, as the unsliced kernel's final G += S does.
+// One workgroup per 4 rows of a tile, two columns per thread. Entries of waves
+// above the diagonal are never written to the partials; they are not read.
 __global__ __launch_bounds__(256) void gram_slices_combine_kernel(const float* __restrict__ part,
                                                                  int64_t n_tiles, int32_t n_split,
                                                                  int32_t D,
@@ -1288,33 +1537,23 @@ __global__ __launch_bounds__(256) void gram_slices_combine_kernel(const float* _
   const int64_t gi = I * TM + i, gj = J * TN + j;
   if (gi >= D || gj > gi) return;
   const bool second = gj + 1 < D && gj + 1 <= gi;
-  if constexpr (KAHAN) {
-    // G (which holds slice 0) and the partials in slice order, compensated
-    float2 sum = make_float2(G[gi * D + gj], second ? G[gi * D + gj + 1] : 0.0f);
-    float2 c = make_float2(0.0f, 0.0f);
-    for (int sp = 1; sp < n_split; ++sp) {
-      const float2 v = *reinterpret_cast<const float2*>(
-          part + (int64_t(sp - 1) * n_tiles + t) * (TM * TN) + int64_t(i) * TN + j);
-      const float yx = v.x - c.x, yy = v.y - c.y;
-      const float tx = sum.x + yx, ty = sum.y + yy;
-      c.x = (tx - sum.x) - yx;
-      c.y = (ty - sum.y) - yy;
-      sum.x = tx;
-      sum.y = ty;
+  double x = G[gi * D + gj], y = second ? G[gi * D + gj + 1] : 0.0;
+  const float* src = part + t * (TM * TN) + int64_t(i) * TN + j;
+  for (int s0 = 1; s0 < n_split; s0 += 8) {
+    float2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      v[u] = s0 + u < n_split ? *reinterpret_cast<const float2*>(
+                                    src + int64_t(s0 + u - 1) * n_tiles * (TM * TN))
+                              : make_float2(0.0f, 0.0f);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      x += v[u].x;
+      y += v[u].y;
     }
-    G[gi * D + gj] = sum.x - c.x;
-    if (second) G[gi * D + gj + 1] = sum.y - c.y;
-  } else {
-    float2 acc = make_float2(0.0f, 0.0f);
-    for (int sp = 1; sp < n_split; ++sp) {
-      const float2 v = *reinterpret_cast<const float2*>(
-          part + (int64_t(sp - 1) * n_tiles + t) * (TM * TN) + int64_t(i) * TN + j);
-      acc.x += v.x;
-      acc.y += v.y;
-    }
-    G[gi * D + gj] += acc.x;
-    if (second) G[gi * D + gj + 1] += acc.y;
   }
+  G[gi * D + gj] = float(x);
+  if (second) G[gi * D + gj + 1] = float(y);
 }
 
 // ------------------------------------------------ FP32 mode, any D
@@ -1333,7 +1572,8 @@ void gram_fp32_kernel(const float* __restrict__ Z, int64_t M, int32_t D, int64_t
   __shared__ float sB[2][KB][LDB];
 
   int64_t I, J;
-  if (!super_tile(blockIdx.x, D, nI, nJ, I, J)) return;
+  if (!super_tile(block_super(blockIdx.x), int((blockIdx.x / 8) % (SR_T * SC_T)), D, nI, nJ, I, J))
+    return;
   (void)n_tiles;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -1547,7 +1787,8 @@ struct GramLayout {
   int64_t chunks;    // Z^T y partial chunks
   size_t part_bytes, zpart_bytes;
 };
-constexpr size_t kZeroBytes = 1024;
+constexpr size_t kZeroBytes = 1024, kFlagBytes = 256;
+constexpr int64_t kPartsMinRows = 512, kPartsMinCols = 1024;
 GramLayout gram_layout(int64_t M, int32_t D) {
   GramLayout g;
   g.n_slabs = ((M + 4 * KB - 1) / (4 * KB)) * 4;
@@ -1575,49 +1816,155 @@ size_t x1_partial_bytes(int64_t n_rows, int32_t D) {
   return al256(b);
 }
 
-// Row-slice plan of the FP32 tile kernel: the slice count in 1..8 with the
-// least estimated time, counted in rounds of 256 items (one per compute unit,
-// each a slice of one tile at the FP32 matrix-core rate) plus the partial
-// tiles' HBM traffic (written once, read once, at 5 TB/s). Ties: fewer
-// slices. Slices keep at least 2048 rows; the partials stay within 4 GB.
-static SlicePlan slice_plan(int64_t M, int32_t D) {
+// Rounds of 32 items that the busiest XCD runs when the super-tiles of n
+// slices are dealt round-robin to the 8 XCDs.
+static double busiest_rounds(int64_t D, int64_t n_super, int64_t n, double tiles) {
+  if (n_super > 64) return std::ceil(tiles * double(n) / kX1Slots);   // even enough
   int64_t nI, nJ;
-  const int64_t T = gram_tiles(D, nI, nJ);
-  const int64_t grid1 = ((gram_super_tiles(D) + 7) / 8) * 8 * SR_T * SC_T;
-  const double tile_s = 2.0 * TM * TN * double(M) / (157.3e12 / kX1Slots);   // whole tile
-  const double part_s = double(TM * TN * sizeof(float)) * 2.0 / 5e12;       // per partial tile
-  SlicePlan best{1, M, grid1};
-  double best_cost = double((T + kX1Slots - 1) / kX1Slots) * tile_s;
-  for (int s = 2; s <= 8; ++s) {
+  gram_tiles(D, nI, nJ);
+  const int64_t nS = (D + SR_T * TM - 1) / (SR_T * TM);
+  int64_t load[8] = {0, 0, 0, 0, 0, 0, 0, 0}, size[64], G = 0;
+  auto count = [&](int64_t R, int64_t C) {   // tiles of super-tile (R, C)
+    int64_t t = 0;
+    for (int64_t I = R * SR_T; I < R * SR_T + SR_T && I < nI; ++I)
+      for (int64_t J = C * SC_T; J < C * SC_T + SC_T && J < nJ && J * TN <= I * TM + TM - 1; ++J) ++t;
+    return t;
+  };
+  for (int64_t R = 1; R < nS; ++R)
+    for (int64_t C = 0; C < R; ++C) size[G++] = count(R, C);
+  for (int64_t R = 0; R < nS; ++R) size[G++] = count(R, R);
+  for (int64_t g = 0; g < n * n_super; ++g) load[g % 8] += size[g % n_super];
+  return std::ceil(double(*std::max_element(load, load + 8)) / (kX1Slots / 8));
+}
+
+// Row-slice plan of the FP32 tile kernels: the slice count in 1..64 with the
+// least estimated time, counted in rounds of one item per compute unit (each a
+// slice of one tile at `rate` flops per second, and 3 us to fill its ring and
+// store its sums) plus the partial tiles' HBM traffic (written once, read
+// once, at 3 TB/s each: what the combine kernel reaches). Ties: fewer slices.
+// Slices keep at least 512 rows (two flush blocks) and, while the partials stay
+// within 4 GB, at most 4096: the slices are combined in FP64, so shorter FP32
+// sums are closer ones (relative error of G at 20,000 x 8192: 7.6e-8 with two
+// slices, 4.4e-8 with five). Against at most 8 slices of at least 2048
+// rows dealt slice by slice from XCD 0 on (which put all tiles of D <= 1024 on
+// one XCD), on the FP32 matrix cores: 20,000 x 1024 0.33 ms instead of 1.71,
+// 20,000 x 4096 3.00 instead of 4.46, 20,000 x 8192 11.1 instead of 12.6.
+constexpr int64_t kSliceMaxRows = 4096;
+constexpr double kRingRate = 157.3e12;    // FP32 matrix cores
+constexpr double kPartsRate = 2.5e15 / 6; // six bf16 products for one
+static SlicePlan slice_plan(int64_t M, int32_t D, double rate) {
+  int64_t nI, nJ;
+  const int64_t T = gram_tiles(D, nI, nJ), n_super = gram_super_tiles(D);
+  const double tile_s = 2.0 * TM * TN * double(M) / (rate / kX1Slots);      // whole tile
+  const double part_s = double(TM * TN * sizeof(float)) * 2.0 / 3e12;       // per partial tile
+  constexpr double item_s = 3e-6;
+  SlicePlan best{1, M, n_super};
+  bool fine = M <= kSliceMaxRows;   // whether `best` has short slices
+  double best_cost = busiest_rounds(D, n_super, 1, double(T)) * (tile_s + item_s);
+  for (int s = 2; s <= 64; ++s) {
     const int64_t rows = ((M + s - 1) / s + kFlushRows - 1) / kFlushRows * kFlushRows;
     const int64_t n = (M + rows - 1) / rows;
-    if (rows < 2048 || size_t(n - 1) * size_t(T) * TM * TN * sizeof(float) > (size_t(4) << 30))
+    if (rows < 2 * kFlushRows || size_t(n - 1) * size_t(T) * TM * TN * sizeof(float) > (size_t(4) << 30))
       break;
-    const double cost = double((T * n + kX1Slots - 1) / kX1Slots) * tile_s * double(rows) / double(M) +
+    const double cost = busiest_rounds(D, n_super, n, double(T)) *
+                            (tile_s * double(rows) / double(M) + item_s) +
                         double((n - 1) * T) * part_s;
-    if (cost < best_cost - 1e-9) {
+    if (!fine || cost < best_cost - 1e-9) {   // long slices give way to any shorter ones
       best_cost = cost;
-      best = SlicePlan{int32_t(n), rows, grid1};
+      best = SlicePlan{int32_t(n), rows, n_super};
+      fine = rows <= kSliceMaxRows;
     }
   }
   return best;
 }
 
-static size_t slice_partial_bytes(int64_t M, int32_t D) {
-  const SlicePlan p = slice_plan(M, D);
+static size_t slice_partial_bytes(const SlicePlan& p, int32_t D) {
   if (p.n_split <= 1) return 0;
   int64_t nI, nJ;
   return al256(size_t(p.n_split - 1) * size_t(gram_tiles(D, nI, nJ)) * TM * TN * sizeof(float));
+}
+
+// FP32 mode on the bf16 matrix cores (gram_parts_kernel) from 512 rows and
+// 1024 columns on. Below that the products are too few to pay for packing the
+// parts: 512 x 1024 takes 86 us against 102 on the FP32 matrix cores and 1024
+// x 1024 118 against 124, but 512 x 512 73 against 64 and 200 x 1024 54
+// against 53.
+static bool use_parts(int64_t M, int32_t D, int mode) {
+  return mode == kFP32 && D % 4 == 0 && M >= kPartsMinRows && D >= kPartsMinCols;
+}
+// Rows of one pass: the packed parts of a pass stay within 2 GB; whole Z^T y
+// chunks, so that Z^T y is summed as in one pass.
+static int64_t parts_rows(int64_t M, int32_t D) {
+  constexpr int64_t chunk = int64_t(KB) * kPackSlabs;
+  const int64_t row = 6 * int64_t(gram_layout(1, D).ncb) * 32;
+  const int64_t most = (int64_t(2) << 30) / row / chunk * chunk;
+  const int64_t rows = most > 2 * chunk ? most : 2 * chunk;
+  if (rows >= M) return M;
+  const int64_t passes = (M + rows - 1) / rows;   // even passes
+  return ((M + passes - 1) / passes + chunk - 1) / chunk * chunk;
 }
 
 size_t sorf_gram_ws_bytes(int64_t n_rows, int32_t D, int mode) {
   if (n_rows <= 0 || D <= 0) return 0;
   const GramLayout g = gram_layout(n_rows, D);
   size_t b = g.zpart_bytes + kZeroBytes;
-  if ((mode == kFP32 || mode == kFP32Kahan) && D % 4 == 0) b += slice_partial_bytes(n_rows, D);
+  if (use_parts(n_rows, D, mode)) {
+    const int64_t rows = parts_rows(n_rows, D);
+    return b + kFlagBytes + slice_partial_bytes(slice_plan(rows, D, kPartsRate), D) +
+           3 * gram_layout(rows, D).part_bytes;
+  }
+  if ((mode == kFP32 || mode == kFP32Kahan) && D % 4 == 0)
+    b += slice_partial_bytes(slice_plan(n_rows, D, kRingRate), D);
   if (mode != kFP32 && mode != kFP32Kahan) b += g.part_bytes * (is_hilo(mode) ? 2 : 1);
   if (mode == kBF16 || mode == kFP16) b += x1_partial_bytes(n_rows, D);
   return b;
+}
+
+// Workspace of the parts path: [Z^T y partials][zeros][flag][slice partials][three parts]
+static hipError_t launch_gram_parts(int64_t M, int32_t D, const float* Z, const float* y, float* G,
+                                    float* Zty, char* w, hipStream_t st) {
+  const GramLayout all = gram_layout(M, D);
+  const int64_t rows = parts_rows(M, D);
+  const SlicePlan most = slice_plan(rows, D, kPartsRate);
+  double* zpart = reinterpret_cast<double*>(w);
+  float* zeros = reinterpret_cast<float*>(w + all.zpart_bytes);
+  int32_t* wide = reinterpret_cast<int32_t*>(w + all.zpart_bytes + kZeroBytes);
+  float* part = reinterpret_cast<float*>(w + all.zpart_bytes + kZeroBytes + kFlagBytes);
+  u16x8* packed = reinterpret_cast<u16x8*>(w + all.zpart_bytes + kZeroBytes + kFlagBytes +
+                                           slice_partial_bytes(most, D));
+  int64_t nI, nJ;
+  const int64_t n_tiles = gram_tiles(D, nI, nJ);
+  const dim3 blk{256};
+  hipError_t e = sorf_launch_fill(zeros, int64_t((kZeroBytes + kFlagBytes) / sizeof(float)), 0.0f, st);
+  if (e != hipSuccess) return e;
+  for (int64_t r0 = 0; r0 < M; r0 += rows) {
+    const int64_t m = rows < M - r0 ? rows : M - r0;
+    const float* Zp = Z + r0 * D;
+    const GramLayout g = gram_layout(m, D);
+    SlicePlan plan = slice_plan(m, D, kPartsRate);
+    if (slice_partial_bytes(plan, D) > slice_partial_bytes(most, D)) plan = SlicePlan{1, m, plan.n_super};
+    const int64_t stride = int64_t(g.part_bytes / sizeof(u16x8));
+    hipLaunchKernelGGL(pack_kernel<kFP32Parts>, dim3(unsigned(g.ncb / 4), unsigned(g.chunks)), blk,
+                       0, st, Zp, m, D, g.n_slabs, g.ncb, 1.0f, packed, packed + stride,
+                       y != nullptr ? y + r0 : nullptr, zpart + (r0 / (KB * kPackSlabs)) * D,
+                       packed + 2 * stride, wide);
+    hipLaunchKernelGGL(gram_parts_kernel, dim3(slice_grid(plan)),
+                       dim3(64 * kPackedWaves), 0, st, packed, stride, g.n_slabs, g.ncb, D, n_tiles,
+                       nI, nJ, G, plan, part, wide);
+    hipLaunchKernelGGL((gram_fp32_ring_kernel<false, kFP32Waves, kFP32StageRows, kFP32Half>),
+                       dim3((kFP32Half ? 2 : 1) * slice_grid(plan)),
+                       dim3(64 * kFP32Waves), 0, st, Zp, m, D, n_tiles, nI, nJ, zeros, G, plan,
+                       part, wide);
+    if (plan.n_split > 1)
+      hipLaunchKernelGGL(gram_slices_combine_kernel,
+                         dim3(unsigned(n_tiles), unsigned(TM / 4)), blk, 0, st, part, n_tiles,
+                         plan.n_split, D, G);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if (y != nullptr)
+    hipLaunchKernelGGL(zty_finalize_kernel<float>, dim3(unsigned((D + 255) / 256)), blk, 0, st,
+                       zpart, all.chunks, D, Zty);
+  return hipGetLastError();
 }
 
 hipError_t sorf_launch_gram(int64_t n_rows, int32_t D, const float* Z, const float* y, int mode,
@@ -1625,6 +1972,7 @@ hipError_t sorf_launch_gram(int64_t n_rows, int32_t D, const float* Z, const flo
   if (n_rows == 0 || D == 0) return hipSuccess;
   const GramLayout g = gram_layout(n_rows, D);
   char* w = static_cast<char*>(ws);
+  if (use_parts(n_rows, D, mode)) return launch_gram_parts(n_rows, D, Z, y, G, Zty, w, st);
   double* zpart = reinterpret_cast<double*>(w);
   float* zeros = reinterpret_cast<float*>(w + g.zpart_bytes);
   u16x8* hi = reinterpret_cast<u16x8*>(w + g.zpart_bytes + kZeroBytes);
@@ -1675,24 +2023,20 @@ hipError_t sorf_launch_gram(int64_t n_rows, int32_t D, const float* Z, const flo
         if ((e = sorf_launch_fill(zeros, int64_t(kZeroBytes / sizeof(float)), 0.0f, st)) !=
             hipSuccess)
           return e;
-        const SlicePlan plan = slice_plan(n_rows, D);
+        const SlicePlan plan = slice_plan(n_rows, D, kRingRate);
         float* part = reinterpret_cast<float*>(w + g.zpart_bytes + kZeroBytes);
-        const dim3 rgrid{unsigned(plan.grid1 * plan.n_split)};
+        const dim3 rgrid{slice_grid(plan)};
         if (mode == kFP32Kahan)
           hipLaunchKernelGGL((gram_fp32_ring_kernel<true, kFP32Waves, kFP32StageRows, kFP32Half>),
                              dim3((kFP32Half ? 2 : 1) * rgrid.x), dim3(64 * kFP32Waves), 0, st, Z,
-                             n_rows, D, n_tiles, nI, nJ, zeros, G, plan, part);
+                             n_rows, D, n_tiles, nI, nJ, zeros, G, plan, part, nullptr);
         else
           hipLaunchKernelGGL((gram_fp32_ring_kernel<false, kFP32Waves, kFP32StageRows, kFP32Half>),
                              dim3((kFP32Half ? 2 : 1) * rgrid.x), dim3(64 * kFP32Waves), 0, st, Z,
-                             n_rows, D, n_tiles, nI, nJ, zeros, G, plan, part);
+                             n_rows, D, n_tiles, nI, nJ, zeros, G, plan, part, nullptr);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        if (plan.n_split > 1 && mode == kFP32Kahan)
-          hipLaunchKernelGGL(gram_slices_combine_kernel<true>,
-                             dim3(unsigned(n_tiles), unsigned(TM / 4)), blk, 0, st, part, n_tiles,
-                             plan.n_split, D, G);
-        else if (plan.n_split > 1)
-          hipLaunchKernelGGL(gram_slices_combine_kernel<false>,
+        if (plan.n_split > 1)
+          hipLaunchKernelGGL(gram_slices_combine_kernel,
                              dim3(unsigned(n_tiles), unsigned(TM / 4)), blk, 0, st, part, n_tiles,
                              plan.n_split, D, G);
       } else if (mode == kFP32Kahan) {

@@ -1,0 +1,87 @@
+"""GPU: the FP32 Gram on three bf16 parts per entry (large systems) and its row
+slices.
+
+Bound of an entry: the six products keep each z z' to 2^-22, and the sums round
+at most 2 (6 * 16 + 8) times per 256-row block, once per block and once per
+slice, so |dG_ij| <= (208 + ceil(M / 256) + 64 + 4) 2^-24 sum_m |z_mi z_mj|, plus
+the rounding of the value that was in G.
+"""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def gram(Z, G0, mode="fp32"):
+    from paper_2206_01580_amd import sorf
+    G = G0.clone()
+    sorf.gram_accumulate(Z, G, precision=mode)
+    return G
+
+
+def check(Z, G, G0):
+    M = len(Z)
+    Zd = Z.double()
+    exact, scale = Zd.T @ Zd, Zd.abs().T @ Zd.abs()
+    bound = (276 + -(-M // 256)) * 2.0 ** -24 * scale + 2.0 ** -22 * G0.abs()
+    diff = (G.double() - G0.double() - exact).abs()
+    assert bool((torch.tril(diff) <= bound).all()), float(torch.tril(diff / bound.clamp_min(1e-300)).max())
+    upper = torch.triu(torch.ones_like(G, dtype=torch.bool), 1)
+    assert torch.equal(G[upper], G0[upper])
+
+
+@pytest.mark.parametrize("mode", ["fp32", "fp32_kahan"])
+@pytest.mark.parametrize("M,D", [(511, 1024), (512, 1020), (512, 1024), (513, 1028), (769, 1156),
+                                 (2049, 1024), (5000, 1284), (20001, 1024), (3000, 4100)])
+def test_edges(mode, M, D):
+    """Both sides of the rule (511 rows, 1020 columns), one row past a flush block or a
+    slice, columns past a tile, one and several super-tiles."""
+    g = torch.Generator(device="cuda").manual_seed(M + D)
+    Z = torch.randn(M, D, device="cuda", generator=g) * torch.exp(4 * torch.rand(D, device="cuda", generator=g) - 2)
+    G0 = torch.randn(D, D, device="cuda", generator=g)
+    G = gram(Z, G0, mode)
+    check(Z, G, G0)
+    assert torch.equal(G, gram(Z, G0, mode))
+
+
+def test_several_passes():
+    """More rows than one pass packs (2 GB of parts), checked on sampled columns."""
+    M, D = 44001, 8192
+    g = torch.Generator(device="cuda").manual_seed(1)
+    Z = torch.randn(M, D, device="cuda", generator=g)
+    y = torch.randn(M, device="cuda", generator=g)
+    G, Zty = torch.zeros(D, D, device="cuda"), torch.zeros(D, device="cuda")
+    from paper_2206_01580_amd import sorf
+    sorf.gram_accumulate(Z, G, y, Zty)
+    cols = torch.randperm(D, device="cuda", generator=g)[:96].sort().values
+    check(Z[:, cols].contiguous(), G[cols][:, cols], torch.zeros(96, 96, device="cuda"))
+    r = Z[:, cols].double().T @ y.double()
+    scale = Z[:, cols].double().abs().T @ y.double().abs()
+    assert bool(((Zty[cols].double() - r).abs() <= 2.0 ** -22 * scale).all())
+
+
+@pytest.mark.parametrize("value", [2.0 ** 126, -3e38, 2.0 ** -101, 1e-40, float("inf"), float("-inf"),
+                                   float("nan")])
+def test_entries_that_have_no_parts(value):
+    """An entry whose parts would overflow, underflow or are no numbers: the FP32 products'
+    result, non-finite values in its row and column of G only."""
+    M, D = 600, 1024
+    g = torch.Generator(device="cuda").manual_seed(7)
+    Z = torch.randn(M, D, device="cuda", generator=g)
+    Z[:, 5] = 0.0
+    Z[311, 5] = value
+    G = gram(Z, torch.zeros(D, D, device="cuda"))
+    row = torch.cat([G[5, :5], G[6:, 5]]).cpu()
+    z = torch.cat([Z[311, :5], Z[311, 6:]]).cpu()
+    with np.errstate(over="ignore"):
+        want = np.float32(value) * z.numpy()   # some products of the large ones overflow
+    if np.isnan(value):
+        assert np.all(np.isnan(row.numpy()))
+    else:
+        fine = np.isfinite(want)
+        tol = 2.0 ** -22 * np.abs(want[fine]) + 2.0 ** -148
+        assert np.all(np.abs(row.numpy()[fine].astype(np.float64) - want[fine]) <= tol)
+        assert np.array_equal(row.numpy()[~fine], want[~fine])
+    keep = torch.arange(D, device="cuda") != 5
+    check(Z[:, keep].contiguous(), G[keep][:, keep].contiguous(), torch.zeros(D - 1, D - 1, device="cuda"))
