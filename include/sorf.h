@@ -146,7 +146,7 @@ size_t sorf_energy_grad_workspace_bytes(int64_t n_atoms);
  * give both its energy share alpha^T z(x_i) and its gradient row.
  *   alpha: [D] FP32.  E: [n_mols] FP32 out, each molecule's atom shares summed in atom
  *   order (as sorf_predict with J: equal to sorf_predict's energies without J to FP32
- *   rounding, not bitwise).  grad_x: [n_atoms][d] FP32 out, the same values as
+ *   rounding, not bitwise; from d = 64 on bitwise those with J).  grad_x: [n_atoms][d] FP32 out, the same values as
  *   sorf_backward with dE = NULL.
  *   workspace: device memory of at least sorf_energy_grad_workspace_bytes(n_atoms),
  *   256-byte aligned (the atoms' energy shares). */
@@ -457,8 +457,8 @@ sorf_status sorf_forces(int32_t d, int64_t n_atoms, int64_t n_mols, const int64_
  * whatever batch it is served in.
  * Exceptions to the conventions above: sorf_server_start allocates the ring,
  * control word and result slots in pinned host memory (hipHostMalloc) and
- * sorf_server_stop frees them; while the kernel runs it holds nearly all the
- * vector registers of every compute unit, so other kernels on the device wait
+ * sorf_server_stop frees them; while the kernel runs it holds most of the
+ * vector registers of every compute unit, so other kernels on the device may wait
  * until it exits (sorf_server_stop, or the idle timeout): a served device serves
  * only; sorf_server_stop blocks until the kernel has exited. A server is used
  * from one host thread at a time.

@@ -17,6 +17,7 @@
 // Adjoint: one wave per atom; its lane groups cover the stacks in passes and
 // the stack sum is a wave reduction at the end.
 #include <cmath>
+#include <type_traits>
 
 #include "sorf_internal.h"
 
@@ -210,6 +211,10 @@ __device__ __forceinline__ void dma4(const void* g, void* lds) {
 __device__ __forceinline__ void dma16(const void* g, void* lds) {
   __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
 }
+template <int N>
+__device__ __forceinline__ void wait_loads() {   // at most N loads or copies still in flight
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
 __device__ __forceinline__ void lock_step() {
   __builtin_amdgcn_sched_barrier(0);
   __builtin_amdgcn_s_barrier();
@@ -233,7 +238,7 @@ struct LockLayout {
   static constexpr int DV = 1 << LOG_D, EPL = 32, LOGK = LOG_D - 5, K = 1 << LOGK, VPW = 64 >> LOGK;
   static constexpr int W = DV / 32;                 // sign words per vector
   static constexpr int RAW = W < 4 ? W : 4;         // words that hold a lane's four sign bytes
-  static_assert(LOG_D >= 6 && LOG_D <= 8, "layout");
+  static_assert(LOG_D >= 6 && LOG_D <= 10, "layout");
   static __device__ __forceinline__ int entry(int r, uint32_t q) {
     return 8 * K * (r >> 3) + 8 * int(q) + (r & 7);
   }
@@ -241,7 +246,7 @@ struct LockLayout {
   static __device__ __forceinline__ void load_raw(uint32_t (&raw)[RAW], const uint32_t* vec,
                                                   uint32_t q) {
 #pragma unroll
-    for (int i = 0; i < RAW; ++i) raw[i] = vec[K == 8 ? 2 * i + int(q >> 2) : i];
+    for (int i = 0; i < RAW; ++i) raw[i] = vec[K >= 8 ? i * (K / 4) + int(q >> 2) : i];
   }
   // Sign bit of entry r at bit r.
   static __device__ __forceinline__ uint32_t sign_word(const uint32_t (&raw)[RAW], uint32_t q) {
@@ -345,7 +350,7 @@ void forward_lock_kernel(const float* __restrict__ x, const int32_t* __restrict_
     const bool more = i + 1 < trips;
     const int buf = int(i) & 1;
     float v[EPL];
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // row and sign words have landed
+    wait_loads<0>();   // row and sign words have landed
 #pragma unroll
     for (int r = 0; r < EPL; r += 4) {
       const float4 t = *reinterpret_cast<const float4*>(&xrow[wv][buf][L::entry(r, q)]);
@@ -368,7 +373,7 @@ void forward_lock_kernel(const float* __restrict__ x, const int32_t* __restrict_
         if (t < T - 1) lock_step();
       }
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the phases have landed
+    wait_loads<0>();   // the phases have landed
     if (more) {
       e = e_next;
       request(atom(i + 1), e, buf ^ 1);
@@ -481,12 +486,274 @@ __global__ __launch_bounds__(1024) void energy_chunks_kernel(const int64_t* __re
 // ---------------------------------------------------------------------------
 // Per-atom adjoint: dE/dx_i (and the atom's energy share)
 // ---------------------------------------------------------------------------
+// From d = 64 on in lockstep (see forward_lock_kernel): eight waves per
+// workgroup, a barrier after every transform of both chains and after the sines.
+// The passes of an atom (VPW stacks each) go to nw waves, wave w taking the
+// passes w, w + nw, ...: one wave per atom when the atoms fill the chip, one
+// pass per wave (up to eight waves) when there are few, so that a served
+// request or a single molecule spreads over the SIMDs. Either way the sums are
+// the same, bit for bit: chunk c of a lane group adds its passes p = c mod 8 in
+// order, the chunks are added in order (in registers by one wave, through LDS by
+// several), then the lane groups, first and second half, each in order. An
+// atom's result therefore depends on the atom and the model alone.
+// 360,149 atoms, D = 8192, energies and gradients: 3.9 ms against 5.06 with one
+// wave per atom, no barriers and a butterfly over the lane groups; 8400 atoms
+// with 128 stacks 0.26 ms against 0.76; a 21-atom molecule with 256 stacks
+// 17 us against 97.
+constexpr int kAdjMaxWaves = 8;
+template <int LOG_D>
+struct AdjointShared {
+  // a wave's phases, and at the end its lane sums: eight blocks of 64 float4, 1088 bytes apart
+  static constexpr int BLOCK = 272, FLOATS = 8 * BLOCK;
+  static_assert(FLOATS >= 8 * 256 + 100, "phases fit");
+  __attribute__((aligned(16))) float xrow[kLockWaves][1 << LOG_D];
+  __attribute__((aligned(16))) float part[kLockWaves][FLOATS];
+  float energy[kLockWaves][64];
+};
+
+struct AdjointArgs {
+  const float* x;
+  const int32_t* element;
+  const uint32_t* signs;
+  const float* bias;
+  const float* alpha;
+  float* grad_x;
+  float* e_atom;
+  int32_t S, T;
+  float c_rev, g_scale, e_scale;
+};
+
+// Largest m with ptr[m] <= v (ptr[0] <= v < ptr[n]) by the 64 lanes of a wave.
+__device__ __forceinline__ int64_t wave_segment(const int64_t* __restrict__ ptr, int64_t n,
+                                                int64_t v) {
+  int64_t lo = 0, hi = n;
+  while (hi - lo > 1) {
+    const int64_t step = (hi - lo + 63) / 64;
+    const int64_t i = lo + (int64_t(lane_id()) + 1) * step;
+    const int64_t at = ptr[i < hi ? i : hi - 1];
+    const int64_t under = __popcll(__ballot(i < hi && at <= v));
+    lo += under * step;
+    hi = lo + step < hi ? lo + step : hi;
+  }
+  return lo;
+}
+
+// Atom `a` (< 0: none) by waves wv - part .. wv - part + nw - 1 of the workgroup;
+// every wave of the workgroup calls it, with the same nw. scale multiplies the
+// gradient.
+template <int LOG_D, bool WANT_E>
+__device__ __forceinline__ void adjoint_atom(const AdjointArgs& g, int64_t a, int part, int nw,
+                                             float scale, AdjointShared<LOG_D>& sh) {
+  using L = LockLayout<LOG_D>;
+  constexpr int DV = L::DV, EPL = L::EPL, LOGK = L::LOGK, VPW = L::VPW, W = L::W;
+  constexpr int CH = 8;                      // weights live at once
+  const uint32_t lane = lane_id();
+  const uint32_t q = lane & (L::K - 1u);
+  const uint32_t grp = lane >> LOGK;
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const bool live = a >= 0;
+  const int32_t S = g.S, T = g.T;
+  const int passes = (S + VPW - 1) / VPW;
+  const int64_t Dtot = int64_t(S) * DV;
+  const bool oddq = (__builtin_popcount(q) & 1) != 0;
+  const uint32_t flip = oddq ? 0xFFFFFFFFu : 0u;
+  const float c_lane = oddq ? -g.c_rev : g.c_rev;
+  const int64_t tstride = int64_t(S) * W;
+  const int vec0 = int(grp) * DV + 8 * int(q);
+  const float* ph = &sh.part[wv][phase_piece<LOG_D>(vec0 >> 8) + (vec0 & 255)];
+
+  float acc[EPL];
+#pragma unroll
+  for (int r = 0; r < EPL; ++r) acc[r] = 0.0f;
+  float eacc = 0.0f;
+  int32_t e = 0;
+  if (live) {
+    e = __builtin_amdgcn_readfirstlane(g.element[a]);
+#pragma unroll
+    for (int i = 0; i < DV / 64; ++i) dma4(g.x + a * DV + 64 * i + lane, &sh.xrow[wv][64 * i]);
+  }
+  const uint32_t* signs_e = g.signs + int64_t(e) * T * S * W;
+  const float* bias_e = g.bias + int64_t(e) * Dtot;
+  for (int p0 = 0; p0 < passes; p0 += nw) {
+    const int p = p0 + part;
+    const bool act = live && p < passes;
+    const bool inside = p * VPW + int(grp) < S;          // the last pass may be partial
+    const int32_t s = inside ? p * VPW + int(grp) : S - 1;
+    uint32_t raw[3][L::RAW];
+    float v[EPL], al[2][CH];
+    float ep = 0.0f;
+    if (act) {
+      const uint32_t* sv = signs_e + int64_t(s) * W;
+#pragma unroll
+      for (int t = 0; t < 3; ++t)
+        if (t < T) L::load_raw(raw[t], sv + t * tstride, q);
+      // (Requesting a pass's phases or sign words during the pass before costs
+      // more registers than there are: 40 to 128 of them spilled.)
+      const int64_t b0 = int64_t(p) * VPW * DV + 4 * lane;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const int64_t b = b0 + 256 * j;
+        dma16(bias_e + (b < Dtot ? b : Dtot - 4), &sh.part[wv][phase_piece<LOG_D>(j)]);
+      }
+      wait_loads<8>();                                   // row and sign words
+#pragma unroll
+      for (int r = 0; r < EPL; r += 4) {
+        const float4 t = *reinterpret_cast<const float4*>(&sh.xrow[wv][L::entry(r, q)]);
+        v[r] = t.x;
+        v[r + 1] = t.y;
+        v[r + 2] = t.z;
+        v[r + 3] = t.w;
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    lock_step();
+    const float* ap = g.alpha + int64_t(s) * DV + 8 * q;
+    auto weights = [&](int i) {                          // entries 8 i .. 8 i + 7 of the lane
+      load_vec<CH>(al[i & 1], ap + 8 * L::K * i);
+    };
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      if (t < T) {
+        if (act) {
+          if (t == T - 1) weights(0);
+          const uint32_t w[1] = {L::sign_word(raw[t], q) ^ (t > 0 ? flip : 0u)};
+          apply_signs<EPL>(v, w);
+          fwht<LOGK, EPL>(v, q);
+        }
+        if (t < T - 1) lock_step();
+      }
+    }
+    if (act) {
+      wait_loads<0>();                                   // phases
+#pragma unroll
+      for (int i = 0; i < EPL / CH; ++i) {
+        if (i + 1 < EPL / CH) weights(i + 1);
+#pragma unroll
+        for (int r = 0; r < CH; r += 4) {
+          const float4 b = *reinterpret_cast<const float4*>(ph + L::entry(CH * i + r, 0));
+          const float bb[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float wt = inside ? al[i & 1][r + k] : 0.0f;
+            const float u = __builtin_fmaf(v[CH * i + r + k], c_lane, bb[k] * kInv2Pi);
+            if constexpr (WANT_E) ep = __builtin_fmaf(wt, __builtin_amdgcn_cosf(u), ep);
+            v[CH * i + r + k] = wt * __builtin_amdgcn_sinf(u);
+          }
+        }
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
+    lock_step();
+    // transposed chain: H first, then D_{T-1}, ..., H, then D_0
+#pragma unroll
+    for (int t = 2; t >= 0; --t) {
+      if (t < T) {
+        if (act) {
+          fwht<LOGK, EPL>(v, q);
+          const uint32_t w[1] = {L::sign_word(raw[t], q) ^ flip};
+          apply_signs<EPL>(v, w);
+        }
+        if (t > 0) lock_step();
+      }
+    }
+    if (act) {
+#pragma unroll
+      for (int r = 0; r < EPL; ++r) acc[r] += v[r];
+      eacc += ep;
+    }
+  }
+
+  // lane sums into LDS (the phases are done with), then the sums over chunks and groups
+  constexpr int BLOCK = AdjointShared<LOG_D>::BLOCK;
+#pragma unroll
+  for (int r = 0; r < EPL; r += 4)
+    *reinterpret_cast<float4*>(&sh.part[wv][(r / 4) * BLOCK + 4 * lane]) =
+        make_float4(acc[r], acc[r + 1], acc[r + 2], acc[r + 3]);
+  if constexpr (WANT_E) sh.energy[wv][lane] = eacc;
+  const int base = wv - part;
+  if (nw > 1) {
+    __syncthreads();
+    for (int r4 = part; r4 < 8 && live; r4 += nw) {
+      float* mine = &sh.part[base][r4 * BLOCK + 4 * lane];
+      float4 t = *reinterpret_cast<const float4*>(mine);
+      for (int c = 1; c < nw; ++c) {
+        const float4 o = *reinterpret_cast<const float4*>(&sh.part[base + c][r4 * BLOCK + 4 * lane]);
+        t.x += o.x;
+        t.y += o.y;
+        t.z += o.z;
+        t.w += o.w;
+      }
+      *reinterpret_cast<float4*>(mine) = t;
+    }
+    if constexpr (WANT_E) {
+      if (part == 0 && live) {
+        float t = eacc;
+        for (int c = 1; c < nw; ++c) t += sh.energy[base + c][lane];
+        eacc = t;
+      }
+    }
+    __syncthreads();
+  } else {
+    lds_wave_sync();
+  }
+  if (part == 0 && live) {
+    for (int u = int(lane); u < DV / 4; u += 64) {       // entries 4 u .. 4 u + 3
+      const int i = (4 * u) / (8 * L::K), rem = (4 * u) % (8 * L::K);
+      const float* src = &sh.part[wv][(2 * i + (rem >> 2 & 1)) * BLOCK + 4 * (rem >> 3)];
+      float4 h[2];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        float4 t = *reinterpret_cast<const float4*>(src + 4 * L::K * (k * (VPW / 2)));
+#pragma unroll
+        for (int j = 1; j < VPW / 2; ++j) {
+          const float4 o = *reinterpret_cast<const float4*>(src + 4 * L::K * (k * (VPW / 2) + j));
+          t.x += o.x;
+          t.y += o.y;
+          t.z += o.z;
+          t.w += o.w;
+        }
+        h[k] = t;
+      }
+      *reinterpret_cast<float4*>(g.grad_x + a * DV + 4 * u) =
+          make_float4((h[0].x + h[1].x) * scale, (h[0].y + h[1].y) * scale,
+                      (h[0].z + h[1].z) * scale, (h[0].w + h[1].w) * scale);
+    }
+    if constexpr (WANT_E) {
+      eacc += lane_xor<0>(eacc);
+      eacc += lane_xor<1>(eacc);
+      eacc += lane_xor<2>(eacc);
+      eacc += lane_xor<3>(eacc);
+      eacc += lane_xor<4>(eacc);
+      eacc += lane_xor<5>(eacc);
+      if (lane == 0) g.e_atom[a] = eacc * g.e_scale;
+    }
+  }
+  __syncthreads();   // the shared sums are rewritten for the next atom
+}
+
+// 8 / nw atoms per workgroup. dE: upstream weights of the molecules, or null.
+template <int LOG_D, bool WANT_E>
+__global__ __launch_bounds__(64 * kLockWaves) __attribute__((amdgpu_waves_per_eu(LOG_D < 9 ? 4 : 2)))
+void adjoint_lock_kernel(AdjointArgs g, const int64_t* __restrict__ mol_ptr,
+                         const float* __restrict__ dE, int64_t n_atoms, int64_t n_mols, int nw) {
+  __shared__ AdjointShared<LOG_D> sh;
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int per = kLockWaves / nw;
+  int64_t a = wv < per * nw ? int64_t(blockIdx.x) * per + wv / nw : -1;
+  if (a >= n_atoms) a = -1;
+  float scale = g.g_scale;
+  if (!WANT_E && dE != nullptr && a >= 0) scale *= dE[wave_segment(mol_ptr, n_mols, a)];
+  adjoint_atom<LOG_D, WANT_E>(g, a, wv % nw, nw, scale, sh);
+}
+
+// Below d = 64 a vector lies in one lane, there is no exchange, and the transforms are short:
+// one wave per atom, its lanes covering the stacks in passes of 64.
 // The stacks s = s_begin, s_begin + s_step, ... of atom a (element e) for the
 // lane group grp of a wave (lane q inside the group): the forward chain, the
 // phase, the energy share sum_f alpha_f cos(u_f) into eacc and, for the
 // gradient, alpha_f sin(u_f) taken back through the transposed chain and
 // added into gacc (per lane, before any sum over the groups).
-template <int LOG_D, int LOG_EPL, bool WANT_E, bool WANT_G>
+template <int LOG_D, int LOG_EPL, bool WANT_E>
 __device__ __forceinline__ void adjoint_stacks(const float* __restrict__ xrow,
                                                const uint32_t* __restrict__ signs_e,
                                                const float* __restrict__ bias_e,
@@ -529,36 +796,32 @@ __device__ __forceinline__ void adjoint_stacks(const float* __restrict__ xrow,
         for (int r = 0; r < CH; ++r) {
           const float u = __builtin_fmaf(v[r0 + r], c_lane, b[r] * kInv2Pi);
           if constexpr (WANT_E) eacc = __builtin_fmaf(al[r], __builtin_amdgcn_cosf(u), eacc);
-          if constexpr (WANT_G) v[r0 + r] = al[r] * __builtin_amdgcn_sinf(u);
+          v[r0 + r] = al[r] * __builtin_amdgcn_sinf(u);
         }
       }
-      if constexpr (WANT_G) {
-        // transposed chain: H first, then D_{T-1}, ..., H, then D_0
-        for (int t = T - 1; t >= 0; --t) {
-          fwht<LOGK, EPL>(v, q);
-          uint32_t w[LW];
-          load_sign_words<EPL>(w, sv + t * tstride, q, flip);
-          apply_signs<EPL>(v, w);
-        }
+      // transposed chain: H first, then D_{T-1}, ..., H, then D_0
+      for (int t = T - 1; t >= 0; --t) {
+        fwht<LOGK, EPL>(v, q);
+        uint32_t w[LW];
+        load_sign_words<EPL>(w, sv + t * tstride, q, flip);
+        apply_signs<EPL>(v, w);
+      }
 #pragma unroll
-        for (int r = 0; r < EPL; ++r) gacc[r] += v[r];
-      }
+      for (int r = 0; r < EPL; ++r) gacc[r] += v[r];
     }
   }
 }
 
 // Sum of gacc over the lane groups of a wave (lane bits LOGK .. 5) and of
 // eacc over all its lanes, in a fixed order.
-template <int LOGK, int EPL, bool WANT_E, bool WANT_G>
+template <int LOGK, int EPL, bool WANT_E>
 __device__ __forceinline__ void adjoint_wave_sums(float (&gacc)[EPL], float& eacc) {
-  if constexpr (WANT_G) {
-    if constexpr (LOGK <= 0) { for (int r = 0; r < EPL; ++r) gacc[r] += lane_xor<0>(gacc[r]); }
-    if constexpr (LOGK <= 1) { for (int r = 0; r < EPL; ++r) gacc[r] += lane_xor<1>(gacc[r]); }
-    if constexpr (LOGK <= 2) { for (int r = 0; r < EPL; ++r) gacc[r] += lane_xor<2>(gacc[r]); }
-    if constexpr (LOGK <= 3) { for (int r = 0; r < EPL; ++r) gacc[r] += lane_xor<3>(gacc[r]); }
-    if constexpr (LOGK <= 4) { for (int r = 0; r < EPL; ++r) gacc[r] += lane_xor<4>(gacc[r]); }
-    if constexpr (LOGK <= 5) { for (int r = 0; r < EPL; ++r) gacc[r] += lane_xor<5>(gacc[r]); }
-  }
+  if constexpr (LOGK <= 0) { for (int r = 0; r < EPL; ++r) gacc[r] += lane_xor<0>(gacc[r]); }
+  if constexpr (LOGK <= 1) { for (int r = 0; r < EPL; ++r) gacc[r] += lane_xor<1>(gacc[r]); }
+  if constexpr (LOGK <= 2) { for (int r = 0; r < EPL; ++r) gacc[r] += lane_xor<2>(gacc[r]); }
+  if constexpr (LOGK <= 3) { for (int r = 0; r < EPL; ++r) gacc[r] += lane_xor<3>(gacc[r]); }
+  if constexpr (LOGK <= 4) { for (int r = 0; r < EPL; ++r) gacc[r] += lane_xor<4>(gacc[r]); }
+  if constexpr (LOGK <= 5) { for (int r = 0; r < EPL; ++r) gacc[r] += lane_xor<5>(gacc[r]); }
   if constexpr (WANT_E) {
     eacc += lane_xor<0>(eacc);
     eacc += lane_xor<1>(eacc);
@@ -569,8 +832,9 @@ __device__ __forceinline__ void adjoint_wave_sums(float (&gacc)[EPL], float& eac
   }
 }
 
+
 // One wave per atom: its lane groups cover the stacks in passes of VPW.
-template <int LOG_D, int LOG_EPL, bool WANT_E, bool WANT_G>
+template <int LOG_D, int LOG_EPL, bool WANT_E>
 __global__ __launch_bounds__(256) void atom_adjoint_kernel(
     const float* __restrict__ x, const int32_t* __restrict__ element,
     const int64_t* __restrict__ mol_ptr, const uint32_t* __restrict__ signs,
@@ -601,30 +865,20 @@ __global__ __launch_bounds__(256) void atom_adjoint_kernel(
 #pragma unroll
   for (int r = 0; r < EPL; ++r) gacc[r] = 0.0f;
   float eacc = 0.0f;
-  adjoint_stacks<LOG_D, LOG_EPL, WANT_E, WANT_G>(xrow, signs + int64_t(e) * T * S * W,
+  adjoint_stacks<LOG_D, LOG_EPL, WANT_E>(xrow, signs + int64_t(e) * T * S * W,
                                                  bias + int64_t(e) * Dtot, alpha, S, T, 0, VPW,
                                                  q, grp, c_rev, gacc, eacc);
-  adjoint_wave_sums<LOGK, EPL, WANT_E, WANT_G>(gacc, eacc);
-  if constexpr (WANT_G) {
-    if (grp == 0) {
-      float w_m = 1.0f;
-      if (dE != nullptr) w_m = dE[molecule_of(mol_ptr, n_mols, a)];
-      store_vec<EPL>(grad_x + a * DV + q * EPL, gacc, g_scale * w_m);
-    }
+  adjoint_wave_sums<LOGK, EPL, WANT_E>(gacc, eacc);
+  if (grp == 0) {
+    float w_m = 1.0f;
+    if (dE != nullptr) w_m = dE[molecule_of(mol_ptr, n_mols, a)];
+    store_vec<EPL>(grad_x + a * DV + q * EPL, gacc, g_scale * w_m);
   }
   if constexpr (WANT_E) {
     if (lane == 0) e_atom[a] = eacc * e_scale;
   }
 }
 
-// Latency form of the energy + gradient adjoint (sorf_predict with forces):
-// one workgroup of NWAVE waves per atom, wave w taking the stack passes
-// w, w + NWAVE, ...; the waves' sums are added in wave order through LDS.
-// A small batch (a served request) then spreads over NWAVE times as many
-// SIMDs and finishes in about 1 / NWAVE of the one-wave time. NWAVE depends
-// only on the model (the pass count, at most 8), so a molecule's results do
-// not depend on the batch it is in.
-constexpr int kAdjMaxWaves = 8;
 // Atom a with waves 0 .. nw - 1 of the workgroup (waves at or above nw only
 // take part in the barriers); red/ered are the workgroup's LDS scratch.
 template <int LOG_D, int LOG_EPL>
@@ -650,10 +904,10 @@ __device__ __forceinline__ void adjoint_split_atom(
 #pragma unroll
     for (int r = 0; r < EPL; ++r) gacc[r] = 0.0f;
     float eacc = 0.0f;
-    adjoint_stacks<LOG_D, LOG_EPL, true, true>(xrow, signs + int64_t(e) * T * S * W,
+    adjoint_stacks<LOG_D, LOG_EPL, true>(xrow, signs + int64_t(e) * T * S * W,
                                                bias + int64_t(e) * int64_t(S) * DV, alpha, S, T,
                                                wv * VPW, nw * VPW, q, grp, c_rev, gacc, eacc);
-    adjoint_wave_sums<LOGK, EPL, true, true>(gacc, eacc);
+    adjoint_wave_sums<LOGK, EPL, true>(gacc, eacc);
     if (grp == 0) {
 #pragma unroll
       for (int r = 0; r < EPL; ++r) red[wv][q * EPL + r] = gacc[r];
@@ -681,8 +935,7 @@ __device__ __forceinline__ void adjoint_split_atom(
   __syncthreads();   // red[] and ered[] are rewritten for the next atom
 }
 
-// Latency form of the energy + gradient adjoint (sorf_predict with forces):
-// one workgroup of nw waves per atom, wave w taking the stack passes
+// Energies with forces below d = 64: one workgroup of nw waves per atom, wave w taking the stack passes
 // w, w + nw, ...; the waves' sums are added in wave order through LDS.
 // A small batch (a served request) then spreads over nw times as many SIMDs
 // and finishes in about 1 / nw of the one-wave time. nw depends only on the
@@ -997,31 +1250,53 @@ static hipError_t forward_dispatch(const SorfFeatureArgs& a, float* Z, const flo
   return hipGetLastError();
 }
 
-// latency: energies with gradients in the latency form (several waves per
-// atom); otherwise one wave per atom.
+// Gradients (and the atoms' energy shares when e_atom is given; then dE is
+// null). latency: below d = 64, several waves per atom.
+// From d = 64 on both work splits of adjoint_lock_kernel give the same bits.
+// One wave per atom saves the sums over waves, several fill the chip evenly:
+// 21,000 atoms with 64 stacks take 383 us with one and 390 with four (the whole
+// prediction), 360,149 atoms 8.87 and 9.29 ms (energies and forces from
+// coordinates), but 8400 atoms 181 and 172, and with 128 stacks 287 and 263.
+constexpr int64_t kAdjBulkAtoms = 16384;
 template <int LOG_D>
 static hipError_t adjoint_dispatch(const SorfFeatureArgs& a, const float* alpha, const float* dE,
                                    float* grad_x, float* e_atom, bool latency, hipStream_t st) {
-  constexpr int LOG_EPL = default_log_epl<LOG_D>();
-  const int64_t blocks = (a.n_atoms + 3) / 4;
   float c_rev, g_scale, e_scale;
   sorf_adjoint_scales(a, &c_rev, &g_scale, &e_scale);
-  const dim3 grid{unsigned(blocks)}, block{256};
-#define SORF_ADJ(WE, WG)                                                                        \
-  hipLaunchKernelGGL((atom_adjoint_kernel<LOG_D, LOG_EPL, WE, WG>), grid, block, 0, st, a.x,   \
-                     a.element, a.mol_ptr, a.signs, a.bias, alpha, dE, grad_x, e_atom,        \
-                     a.n_atoms, a.n_mols, a.n_stacks, a.n_transforms, c_rev, g_scale, e_scale)
-  if (e_atom && grad_x && dE == nullptr && latency) {
-    // energies with forces: the latency form, one pass of stacks per wave
-    const int nw = sorf_adjoint_waves(a.d, a.n_stacks);
-    const int64_t grid = a.n_atoms < (int64_t(1) << 20) ? a.n_atoms : (int64_t(1) << 20);
-    hipLaunchKernelGGL((atom_adjoint_split_kernel<LOG_D, LOG_EPL>), dim3(unsigned(grid)),
-                       dim3(64 * nw), 0, st, a.x, a.element, a.signs, a.bias, alpha, grad_x,
-                       e_atom, a.n_atoms, a.n_stacks, a.n_transforms, c_rev, g_scale, e_scale);
-  } else if (e_atom && grad_x) SORF_ADJ(true, true);
-  else if (e_atom) SORF_ADJ(true, false);
-  else SORF_ADJ(false, true);
-#undef SORF_ADJ
+  const int waves = sorf_adjoint_waves(a.d, a.n_stacks);
+  if constexpr (LOG_D >= 6) {
+    (void)latency;
+    constexpr int VPW = LockLayout<LOG_D>::VPW;
+    const int64_t passes = (int64_t(a.n_stacks) + VPW - 1) / VPW;
+    const int nw = passes <= kAdjMaxWaves && a.n_atoms >= kAdjBulkAtoms ? 1 : waves;
+    const int64_t per = kLockWaves / nw;
+    const dim3 grid{unsigned((a.n_atoms + per - 1) / per)}, block{64 * kLockWaves};
+    const AdjointArgs g{a.x, a.element, a.signs, a.bias, alpha, grad_x, e_atom, a.n_stacks,
+                        a.n_transforms, c_rev, g_scale, e_scale};
+    if (e_atom != nullptr)
+      hipLaunchKernelGGL((adjoint_lock_kernel<LOG_D, true>), grid, block, 0, st, g, a.mol_ptr, dE,
+                         a.n_atoms, a.n_mols, nw);
+    else
+      hipLaunchKernelGGL((adjoint_lock_kernel<LOG_D, false>), grid, block, 0, st, g, a.mol_ptr, dE,
+                         a.n_atoms, a.n_mols, nw);
+  } else {
+    constexpr int LOG_EPL = default_log_epl<LOG_D>();
+    const dim3 grid{unsigned((a.n_atoms + 3) / 4)}, block{256};
+    if (e_atom != nullptr && latency) {
+      const int64_t most = a.n_atoms < (int64_t(1) << 20) ? a.n_atoms : (int64_t(1) << 20);
+      hipLaunchKernelGGL((atom_adjoint_split_kernel<LOG_D, LOG_EPL>), dim3(unsigned(most)),
+                         dim3(64 * waves), 0, st, a.x, a.element, a.signs, a.bias, alpha, grad_x,
+                         e_atom, a.n_atoms, a.n_stacks, a.n_transforms, c_rev, g_scale, e_scale);
+    } else if (e_atom != nullptr) {
+      hipLaunchKernelGGL((atom_adjoint_kernel<LOG_D, LOG_EPL, true>), grid, block, 0, st, a.x,
+                         a.element, a.mol_ptr, a.signs, a.bias, alpha, dE, grad_x, e_atom,
+                         a.n_atoms, a.n_mols, a.n_stacks, a.n_transforms, c_rev, g_scale, e_scale);
+    } else {
+      hipLaunchKernelGGL((atom_adjoint_kernel<LOG_D, LOG_EPL, false>), grid, block, 0, st, a.x,
+                         a.element, a.mol_ptr, a.signs, a.bias, alpha, dE, grad_x, e_atom,
+                         a.n_atoms, a.n_mols, a.n_stacks, a.n_transforms, c_rev, g_scale, e_scale);
+    }
+  }
   return hipGetLastError();
 }
 
@@ -1033,7 +1308,7 @@ static hipError_t adjoint_dispatch(const SorfFeatureArgs& a, const float* alpha,
 //   B0  workgroup 0 waits until every workgroup has finished the previous
 //       batch, publishes it as done, waits for the host to publish the next
 //       one and copies its descriptor into device memory;
-//   A   energy + gradient adjoint of the batch's atoms (adjoint_split_atom,
+//   A   energy + gradient adjoint of the batch's atoms (adjoint_atom,
 //       the sorf_predict kernel's per-atom work);
 //   B   force tiles (force_tile, two tiles per workgroup at a time);
 //   C   forces and energies (force_entry, molecule_energy) written straight
@@ -1077,12 +1352,19 @@ __device__ __forceinline__ bool serve_barrier(unsigned long long* bar, unsigned 
   return *lds_ok != 0;
 }
 
+template <int LOG_D>
+struct SplitShared {   // adjoint_split_atom's scratch
+  float red[kAdjMaxWaves][1 << LOG_D];
+  float ered[kAdjMaxWaves];
+};
+template <int LOG_D>
+using ServeShared = std::conditional_t<(LOG_D >= 6), AdjointShared<LOG_D < 6 ? 6 : LOG_D>, SplitShared<LOG_D>>;
+
 template <int LOG_D, int LOG_EPL>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void serve_kernel(
     ServeKernelArgs a) {
   constexpr int DV = 1 << LOG_D;
-  __shared__ float red[kAdjMaxWaves][DV];
-  __shared__ float ered[kAdjMaxWaves];
+  __shared__ ServeShared<LOG_D> adj;
   __shared__ float fred[2][4][64];
   __shared__ int s_ok;
   __shared__ int64_t s_flag;
@@ -1163,10 +1445,20 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void s
     const int64_t n_atoms = d->n_atoms, atom0 = d->atom0;
 
     // ---- A: adjoint of every atom, one atom per workgroup at a time
-    for (int64_t i = b; i < n_atoms; i += G)
-      adjoint_split_atom<LOG_D, LOG_EPL>(i, a.n_waves, a.x_pool + atom0 * DV, a.element_pool + atom0,
-                                         a.signs, a.bias, a.alpha, a.grad, a.e_atom, a.n_stacks,
-                                         a.n_transforms, a.c_rev, a.g_scale, a.e_scale, red, ered);
+    for (int64_t i = b; i < n_atoms; i += G) {
+      if constexpr (LOG_D >= 6) {
+        const AdjointArgs g{a.x_pool + atom0 * DV, a.element_pool + atom0, a.signs, a.bias, a.alpha,
+                            a.grad, a.e_atom, a.n_stacks, a.n_transforms, a.c_rev, a.g_scale,
+                            a.e_scale};
+        adjoint_atom<LOG_D, true>(g, wv < a.n_waves ? i : -1, wv % a.n_waves, a.n_waves, a.g_scale,
+                                  adj);
+      } else {
+        adjoint_split_atom<LOG_D, LOG_EPL>(i, a.n_waves, a.x_pool + atom0 * DV,
+                                           a.element_pool + atom0, a.signs, a.bias, a.alpha, a.grad,
+                                           a.e_atom, a.n_stacks, a.n_transforms, a.c_rev, a.g_scale,
+                                           a.e_scale, adj.red, adj.ered);
+      }
+    }
     if (!serve_barrier(a.bar, nbar++, a.wait_ticks, &s_ok)) return;
 
     // ---- B: force tiles, two per workgroup at a time (waves 0-3 and 4-7)
