@@ -1687,91 +1687,203 @@ __device__ __forceinline__ void tile_of_square(int64_t t, int64_t& I, int64_t& J
 }
 
 // ----------------------------------------------------------------- FP64 mode
-// The paper's double-precision training: Z (FP32) promoted to FP64 in LDS and
+// The paper's double-precision training: Z (FP32) promoted to FP64 and
 // multiplied on the FP64 matrix cores; G is FP64. 64 x 64 tiles, 4 waves of
-// 32 x 32 (2 x 2 blocks of v_mfma_f64_16x16x4f64).
+// 32 x 32 (2 x 2 blocks of v_mfma_f64_16x16x4f64), rows in order.
+// Bound: the FP64 matrix cores, 64 cycles per product, which need only four
+// 4-byte LDS reads and conversions per 256 cycles. The tiles stay small because
+// the call has no workspace for partial sums: at D = 4096 there are 2080 of them
+// (8.1 per compute unit), and four workgroups share a compute unit, so the last
+// round costs little. Z goes straight into LDS in FP32, four bytes a lane (any
+// D, any alignment), in a ring of two 32-row stages with one barrier each; LDS
+// rows are 80 floats apart, so that the four rows of a product are read from
+// different banks. 6001 x 4096: 2.02 ms (50 TF) against 3.36 with one buffer of
+// converted values and two barriers per 16 rows (2.07 with four 16-row stages);
+// 20,000 x 8192 23.4 ms (57 TF; a register-only loop reaches 67-69) against 42.4.
+// The register budget is fixed at four waves per SIMD: left open, the compiler
+// keeps the sums in accumulation registers and moves all 32 there and back every
+// stage (2.35 ms).
+// Tiles are dealt so that each XCD gets a contiguous run of them: its 128
+// workgroups then walk a few tile rows together and share their panels in L2.
 typedef double f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kF64Tile = 64, kF64Row = 80;
+constexpr int64_t kF64Few = 256;
 
-__global__ __launch_bounds__(256) void gram_fp64_kernel(const float* __restrict__ Z, int64_t M,
-                                                       int32_t D, double* __restrict__ G,
-                                                       const float* __restrict__ y,
-                                                       double* __restrict__ Zty) {
-  constexpr int T64 = 64;
-  __shared__ double sA[KB][T64 + 1];
-  __shared__ double sB[KB][T64 + 1];
-  __shared__ double zred[KB][T64];
-  int64_t I, J;
-  tile_of_square(blockIdx.x, I, J);
-  const bool diag = (I == J);
-  const int64_t I0 = I * T64, J0 = J * T64;
+__device__ __forceinline__ void dma4(const void* g, void* lds) {
+  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds, 4, 0, 0);
+}
+
+// Z^T y rides along in the first n_zty workgroups, 64 columns each.
+template <int GROUPS>
+__device__ __forceinline__ void zty_fp64(const float* __restrict__ Z, int64_t M, int32_t D,
+                                         int64_t c0, const float* __restrict__ y,
+                                         double* __restrict__ Zty, double (*red)[64]) {
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wv = tid >> 6;
-  const int wy = wv >> 1, wx = wv & 1;
-  f64x4 acc[2][2];
+  constexpr int LK = 16 * GROUPS;                 // rows lk, lk + LK, ...; four columns
+  const int lk = tid >> 4, li = (tid & 15) * 4;
+  int64_t col[4];
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int c = 0; c < 4; ++c) col[c] = c0 + li + c < D ? c0 + li + c : D - 1;
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t m0 = lk; m0 < M; m0 += 8 * LK) {   // eight rows in flight
+    float z[8][4], w[8];
 #pragma unroll
-    for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
-  const int lk = tid >> 4;        // slab row 0..15
-  const int li = (tid & 15) * 4;  // 4 consecutive columns
-  const bool want_zty = diag && y != nullptr;
-  double zacc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t m0 = 0; m0 < M; m0 += KB) {
-    const int64_t m = m0 + lk;
-    const double yl = want_zty ? double(y[m < M ? m : M - 1]) : 0.0;
-    const double ym = (m < M) ? yl : 0.0;
+    for (int u = 0; u < 8; ++u) {
+      const int64_t m = m0 + u * LK < M ? m0 + u * LK : M - 1;
+      w[u] = y[m];
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      const int64_t ci = I0 + li + c, cj = J0 + li + c;
-      const int64_t mc = m < M ? m : M - 1;
-      const float zil = Z[mc * D + (ci < D ? ci : D - 1)];
-      const float zjl = Z[mc * D + (cj < D ? cj : D - 1)];
-      const double zi = (m < M && ci < D) ? double(zil) : 0.0;
-      sA[lk][li + c] = zi;
-      zacc[c] += zi * ym;
-      if (!diag) sB[lk][li + c] = (m < M && cj < D) ? double(zjl) : 0.0;
+      for (int c = 0; c < 4; ++c) z[u][c] = Z[m * D + col[c]];
     }
-    __syncthreads();
-    const double (*sb)[T64 + 1] = diag ? sA : sB;
 #pragma unroll
-    for (int kk = 0; kk < KB; kk += 4) {
-      const int k = kk + (lane >> 4);
-      double av[2], bv[2];
+    for (int u = 0; u < 8; ++u)
+      if (m0 + u * LK < M)
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
-        av[b] = sA[k][wy * 32 + b * 16 + (lane & 15)];
-        bv[b] = sb[k][wx * 32 + b * 16 + (lane & 15)];
-      }
-#pragma unroll
-      for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[a], bv[b], acc[a][b], 0, 0, 0);
-    }
-    __syncthreads();
+        for (int c = 0; c < 4; ++c) acc[c] += double(z[u][c]) * double(w[u]);
   }
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+  for (int c = 0; c < 4; ++c) red[lk][li + c] = acc[c];
+  __syncthreads();
+  if (tid < 64 && c0 + tid < D) {
+    double sum = 0.0;
+    for (int r = 0; r < LK; ++r) sum += red[r][tid];
+    Zty[c0 + tid] += sum;
+  }
+}
+
+template <int GROUPS, int KS, int NS>
+__global__ __launch_bounds__(256 * GROUPS) __attribute__((amdgpu_waves_per_eu(4, 4)))
+void gram_fp64_kernel(const float* __restrict__ Z, int64_t M, int32_t D, int64_t n_tiles,
+                      double* __restrict__ G, int64_t n_zty, const float* __restrict__ y,
+                      double* __restrict__ Zty) {
+  constexpr int T64 = kF64Tile, CP = 2 * KS / 4;   // copies per wave and stage
+  __shared__ __attribute__((aligned(16))) float ring[2][GROUPS][NS][KS][kF64Row];
+  auto& ra = ring[0];
+  auto& rb = ring[1];
+  if (int64_t(blockIdx.x) < n_zty) {
+    if (int64_t(blockIdx.x) * 64 < D)
+      zty_fp64<GROUPS>(Z, M, D, int64_t(blockIdx.x) * 64, y, Zty,
+                       reinterpret_cast<double (*)[64]>(&ra[0][0][0][0]));
+    return;
+  }
+  // XCD b % 8 takes tiles [x run, (x + 1) run)
+  const int64_t b = int64_t(blockIdx.x) - n_zty, run = (n_tiles + 7) / 8;
+  const int64_t t = (b % 8) * run + b / 8;
+  if (t >= n_tiles) return;
+  int64_t I, J;
+  tile_of_square(t, I, J);
+  const int64_t I0 = I * T64, J0 = J * T64;
+  const int lane = int(threadIdx.x & 63);
+  const int gw = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int grp = gw / 4, wv = gw % 4;
+  const int wy = wv >> 1, wx = wv & 1;
+  const uint32_t colA = uint32_t(I0 + lane < D ? I0 + lane : D - 1);   // clamped columns are
+  const uint32_t colB = uint32_t(J0 + lane < D ? J0 + lane : D - 1);   // never stored
+  const int64_t n_st = (M + KS - 1) / KS;
+  const int rem = int(M % KS);                    // rows of a partial last stage
+  // rows wv, wv + 4, ... of a stage; rows past M are clamped and left out of the products
+  auto issue = [&](int64_t st, int slot) {
+    const float* base = Z + st * KS * D;
+    const int most = rem != 0 && st == n_st - 1 ? rem - 1 : KS - 1;
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+    for (int i = 0; i < KS / 4; ++i) {
+      const int k = wv + 4 * i;
+      const float* row = base + int64_t(k < most ? k : most) * D;
+      dma4(row + colA, &ra[grp][slot][k][0]);
+      dma4(row + colB, &rb[grp][slot][k][0]);
+    }
+  };
+  f64x4 acc[2][2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) acc[i][j] = f64x4{0.0, 0.0, 0.0, 0.0};
+  // products of rows [0, rows) of a slot, 16 rows read at a time
+  auto products = [&](int slot, int rows, bool partial) {
+#pragma unroll
+    for (int k0 = 0; k0 < KS; k0 += 16) {
+      float av[4][2], bv[4][2];
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        const int k = k0 + 4 * kk + (lane >> 4);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          av[kk][i] = ra[grp][slot][k][wy * 32 + i * 16 + (lane & 15)];
+          bv[kk][i] = rb[grp][slot][k][wx * 32 + i * 16 + (lane & 15)];
+          if (partial && k >= rows) av[kk][i] = bv[kk][i] = 0.0f;
+        }
+      }
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) {
+        double da[2], db[2];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          da[i] = double(av[kk][i]);
+          db[i] = double(bv[kk][i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(da[i], db[j], acc[i][j], 0, 0, 0);
+      }
+    }
+  };
+  // group g takes the stages g, g + GROUPS, ...
+  for (int j = 0; j < NS - 1; ++j)
+    if (grp + GROUPS * j < n_st) issue(grp + GROUPS * j, j);
+  int slot = 0;
+  const int64_t full = rem != 0 ? n_st - 1 : n_st;
+  const int64_t trips = (full + GROUPS - 1) / GROUPS;
+  for (int64_t i = 0; i < trips; ++i) {
+    const int64_t st = grp + GROUPS * i;
+    const int64_t later = st < n_st ? (n_st - 1 - st) / GROUPS : 0;
+    wait_stage<CP>(later < NS - 2 ? later : NS - 2);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");   // this wave's reads of the slot refilled next
+    stage_barrier();
+    if (st + GROUPS * (NS - 1) < n_st) issue(st + GROUPS * (NS - 1), slot == 0 ? NS - 1 : slot - 1);
+    if (GROUPS == 1 || st < full) {
+      products(slot, KS, false);
+      slot = slot + 1 == NS ? 0 : slot + 1;
+    }
+  }
+  if (rem != 0) {
+    wait_stage<CP>(0);
+    stage_barrier();
+    if ((n_st - 1) % GROUPS == grp) products(slot, rem, true);
+  }
+  if constexpr (GROUPS > 1) {
+    // the groups' sums, halving their number each time: ((0 + 2) + (1 + 3))
+    static_assert(sizeof(ring) >= size_t(GROUPS / 2) * 4 * 16 * 64 * sizeof(double),
+                  "half the groups' sums fit the ring");
+    double* sums = reinterpret_cast<double*>(&ra[0][0][0][0]);   // [group][4 waves][16][64]
+#pragma unroll
+    for (int n = GROUPS / 2; n > 0; n /= 2) {
+      __syncthreads();
+      if (grp >= n && grp < 2 * n) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          sums[(((grp - n) * 4 + wv) * 16 + r) * 64 + lane] = acc[r >> 3][(r >> 2) & 1][r & 3];
+      }
+      __syncthreads();
+      if (grp < n) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          acc[r >> 3][(r >> 2) & 1][r & 3] += sums[((grp * 4 + wv) * 16 + r) * 64 + lane];
+      }
+    }
+    if (grp > 0) return;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         // v_mfma_f64_16x16x4f64: lane l, register r holds row l/16 + 4 r, column l%16
-        const int64_t gi = I0 + wy * 32 + a * 16 + (lane >> 4) + 4 * r;
-        const int64_t gj = J0 + wx * 32 + b * 16 + (lane & 15);
-        if (gi < D && gj < D && gi >= gj) G[gi * D + gj] += acc[a][b][r];
+        const int64_t gi = I0 + wy * 32 + i * 16 + (lane >> 4) + 4 * r;
+        const int64_t gj = J0 + wx * 32 + j * 16 + (lane & 15);
+        if (gi < D && gj < D && gi >= gj) G[gi * D + gj] += acc[i][j][r];
       }
-  if (want_zty) {
-#pragma unroll
-    for (int c = 0; c < 4; ++c) zred[lk][li + c] = zacc[c];
-    __syncthreads();
-    if (tid < T64 && I0 + tid < D) {
-      double t = 0.0;
-      for (int r = 0; r < KB; ++r) t += zred[r][tid];
-      Zty[I0 + tid] += t;
-    }
-  }
 }
 
 }  // namespace sorf
@@ -2183,8 +2295,16 @@ hipError_t sorf_launch_gram_split(int64_t n_rows, int32_t D, const float* Z, con
 hipError_t sorf_launch_gram_f64(int64_t n_rows, int32_t D, const float* Z, const float* y,
                                 double* G, double* Zty, hipStream_t st) {
   if (n_rows == 0 || D == 0) return hipSuccess;
-  const int64_t nt = (D + 63) / 64;
-  hipLaunchKernelGGL(gram_fp64_kernel, dim3(unsigned(nt * (nt + 1) / 2)), dim3(256), 0, st, Z,
-                     n_rows, D, G, y, Zty);
+  const int64_t nt = (D + kF64Tile - 1) / kF64Tile, tiles = nt * (nt + 1) / 2;
+  const int64_t zty = y != nullptr ? (nt + 7) / 8 * 8 : 0;   // whole rounds over the XCDs
+  const dim3 grid{unsigned(zty + (tiles + 7) / 8 * 8)};
+  // at most one tile per compute unit: four groups of waves share its rows, 5000 x
+  // 1024 0.21 ms against 0.27 with one group; at D = 2048 (528 tiles) 0.60 against 0.57
+  if (tiles <= kF64Few)
+    hipLaunchKernelGGL((gram_fp64_kernel<4, 16, 2>), grid, dim3(1024), 0, st, Z, n_rows, D, tiles,
+                       G, zty, y, Zty);
+  else
+    hipLaunchKernelGGL((gram_fp64_kernel<1, 32, 2>), grid, dim3(256), 0, st, Z, n_rows, D, tiles,
+                       G, zty, y, Zty);
   return hipGetLastError();
 }

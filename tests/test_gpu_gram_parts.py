@@ -1,5 +1,5 @@
 """GPU: the FP32 Gram on three bf16 parts per entry (large systems) and its row
-slices.
+slices, and the FP64 Gram.
 
 Bound of an entry: the six products keep each z z' to 2^-22, and the sums round
 at most 2 (6 * 16 + 8) times per 256-row block, once per block and once per
@@ -85,3 +85,23 @@ def test_entries_that_have_no_parts(value):
         assert np.array_equal(row.numpy()[~fine], want[~fine])
     keep = torch.arange(D, device="cuda") != 5
     check(Z[:, keep].contiguous(), G[keep][:, keep].contiguous(), torch.zeros(D - 1, D - 1, device="cuda"))
+
+
+@pytest.mark.parametrize("M,D", [(1, 1), (15, 63), (16, 64), (17, 65), (63, 30), (64, 128), (65, 129),
+                                 (129, 257), (33, 1408), (32, 1409), (95, 1500), (1000, 1411)])
+def test_fp64_edges(M, D):
+    """The FP64 Gram with four groups of waves per tile (D <= 1408) and with one, at the
+    edges of stages and tiles. Entries and Z^T y within M 2^-53 of their terms' sum."""
+    from paper_2206_01580_amd import sorf
+    g = torch.Generator(device="cuda").manual_seed(M * 7 + D)
+    Z = torch.randn(M, D, device="cuda", generator=g)
+    y = torch.randn(M, device="cuda", generator=g)
+    G0 = torch.randn(D, D, device="cuda", dtype=torch.float64, generator=g)
+    G, Zty = G0.clone(), torch.zeros(D, device="cuda", dtype=torch.float64)
+    sorf.gram_accumulate(Z, G, y, Zty, "fp64")
+    Zd, yd = Z.double(), y.double()
+    bound = (M + 2) * 2.0 ** -53 * (Zd.abs().T @ Zd.abs() + G0.abs())
+    assert bool((torch.tril((G - G0 - Zd.T @ Zd).abs()) <= 2 * bound).all())
+    assert bool(((Zty - Zd.T @ yd).abs() <= 2 * (M + 2) * 2.0 ** -53 * (Zd.abs().T @ yd.abs())).all())
+    upper = torch.triu(torch.ones_like(G, dtype=torch.bool), 1)
+    assert torch.equal(G[upper], G0[upper])
