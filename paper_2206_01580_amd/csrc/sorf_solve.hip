@@ -9,7 +9,7 @@
 //
 // Blocked right-looking Cholesky with panel width NB = 128:
 //   1. factor the NB x NB diagonal block in LDS and invert it (one workgroup;
-//      the 64 x 64 halves are factored and inverted by one wave in registers),
+//      16 x 16 parts on FP64 MFMA, one wave on the pivots, the others beside it),
 //   2. panel below: L21 = A21 L11^{-T} = A21 (L11^{-1})^T as an FP64 MFMA GEMM,
 //      fused with the update of the next diagonal tile,
 //   3. trailing update A22 -= L21 L21^T on the rest of the lower triangle,
@@ -100,19 +100,30 @@ __global__ __launch_bounds__(256) void promote_kernel(const TG* __restrict__ G, 
 }
 
 // ---------------------------------------------------------------------------
-// Diagonal block: factor and invert a 128 x 128 block in LDS.
+// Diagonal block: factor a 128 x 128 block in LDS and form the inverse of its
+// factor.
 //
-// The block is split into 64 x 64 halves. A single wave factors (and later
-// inverts) a half with no workgroup barriers: the LDS operations of one wave
-// execute in order, so between steps it only waits for its own LDS traffic
-// (lgkmcnt(0)) and stops the compiler from moving memory operations across
-// the step (wave barrier). The couplings between the halves are 64 x 64 x 64
-// products spread over all four waves.
+// This kernel is the serial part of the factorisation: one workgroup, and the
+// rest of the solve's chain waits for it. What bounds it is the length of the
+// dependent chain of 128 pivots, so the block is cut into 16 x 16 parts whose
+// elimination is a rank-1 update by one FP64 MFMA a pivot, without LDS or
+// lane exchange: in the accumulator layout (row lane / 16 + 4 r, column
+// lane % 16) row J of the symmetric part is register J / 4 of the lanes with
+// lane / 16 == J % 4, which is also where the MFMA reads slot k = J % 4 of
+// either operand. Wave 0 does these steps, and between two parts only the
+// three products that the next part needs, all in registers; the other waves
+// are one part behind it with the rest (one barrier a part). Wave 4 stays
+// out of their work but for the stores, since it would take wave 0's matrix core.
+// 128 x 128: 55 us with one wave on 64 x 64 halves (a column published
+// through LDS a pivot, 256 steps for factor and inverse), now 26.5. A pivot
+// takes 250 cycles (two MFMAs of 67, which FP64 vector instructions of the
+// wave do not overlap), a part 6200 with the three products and the barrier.
+//
+// Row stride NB + 18 doubles: the 16 rows x 2 columns that half a wave reads
+// for an MFMA operand then fall on distinct LDS banks.
 // ---------------------------------------------------------------------------
-// Row stride NB + 8 doubles: the 8 x 8 lane grids of the one-wave steps
-// (rows ly + 8a, columns lx + 8b) then fall on distinct LDS banks.
-constexpr int LDL = NB + 8;
-typedef double LdsBlock[LDL];
+constexpr int LDL = NB + 18;
+constexpr int PB = 16;   // rows of a part
 
 // 1 / d to full double precision: hardware reciprocal plus one Newton step
 // (the exact IEEE division is a longer dependent chain on the critical path).
@@ -122,379 +133,247 @@ static __device__ __forceinline__ double recip(double d) {
   return __builtin_fma(r, e, r);
 }
 
-static __device__ __forceinline__ void wave_step_fence() {
-  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS reads/writes are done
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);  // no compiler motion of memory accesses across
-  __builtin_amdgcn_wave_barrier();
+// 1 / sqrt(d) for a positive finite d: hardware estimate plus one third-order step.
+static __device__ __forceinline__ double recip_sqrt(double d) {
+  const double r = __builtin_amdgcn_rsq(d);
+  const double e = __builtin_fma(-d * r, r, 1.0);
+  return __builtin_fma(r * e, __builtin_fma(0.375, e, 0.5), r);
 }
 
-// One wave factors (and later inverts) a 64 x 64 half with the matrix held in
-// registers: lane (ly, lx) of an 8 x 8 grid owns the entries
-// (ly + 8a, lx + 8b), a, b = 0..7, for the whole factorisation. A step only
-// publishes one column (and, for the inverse, one row) through a 64-entry
-// LDS buffer; since one wave issues its LDS operations in order, the reads
-// that follow see the published values. Step J = 8 JB + jr runs with JB
-// fixed at compile time, so every register index is static; the masks that
-// select the updated entries split into a factor per row block and a
-// factor per column block, so the update is one FMA per entry.
-
-// Cholesky, unscaled right-looking form: at step J every entry (i, l) with
-// i >= l > J loses A[i][J] A[l][J] / A[J][J]; the columns are scaled by
-// 1/sqrt(A[J][J]) after the last step (piv[] keeps the square roots).
-// Software-pipelined: a step first updates the block column that holds
-// column J + 1, publishes that column and issues the reads the next step
-// needs (fr, cr, dJ), and only then updates the remaining block columns, so
-// the LDS round trip overlaps the bulk of the FMAs.
-static __device__ __forceinline__ void order_fence() { __atomic_signal_fence(__ATOMIC_SEQ_CST); }
-
-template <int JB, int BC>
-static __device__ __forceinline__ void rpotrf_col(double (&R)[8][8], const double (&f)[8],
-                                                  const double (&c)[8], bool lower) {
-#pragma unroll
-  for (int a = BC; a < 8; ++a)
-    R[a][BC] = __builtin_fma(-f[a], a == BC ? (lower ? c[BC] : 0.0) : c[BC], R[a][BC]);
+static __device__ __forceinline__ double lane_value(double v, int lane) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), lane),
+                          __builtin_amdgcn_readlane(__double2loint(v), lane));
 }
 
-template <int JB>
-static __device__ __forceinline__ void rpotrf_block(double (&R)[8][8], double* col, double* piv,
-                                                    double* dummy, int ly, int lx, int lane,
-                                                    double (&fr)[8], double (&cr)[8],
-                                                    double& dJ) {
-  const bool lower = ly >= lx;
-  for (int jr = 0; jr < 8; ++jr) {
-    const int J = 8 * JB + jr;
-    const double d = dJ;
-    *(lane == 0 ? &piv[J] : &dummy[lane]) = d;   // checked and rooted after the last step
-    const double rd = recip(d);
-    double f[8], c[8];
+// acc += sum_p a[row][p] b[col][p] over 16 values of p: a and b point at the
+// first of 16 rows in LDS, lane (li, lt) supplies row li.
+static __device__ __forceinline__ f64x4 part_nt(const double* a, const double* b, int li, int lt,
+                                                f64x4 acc) {
+  double av[4], bv[4];
 #pragma unroll
-    for (int a = 0; a < 8; ++a) f[a] = a >= JB ? fr[a] * rd : 0.0;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) c[b] = (b >= JB && lx + 8 * b > J) ? cr[b] : 0.0;
-    // 1. the block column of column J + 1, then publish column J + 1
-    if (jr < 7) {
-      rpotrf_col<JB, JB>(R, f, c, lower);
-#pragma unroll
-      for (int a = JB; a < 8; ++a) *(lx == jr + 1 ? &col[ly + 8 * a] : &dummy[lane]) = R[a][JB];
-    } else if constexpr (JB < 7) {
-      rpotrf_col<JB, JB + 1>(R, f, c, lower);
-#pragma unroll
-      for (int a = JB + 1; a < 8; ++a) *(lx == 0 ? &col[ly + 8 * a] : &dummy[lane]) = R[a][JB + 1];
-    }
-    order_fence();
-    // 2. the next step's reads
-    if (J + 1 < 64) {
-#pragma unroll
-      for (int a = JB; a < 8; ++a) {
-        fr[a] = col[ly + 8 * a];
-        cr[a] = col[lx + 8 * a];
-      }
-      dJ = col[J + 1];
-    }
-    order_fence();
-    // 3. the remaining block columns
-#pragma unroll
-    for (int b = JB; b < 8; ++b) {
-      if (b == JB && jr < 7) continue;
-      if (b == JB + 1 && jr == 7) continue;
-#pragma unroll
-      for (int a = b; a < 8; ++a)
-        R[a][b] = __builtin_fma(-f[a], a == b ? (lower ? c[b] : 0.0) : c[b], R[a][b]);
-    }
+  for (int s = 0; s < 4; ++s) {
+    av[s] = a[li * LDL + 4 * s + lt];
+    bv[s] = b[li * LDL + 4 * s + lt];
   }
+#pragma unroll
+  for (int s = 0; s < 4; ++s) acc = mfma64(av[s], bv[s], acc);
+  return acc;
 }
 
-static __device__ __forceinline__ void wave_potrf64(LdsBlock* L, int o, int ly, int lx, int lane,
-                                                    double* piv, double* col, double* dummy,
-                                                    int32_t* info, int gbase, int nvalid) {
-  double R[8][8];
+// acc += sum_p a[row][p] b[p][col]: b is read along its rows.
+static __device__ __forceinline__ f64x4 part_nn(const double* a, const double* b, int li, int lt,
+                                                f64x4 acc) {
+  double av[4], bv[4];
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) R[a][b] = L[o + ly + 8 * a][o + lx + 8 * b];
-  // publish column 0 and read it for the first step
-#pragma unroll
-  for (int a = 0; a < 8; ++a) *(lx == 0 ? &col[ly + 8 * a] : &dummy[lane]) = R[a][0];
-  wave_step_fence();
-  double fr[8], cr[8], dJ;
-#pragma unroll
-  for (int a = 0; a < 8; ++a) {
-    fr[a] = col[ly + 8 * a];
-    cr[a] = col[lx + 8 * a];
+  for (int s = 0; s < 4; ++s) {
+    av[s] = a[li * LDL + 4 * s + lt];
+    bv[s] = b[(4 * s + lt) * LDL + li];
   }
-  dJ = col[0];
-  order_fence();
-  rpotrf_block<0>(R, col, piv, dummy, ly, lx, lane, fr, cr, dJ);
-  rpotrf_block<1>(R, col, piv, dummy, ly, lx, lane, fr, cr, dJ);
-  rpotrf_block<2>(R, col, piv, dummy, ly, lx, lane, fr, cr, dJ);
-  rpotrf_block<3>(R, col, piv, dummy, ly, lx, lane, fr, cr, dJ);
-  rpotrf_block<4>(R, col, piv, dummy, ly, lx, lane, fr, cr, dJ);
-  rpotrf_block<5>(R, col, piv, dummy, ly, lx, lane, fr, cr, dJ);
-  rpotrf_block<6>(R, col, piv, dummy, ly, lx, lane, fr, cr, dJ);
-  rpotrf_block<7>(R, col, piv, dummy, ly, lx, lane, fr, cr, dJ);
-  wave_step_fence();
-  // pivots: the first one that is not positive and finite sets info
-  {
-    const double d = piv[lane];
-    const bool bad = !(d > 0.0) || !std::isfinite(d);
-    const unsigned long long m = __ballot(bad && lane < nvalid);
-    if (m != 0ull && lane == 0 && *info == 0) *info = gbase + __ffsll((long long)m);
-    piv[lane] = bad ? __builtin_nan("") : std::sqrt(d);
+#pragma unroll
+  for (int s = 0; s < 4; ++s) acc = mfma64(av[s], bv[s], acc);
+  return acc;
+}
+
+// One wave: C is a symmetric 16 x 16 part in the accumulator layout; returns
+// the inverse of its Cholesky factor (zero above the diagonal). Elimination
+// of [C | I] without scaling: at pivot J, row i > J loses C[i][J] / d_J times
+// row J, d_J = C[J][J]; the rows of the second half are scaled by
+// 1 / sqrt(d_i) at the end. A pivot that is not positive and finite makes its
+// row NaN, and the first one (of the nvalid rows inside the matrix) sets info.
+static __device__ __forceinline__ f64x4 part_factor_inverse(f64x4 C, int li, int lt, int lane,
+                                                            int32_t* info, int gbase,
+                                                            int nvalid) {
+  f64x4 X, piv;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    X[r] = lt + 4 * r == li ? 1.0 : 0.0;
+    piv[r] = 1.0;
   }
-  wave_step_fence();
-  // L[i][l] = A[i][l] / piv[l] below the diagonal, piv[l] on it, 0 above
+  double d = lane_value(C[0], 0);
+  double rd = recip(d);
 #pragma unroll
-  for (int b = 0; b < 8; ++b) {
-    const int l = lx + 8 * b;
-    const double p = piv[l];
-    const double rp = recip(p);
-#pragma unroll
-    for (int a = 0; a < 8; ++a) {
-      const int i = ly + 8 * a;
-      L[o + i][o + l] = i > l ? R[a][b] * rp : (i == l ? p : 0.0);
+  for (int J = 0; J < PB; ++J) {
+    const int rr = J >> 2, rq = J & 3;
+    const bool own = lt == rq;
+    const double row = own && li > J ? C[rr] : 0.0;   // row J = column J right of the diagonal
+    const double f = -row * rd;
+    const double xrow = own ? X[rr] : 0.0;
+    // the next pivot, with the MFMA's own operations, beside the MFMA
+    double c10 = 0.0, c11 = 0.0;
+    if (J + 1 < PB) {
+      c10 = lane_value(C[rr], 16 * rq + J + 1);
+      c11 = lane_value(C[(J + 1) >> 2], 16 * ((J + 1) & 3) + J + 1);
     }
-  }
-  wave_step_fence();
-}
-
-// Inverse of the lower-triangular 64 x 64 half by forward elimination of
-// [L | I] in place: at step Q every row i > Q loses L[i][Q] / L[Q][Q] times
-// the (still unscaled) row Q of X on the columns c < Q, and X[i][Q] becomes
-// -L[i][Q] / L[Q][Q]. Row Q is final after step Q except for the scale
-// 1/L[Q][Q], applied at the end (rinv[] holds the reciprocal pivots). The
-// columns of L are read from the untouched LDS copy; a step first finishes
-// row Q + 1, publishes it and issues the next step's reads, then updates the
-// remaining block rows.
-template <int QB, int BR>
-static __device__ __forceinline__ void rtrtri_row(double (&R)[8][8], const double (&f)[8],
-                                                  const double (&r)[8], bool colq) {
-#pragma unroll
-  for (int b = 0; b <= QB; ++b) R[BR][b] = __builtin_fma(-f[BR], r[b], R[BR][b]);
-  R[BR][QB] = colq ? -f[BR] : R[BR][QB];
-}
-
-template <int QB>
-static __device__ __forceinline__ void rtrtri_block(double (&R)[8][8], const LdsBlock* L, int o,
-                                                    double* rowv, const double* rinv,
-                                                    double* dummy, int ly, int lx, int lane,
-                                                    double (&rowr)[8], double (&coll)[8],
-                                                    double& inv) {
-  for (int qr = 0; qr < 8; ++qr) {
-    const int Q = 8 * QB + qr;
-    double f[8], r[8];
-#pragma unroll
-    for (int a = 0; a < 8; ++a) f[a] = (a >= QB && ly + 8 * a > Q) ? coll[a] * inv : 0.0;
-#pragma unroll
-    for (int b = 0; b < 8; ++b) r[b] = (b <= QB && lx + 8 * b < Q) ? rowr[b] : 0.0;
-    const bool mine = lx == qr;   // this lane holds column Q in block column QB
-    // 1. row Q + 1, then publish it (entries at columns <= Q)
-    if (qr < 7) {
-      rtrtri_row<QB, QB>(R, f, r, mine && ly + 8 * QB > Q);
-#pragma unroll
-      for (int b = 0; b <= QB; ++b) *(ly == qr + 1 ? &rowv[lx + 8 * b] : &dummy[lane]) = R[QB][b];
-    } else if constexpr (QB < 7) {
-      rtrtri_row<QB, QB + 1>(R, f, r, mine);
-#pragma unroll
-      for (int b = 0; b <= QB; ++b) *(ly == 0 ? &rowv[lx + 8 * b] : &dummy[lane]) = R[QB + 1][b];
+    if (J + 1 < PB) C = mfma64(f, row, C);
+    piv[rr] = own ? d : piv[rr];
+    if (J + 1 < PB) {
+      d = __builtin_fma(-(c10 * rd), c10, c11);
+      rd = recip(d);
     }
-    order_fence();
-    // 2. the next step's reads
-    if (Q + 1 < 64) {
-#pragma unroll
-      for (int b = 0; b < 8; ++b) rowr[b] = rowv[min(lx + 8 * b, 63)];
-#pragma unroll
-      for (int a = 0; a < 8; ++a) coll[a] = L[o + ly + 8 * a][o + Q + 1];
-      inv = rinv[Q + 1];
-    }
-    order_fence();
-    // 3. the remaining block rows
-#pragma unroll
-    for (int a = QB; a < 8; ++a) {
-      if (a == QB && qr < 7) continue;
-      if (a == QB + 1 && qr == 7) continue;
-#pragma unroll
-      for (int b = 0; b <= QB; ++b) R[a][b] = __builtin_fma(-f[a], r[b], R[a][b]);
-      R[a][QB] = (mine && ly + 8 * a > Q) ? -f[a] : R[a][QB];
-    }
+    X = mfma64(f, xrow, X);
   }
-}
-
-static __device__ __forceinline__ void wave_trtri64(LdsBlock* L, int o, int ly, int lx, int lane,
-                                                    double* rinv, double* colv, double* rowv,
-                                                    double* dummy) {
-  (void)colv;
-  rinv[lane] = recip(L[o + lane][o + lane]);
-  double R[8][8];
+  int first = PB;   // row of this lane's first bad pivot
 #pragma unroll
-  for (int a = 0; a < 8; ++a)
-#pragma unroll
-    for (int b = 0; b < 8; ++b) R[a][b] = L[o + ly + 8 * a][o + lx + 8 * b];
-  wave_step_fence();
-  double rowr[8], coll[8], inv;
-#pragma unroll
-  for (int b = 0; b < 8; ++b) rowr[b] = 0.0;   // row 0 has no entries left of the diagonal
-#pragma unroll
-  for (int a = 0; a < 8; ++a) coll[a] = L[o + ly + 8 * a][o];
-  inv = rinv[0];
-  order_fence();
-  rtrtri_block<0>(R, L, o, rowv, rinv, dummy, ly, lx, lane, rowr, coll, inv);
-  rtrtri_block<1>(R, L, o, rowv, rinv, dummy, ly, lx, lane, rowr, coll, inv);
-  rtrtri_block<2>(R, L, o, rowv, rinv, dummy, ly, lx, lane, rowr, coll, inv);
-  rtrtri_block<3>(R, L, o, rowv, rinv, dummy, ly, lx, lane, rowr, coll, inv);
-  rtrtri_block<4>(R, L, o, rowv, rinv, dummy, ly, lx, lane, rowr, coll, inv);
-  rtrtri_block<5>(R, L, o, rowv, rinv, dummy, ly, lx, lane, rowr, coll, inv);
-  rtrtri_block<6>(R, L, o, rowv, rinv, dummy, ly, lx, lane, rowr, coll, inv);
-  rtrtri_block<7>(R, L, o, rowv, rinv, dummy, ly, lx, lane, rowr, coll, inv);
-  wave_step_fence();
-  // row i scaled by 1/L[i][i] below the diagonal; the diagonal becomes 1/L[i][i]
-#pragma unroll
-  for (int a = 0; a < 8; ++a) {
-    const int i = ly + 8 * a;
-    const double ri = rinv[i];
-#pragma unroll
-    for (int b = 0; b < 8; ++b) {
-      const int c = lx + 8 * b;
-      L[o + i][o + c] = c < i ? R[a][b] * ri : (c == i ? ri : 0.0);
-    }
+  for (int r = 3; r >= 0; --r) {
+    const int i = lt + 4 * r;
+    const bool bad = !(piv[r] > 0.0) || !std::isfinite(piv[r]);
+    if (bad && i < nvalid) first = i;
+    const double s = bad ? __builtin_nan("") : recip_sqrt(piv[r]);
+    X[r] = i >= li ? X[r] * s : 0.0;
   }
-  wave_step_fence();
-}
-
-// C = A B for 64 x 64 operands held in the LDS block, on FP64 MFMA: wave
-// (wy, wx) computes the 32 x 32 quadrant of C at (32 wy, 32 wx).
-// A[i][p] = L[ar + i][ac + p]; B[p][j] = L[br + p][bc + j], or with BT the
-// transposed access B[p][j] = L[br + j][bc + p].
-template <bool BT>
-static __device__ __forceinline__ void lds_mm64(LdsBlock* L, int ar, int ac, int br, int bc,
-                                                int wy, int wx, int lane, f64x4 (&acc)[2][2]) {
+  if (__any(first < PB)) {   // the rows of lane groups 0 .. 3 interleave
+    int f = first;
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int y = 0; y < 2; ++y) acc[x][y] = f64x4{0.0, 0.0, 0.0, 0.0};
-  const int li = lane & 15, lk = lane >> 4;
-#pragma unroll 4
-  for (int kk = 0; kk < 64; kk += 4) {
-    const int p = kk + lk;
-    double a[2], b[2];
-#pragma unroll
-    for (int x = 0; x < 2; ++x) a[x] = L[ar + 32 * wy + 16 * x + li][ac + p];
-#pragma unroll
-    for (int y = 0; y < 2; ++y)
-      b[y] = BT ? L[br + 32 * wx + 16 * y + li][bc + p] : L[br + p][bc + 32 * wx + 16 * y + li];
-#pragma unroll
-    for (int x = 0; x < 2; ++x)
-#pragma unroll
-      for (int y = 0; y < 2; ++y) acc[x][y] = mfma64(a[x], b[y], acc[x][y]);
+    for (int o = 16; o < 64; o <<= 1) f = min(f, __shfl_xor(f, o));
+    if (lane == 0 && *info == 0) *info = gbase + 1 + f;
   }
+  return X;
 }
-
-// Row / column of entry r of accumulator (x, y) in lane `lane` (see mfma64).
-#define SORF_MM_ROW(wy, x, lane, r) (32 * (wy) + 16 * (x) + ((lane) >> 4) + 4 * (r))
-#define SORF_MM_COL(wx, y, lane) (32 * (wx) + 16 * (y) + ((lane) & 15))
 
 // Factor the diagonal block at (k, k) and write the inverse of
 // L into Linv[k / NB] (the diagonal block of L itself is not needed again:
-// the panel solve and the sweeps use the inverse). 256 threads.
-//   L = [L11 0; L21 L22]:  L11 = chol(A11), L21 = A21 L11^{-T},
-//   L22 = chol(A22 - L21 L21^T);  L^{-1} = [X11 0; -X22 L21 X11, X22].
-__global__ __launch_bounds__(256) void potrf_diag_kernel(double* __restrict__ A, int32_t D, int32_t k,
-                                                        int32_t* __restrict__ info,
-                                                        double* __restrict__ Linv,
-                                                        double* __restrict__ LinvT) {
+// the panel solve and the sweeps use the inverse). 512 threads. In parts,
+//   X_jj = chol(A_jj)^{-1}                      A_jj updated by the parts left of it
+//   L_ij = A_ij X_jj^T                          i > j
+//   A_il -= L_ij L_lj^T                         j < l <= i
+//   X_jc = -X_jj sum_{c <= p < j} L_jp X_pc     c < j
+// Step j between two barriers: wave 0 forms L_j,j-1 and X_jj, bringing what
+// they need up to date with the panels j - 2 and j - 1 itself. The helper
+// waves form L_i,j-1 for i > j, apply panel j - 2 to the columns >= j, finish
+// block row j - 1 of the inverse and sum the products of row j that exist.
+// A helper owns the columns c of the inverse, so it waits for no other one.
+// X_jc is stored in the block's upper half, at part (c, j): L_jc is still read.
+__global__ __launch_bounds__(512) void potrf_diag_kernel(const double* __restrict__ A, int32_t D,
+                                                        int32_t k, int32_t* __restrict__ info,
+                                                        double* __restrict__ Linv) {
   __shared__ double L[NB][LDL];
-  __shared__ double piv[64];
-  __shared__ double dummy[64];
-  __shared__ double colv[64], rowv[64];
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wv = tid >> 6;
-  const int wy = wv >> 1, wx = wv & 1;
-  const int ly = lane >> 3, lx = lane & 7;
+  const int lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lt = lane >> 4;
   const int n = (D - k) < NB ? (D - k) : NB;
+  const int np = (n + PB - 1) / PB;   // parts that reach into the matrix
   // rows past the matrix are padded with the identity; every thread issues
-  // its 64 loads (column lane, rows wv + 4 m) before it stores any
+  // its loads (columns lane and lane + 64 of the lower part, rows wv + 8 m)
+  // before it stores any
   {
     const int64_t gj0 = k + min(lane, n - 1), gj1 = k + min(lane + 64, n - 1);
+    double v0[16], v1[8];
 #pragma unroll
-    for (int m0 = 0; m0 < 32; m0 += 16) {
-      double v0[16], v1[16];
+    for (int m = 0; m < 16; ++m) {
+      const int64_t gi = k + min(wv + 8 * m, n - 1);
+      v0[m] = A[gi * D + gj0];
+      if (m >= 8) v1[m - 8] = A[gi * D + gj1];
+    }
 #pragma unroll
-      for (int m = 0; m < 16; ++m) {
-        const int64_t gi = k + min(wv + 4 * (m0 + m), n - 1);
-        v0[m] = A[gi * D + gj0];
-        v1[m] = A[gi * D + gj1];
-      }
-#pragma unroll
-      for (int m = 0; m < 16; ++m) {
-        const int i = wv + 4 * (m0 + m);
-        L[i][lane] = (i < n && lane <= i) ? v0[m] : (i == lane ? 1.0 : 0.0);
-        L[i][lane + 64] = (i < n && lane + 64 <= i) ? v1[m] : (i == lane + 64 ? 1.0 : 0.0);
-      }
+    for (int m = 0; m < 16; ++m) {
+      const int i = wv + 8 * m;
+      L[i][lane] = (i < n && lane <= i) ? v0[m] : (i == lane ? 1.0 : 0.0);
+      if (m >= 8)
+        L[i][lane + 64] = (i < n && lane + 64 <= i) ? v1[m - 8] : (i == lane + 64 ? 1.0 : 0.0);
     }
   }
   __syncthreads();
-  if (wv == 0) wave_potrf64(L, 0, ly, lx, lane, piv, colv, dummy, info, k, n);
-  __syncthreads();
-  if (wv == 0) wave_trtri64(L, 0, ly, lx, lane, piv, colv, rowv, dummy);   // X11 = L11^{-1} in place
-  __syncthreads();
-  f64x4 acc[2][2];
-  // L21 = A21 X11^T
-  lds_mm64<true>(L, 64, 0, 0, 0, wy, wx, lane, acc);
-  __syncthreads();
-#pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int y = 0; y < 2; ++y)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        L[64 + SORF_MM_ROW(wy, x, lane, r)][SORF_MM_COL(wx, y, lane)] = acc[x][y][r];
-  __syncthreads();
-  // A22 -= L21 L21^T (lower part)
-  lds_mm64<true>(L, 64, 0, 64, 0, wy, wx, lane, acc);
-#pragma unroll
-  for (int x = 0; x < 2; ++x)
-#pragma unroll
-    for (int y = 0; y < 2; ++y)
+  const f64x4 zero = {0.0, 0.0, 0.0, 0.0};
+  const int helper = wv == 0 || wv == 4 ? -1 : (wv < 4 ? wv - 1 : wv - 2);   // 0 .. 5
+  f64x4 S[2] = {zero, zero};   // a helper's sums of a block row of the inverse
+  for (int j = 0; j <= np; ++j) {
+    if (wv == 0 && j < np) {
+      f64x4 C;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const int i = SORF_MM_ROW(wy, x, lane, r), j = SORF_MM_COL(wx, y, lane);
-        if (j <= i) L[64 + i][64 + j] -= acc[x][y][r];
+        const int i = lt + 4 * r;
+        C[r] = L[PB * j + max(i, li)][PB * j + min(i, li)];
       }
-  __syncthreads();
-  if (wv == 0) wave_potrf64(L, 64, ly, lx, lane, piv, colv, dummy, info, k + 64, n - 64);
-  __syncthreads();
-  if (wv == 0) wave_trtri64(L, 64, ly, lx, lane, piv, colv, rowv, dummy);   // X22 = L22^{-1} in place
-  __syncthreads();
-  // T = L21 X11, stored over L21
-  lds_mm64<false>(L, 64, 0, 0, 0, wy, wx, lane, acc);
-  __syncthreads();
+      if (j > 0) {
+        // T = (A_j,j-1)^T and then (L_j,j-1)^T = X T in the accumulator layout, whose
+        // register s is what the MFMA reads as k = 4 s + lt of either operand
+        f64x4 T, u = zero;
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+        for (int r = 0; r < 4; ++r) T[r] = L[PB * j + li][PB * (j - 1) + lt + 4 * r];
+        if (j > 1) {
+          const f64x4 t =
+              part_nt(&L[PB * (j - 1)][PB * (j - 2)], &L[PB * j][PB * (j - 2)], li, lt, zero);
+          u = part_nt(&L[PB * j][PB * (j - 2)], &L[PB * j][PB * (j - 2)], li, lt, zero);
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
+          for (int r = 0; r < 4; ++r) T[r] -= t[r];
+        }
+        f64x4 P = zero;
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        L[64 + SORF_MM_ROW(wy, x, lane, r)][SORF_MM_COL(wx, y, lane)] = acc[x][y][r];
-  __syncthreads();
-  // X21 = -X22 T, stored over T
-  lds_mm64<false>(L, 64, 64, 64, 0, wy, wx, lane, acc);
-  __syncthreads();
+        for (int s = 0; s < 4; ++s)
+          P = mfma64(L[PB * (j - 1) + li][PB * (j - 1) + 4 * s + lt], T[s], P);
 #pragma unroll
-  for (int x = 0; x < 2; ++x)
+        for (int s = 0; s < 4; ++s) u = mfma64(P[s], P[s], u);
 #pragma unroll
-    for (int y = 0; y < 2; ++y)
+        for (int r = 0; r < 4; ++r) {
+          L[PB * j + li][PB * (j - 1) + lt + 4 * r] = P[r];
+          C[r] -= u[r];
+        }
+      }
+      C = part_factor_inverse(C, li, lt, lane, info, k + PB * j, n - PB * j);
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        L[64 + SORF_MM_ROW(wy, x, lane, r)][SORF_MM_COL(wx, y, lane)] = -acc[x][y][r];
-  __syncthreads();
+      for (int r = 0; r < 4; ++r) L[PB * j + lt + 4 * r][PB * j + li] = C[r];
+    } else if (helper >= 0 && j > 0) {
+      // panel j - 1 below part (j, j - 1), and panel j - 2's update of the columns >= j
+      // but for part (j, j): the parts of the lower half dealt from the last helper down
+      // (with j == 1 the panel only)
+      const int l1 = j == 1 ? 0 : np - 1;
+      int i = j + 1, l = j - 1 + (5 - helper);
+      for (;; l += 6) {
+        while (i < np && l > min(i, l1)) l -= min(i, l1) - (j - 1) + 1, ++i;
+        if (i >= np) break;
+        if (l == j - 1) {
+          f64x4 u;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) u[r] = L[PB * i + li][PB * l + lt + 4 * r];
+          if (j > 1) {
+            const f64x4 w =
+                part_nt(&L[PB * l][PB * (j - 2)], &L[PB * i][PB * (j - 2)], li, lt, zero);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) u[r] -= w[r];
+          }
+          f64x4 P = zero;
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            P = mfma64(L[PB * l + li][PB * l + 4 * s + lt], u[s], P);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) L[PB * i + li][PB * l + lt + 4 * r] = P[r];
+        } else {
+          const f64x4 u =
+              part_nt(&L[PB * i][PB * (j - 2)], &L[PB * l][PB * (j - 2)], li, lt, zero);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) L[PB * i + lt + 4 * r][PB * l + li] -= u[r];
+        }
+      }
+#pragma unroll
+      for (int v = 0; v < 2; ++v) {
+        const int c = helper + 6 * v;
+        if (c < j - 1) {   // block row j - 1: the last product and the diagonal part
+          S[v] = part_nn(&L[PB * (j - 1)][PB * (j - 2)], &L[PB * c][PB * (j - 2)], li, lt, S[v]);
+          f64x4 x = zero;
+#pragma unroll
+          for (int s = 0; s < 4; ++s)
+            x = mfma64(L[PB * (j - 1) + li][PB * (j - 1) + 4 * s + lt], S[v][s], x);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) L[PB * c + lt + 4 * r][PB * (j - 1) + li] = -x[r];
+        }
+        S[v] = zero;
+        if (j < np)        // block row j: all products but the one with L_j,j-1
+          for (int p = c; p < j - 1; ++p)
+            S[v] = part_nn(&L[PB * j][PB * p], &L[PB * c][PB * p], li, lt, S[v]);
+      }
+    }
+    __syncthreads();
+  }
   double* out = Linv + int64_t(k / NB) * NB * NB;
-  (void)LinvT;   // transposed by transpose_blocks_kernel after the factorisation
 #pragma unroll 8
-  for (int m = 0; m < 32; ++m) {
-    const int i = wv + 4 * m;
+  for (int m = 0; m < 16; ++m) {
+    const int i = wv + 8 * m;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       const int j = lane + 64 * h;
-      out[i * NB + j] = (i < n && j <= i) ? L[i][j] : 0.0;
+      // part (i / 16, j / 16) of the inverse, from the upper half's part (j / 16, i / 16)
+      const int rj = j & ~(PB - 1), ri = i & ~(PB - 1);
+      out[i * NB + j] = (i < n && j <= i) ? L[rj + i - ri][ri + j - rj] : 0.0;
     }
   }
 }
@@ -1374,8 +1253,7 @@ static hipError_t launch_solve(int32_t D, const TG* G, const TG* Zty, double lam
   const bool two = side != nullptr;
   if (!two) side = st;
   hipError_t e = hipSuccess;
-  hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, st, w.A, D, 0, info, w.Linv,
-                     w.LinvT);
+  hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(512), 0, st, w.A, D, 0, info, w.Linv);
   for (int32_t k = 0; k + NB < D; k += NB) {
     const int64_t rest = int64_t(D) - k - NB;
     const int64_t nt = (rest + 127) / 128;
@@ -1401,8 +1279,8 @@ static hipError_t launch_solve(int32_t D, const TG* G, const TG* Zty, double lam
                            n_sub);
       }
     }
-    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(256), 0, st, w.A, D, k + NB, info,
-                       w.Linv, w.LinvT);
+    hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(512), 0, st, w.A, D, k + NB, info,
+                       w.Linv);
     if (two && side_work && (e = hipStreamWaitEvent(st, ev_next, 0)) != hipSuccess) return e;
   }
   // the last far update (if any) before the sweeps read L
