@@ -64,7 +64,7 @@ struct SolveWs {
   double* y;     // [D]
   double* dx;    // [D]
   double* part;  // [nt][nt][64] partial sums of the symmetric product
-  int32_t* pflags;  // [8] strip flags of the panel kernel, then of syrk_next (epoch = block + 1)
+  int32_t* pflags;  // [8] strip flags of the panel kernel, [8] of syrk_next (epoch = block + 1)
 };
 
 static size_t align256(size_t n) { return (n + 255) & ~size_t(255); }
@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void promote_kernel(const TG* __restrict__ G, 
   const int64_t i = blockIdx.y;
   const int64_t j = int64_t(blockIdx.x) * 256 + threadIdx.x;
   if (i == 0 && j == 0) *info = 0;
-  if (i == 0 && j < 8) pflags[j] = 0;
+  if (i == 0 && j < 16) pflags[j] = 0;
   if (i == 0 && j < D) signal_store(y + j, not_ready());   // output of the first forward sweep
   if (j <= i && j < D) A[i * D + j] = double(G[i * D + j]) + (i == j ? lambda : 0.0);
 }
@@ -398,510 +398,403 @@ __global__ __launch_bounds__(256) void transpose_blocks_kernel(const double* __r
     }
 }
 
-// Next block row of the panel, fused with the update of the next diagonal
-// tile: workgroup b (0..3) computes the 32 rows
-// L21 = A21 (L11^{-1})^T starting at k + NB + 32 b (8 waves of 16 x 32, 1 x 2 FP64 MFMA blocks; the inverse
-// block sits in LDS; each lane loads its A operands for all of K at once,
-// four consecutive k per row: the MFMA's k index t = lane / 16 stands for
-// k = kb + 4 t + s in step s, and the B operands use the same order).
-// (The panel rows below the next block row are formed by syrk_next.) Each
-// workgroup publishes its rows (agent release, then flags[b] = epoch), waits for the lower-numbered ones (which
-// are dispatched first, so the waits end), and then applies
-//   A[r][c] -= sum_p L21[r][p] L21[c][p]
-// to its 32 rows r of the next diagonal tile and the columns c <= r. The
-// next diagonal block is therefore updated when the kernel ends, with the
-// tile work spread over four compute units. A wait longer than
-// kPanelWaitTicks (100 MHz counter) sets *info = -1 and stops waiting.
-constexpr int PLD = NB + 4;   // LDS row stride of the panel kernel (doubles)
-constexpr int kSyrkGrid = 248;   // 8 of the 256 compute units stay free for the chain
-constexpr int PR = 32;        // rows per panel workgroup
-constexpr uint64_t kPanelWaitTicks = uint64_t(1) << 28;   // about 2.7 s
+// Trailing update A22 -= L21 L21^T on the lower triangle: tile (I, J) of the
+// trailing matrix, 128 x 128, starts at block row/column k/NB + 1 + I/J.
+constexpr int ST = 128;
 
+// Strips of PR = 16 rows of the panel, the building block of the two kernels
+// below. A workgroup forms its strip L_s = A_s (L_kk^{-1})^T, wave w the
+// columns [16 w, +16), K = NB in 32 MFMAs straight from registers: each lane
+// reads its operands from memory itself (the MFMA's slot k = lane / 16 of
+// product 4 u + e stands for column 16 u + 4 (lane / 16) + e, for both
+// operands: a lane reads 32 consecutive bytes, four lanes a line), and no wave reads what
+// another one reads but for the 16 KB of the strip. Both products of a strip
+// are so short that latency bounds them; what counts is the number of
+// dependent steps. Strips of 32 rows with the inverse in LDS took 43,000
+// cycles a panel: 10,000 to load, 12,700 and 11,000 for the products (with
+// bank conflicts, two blocks a wave), the rest for the exchange.
+constexpr int kSyrkGrid = 248;   // 8 of the 256 compute units stay free for the chain
+constexpr int PR = 16;        // rows of a strip
+constexpr int kStrips = NB / PR;
+constexpr uint64_t kPanelWaitTicks = uint64_t(1) << 28;   // about 2.7 s
+typedef double StripRows[PR][NB + 2];   // 16-byte aligned rows, 16 of them on distinct LDS banks
+
+// Operands of one lane: row `row` of 128 columns from p (rows of A need not
+// be 16-byte aligned).
+static __device__ __forceinline__ void strip_operand(const double* p, int lt, double2 (&v)[16]) {
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    v[u].x = p[16 * (u >> 1) + 4 * lt + 2 * (u & 1)];
+    v[u].y = p[16 * (u >> 1) + 4 * lt + 2 * (u & 1) + 1];
+  }
+}
+static __device__ __forceinline__ f64x4 strip_product(const double2 (&a)[16],
+                                                      const double2 (&b)[16]) {
+  f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    acc = mfma64(a[u].x, b[u].x, acc);
+    acc = mfma64(a[u].y, b[u].y, acc);
+  }
+  return acc;
+}
+
+// Forms the NS strips from row r0 on in A and in sP. 512 threads; ends without a barrier.
+template <int NS>
+static __device__ __forceinline__ void form_strips(double* __restrict__ A, int32_t D, int32_t k,
+                                                   const double* __restrict__ Linv, int64_t r0,
+                                                   StripRows (&sP)[NS], int wv, int li, int lt) {
+  double2 a[NS][16], b[16];
+#pragma unroll
+  for (int j = 0; j < NS; ++j)
+    strip_operand(A + min(r0 + PR * j + li, int64_t(D) - 1) * D + k, lt, a[j]);
+  strip_operand(Linv + (int64_t(k / NB) * NB + 16 * wv + li) * NB, lt, b);
+  // the strips are stored in place: every wave has its operands before any wave stores
+  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < NS; ++j) {
+    const f64x4 acc = strip_product(a[j], b);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t row = r0 + PR * j + lt + 4 * r;
+      sP[j][lt + 4 * r][16 * wv + li] = acc[r];
+      if (row < D) A[row * D + k + 16 * wv + li] = acc[r];
+    }
+  }
+}
+
+// A wave's 16 x 16 entries at (r0, c0), lower part inside the matrix.
+static __device__ __forceinline__ void read_block(const double* __restrict__ A, int32_t D,
+                                                  int64_t r0, int64_t c0, int li, int lt,
+                                                  double (&c)[4]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+    c[r] = A[min(r0 + lt + 4 * r, int64_t(D) - 1) * D + min(c0 + li, int64_t(D) - 1)];
+}
+static __device__ __forceinline__ void write_block(double* __restrict__ A, int32_t D, int64_t r0,
+                                                   int64_t c0, int li, int lt,
+                                                   const double (&c)[4], f64x4 acc) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int64_t gi = r0 + lt + 4 * r, gj = c0 + li;
+    if (gi < D && gi >= gj) A[gi * D + gj] = c[r] - acc[r];
+  }
+}
+
+// Publishes the strips that this workgroup stored (flags = epoch).
+static __device__ __forceinline__ void publish_strips(int32_t* flags, int n, int32_t epoch) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __syncthreads();
+  if (int(threadIdx.x) < n)
+    __hip_atomic_store(flags + threadIdx.x, epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One wave waits for a strip of a workgroup with a lower index, which is
+// dispatched first, so the wait ends; past kPanelWaitTicks of the 100 MHz
+// counter it sets *info = -1 and goes on.
+static __device__ __forceinline__ void await_strip(const int32_t* flag, int32_t epoch,
+                                                   int32_t* info) {
+  const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+  while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch) {
+    if (__builtin_amdgcn_s_memrealtime() - t0 > kPanelWaitTicks) {
+      int32_t expect = 0;
+      __hip_atomic_compare_exchange_strong(info, &expect, -1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_AGENT);
+      break;
+    }
+    __builtin_amdgcn_s_sleep(1);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+}
+
+// Next block row of the panel, fused with the update of the next diagonal
+// tile: workgroup b (0 .. 7) forms strip b of the block row below (k, k) and
+// publishes it (flags[b] = epoch), then wave w <= b applies strip w to the
+// 16 x 16 part (b, w) of the tile, for which it waits for that strip alone.
+// The next diagonal block is therefore updated when the kernel ends, with
+// the tile work spread over eight compute units. (The panel rows below the
+// next block row are formed by syrk_next.) 27 us before, now 14 (21 beside
+// the far update of D = 8192, which takes most of the memory path).
 __global__ __launch_bounds__(512) void panel_kernel(double* __restrict__ A, int32_t D, int32_t k,
                                                    const double* __restrict__ Linv,
                                                    int32_t* __restrict__ flags,
                                                    int32_t* __restrict__ info) {
-  __shared__ double sL[NB][PLD];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int wy = wv >> 2, wx = wv & 3;   // rows [16 wy, +16), columns [32 wx, +32)
+  __shared__ __attribute__((aligned(16))) StripRows sP[1];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int li = lane & 15, lt = lane >> 4;
   const int b = int(blockIdx.x);
-  const int64_t r0 = int64_t(k) + NB + int64_t(b) * PR;
-  const double* inv = Linv + int64_t(k / NB) * NB * NB;
-  for (int t = tid; t < NB * NB / 2; t += 512) {
-    const int j = t >> 6, p = (t & 63) * 2;
-    const double2 v = *reinterpret_cast<const double2*>(inv + j * NB + p);
-    sL[j][p] = v.x;
-    sL[j][p + 1] = v.y;
-  }
-  double ar[8][4];
-  {
-    const int64_t row = r0 + 16 * wy + li;
-    const bool ok = row < D;
-    const double* src = A + (ok ? row : int64_t(D) - 1) * D + k + 4 * lt;
-#pragma unroll
-    for (int kb = 0; kb < 8; ++kb)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const double v = src[16 * kb + s];   // rows of A need not be 16-byte aligned
-        ar[kb][s] = ok ? v : 0.0;
-      }
-  }
-  __syncthreads();
-  f64x4 acc[2];
-  acc[0] = acc[1] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-  for (int kb = 0; kb < 8; ++kb) {
-    double br[2][4];
-#pragma unroll
-    for (int c = 0; c < 2; ++c)
-#pragma unroll
-      for (int s = 0; s < 4; ++s) br[c][s] = sL[32 * wx + 16 * c + li][16 * kb + 4 * lt + s];
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int c = 0; c < 2; ++c) acc[c] = mfma64(ar[kb][s], br[c][s], acc[c]);
-  }
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t row = r0 + 16 * wy + lt + 4 * r;
-      if (row < D) A[row * D + k + 32 * wx + 16 * c + li] = acc[c][r];
-    }
-  // publish this strip of the next block row
   const int32_t epoch = k / NB + 1;
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-  __syncthreads();
-  if (tid == 0) __hip_atomic_store(flags + b, epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-  // wait for the strips above it
-  if (tid == 0) {
-    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-    for (int q = 0; q < b; ++q) {
-      while (__hip_atomic_load(flags + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < epoch) {
-        if (__builtin_amdgcn_s_memrealtime() - t0 > kPanelWaitTicks) {
-          int32_t expect = 0;
-          __hip_atomic_compare_exchange_strong(info, &expect, -1, __ATOMIC_RELAXED,
-                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          break;
-        }
-        __builtin_amdgcn_s_sleep(1);
-      }
-    }
+  const int64_t s0 = int64_t(k) + NB, r0 = s0 + PR * b, c0 = s0 + PR * wv;
+  double c[4];
+  read_block(A, D, r0, c0, li, lt, c);
+  form_strips<1>(A, D, k, Linv, r0, sP, wv, li, lt);
+  publish_strips(flags + b, 1, epoch);
+  if (wv > b) return;
+  double2 av[16], bv[16];
+  if (wv < b) {
+    await_strip(flags + wv, epoch, info);
+    strip_operand(A + min(c0 + li, int64_t(D) - 1) * D + k, lt, bv);
+  } else {
+    strip_operand(sP[0][li], lt, bv);
   }
-  __syncthreads();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-  // rows 0 .. 32 (b + 1) - 1 of the next block row of L, into LDS
-  const int nrow = PR * (b + 1);
-  const int64_t rb = int64_t(k) + NB;
-  for (int t = tid; t < nrow * (NB / 2); t += 512) {
-    const int i = t >> 6, p = (t & 63) * 2;
-    const int64_t row = rb + i;
-    const bool ok = row < D;
-    const double* src = A + (ok ? row : int64_t(D) - 1) * D + k + p;
-    const double v0 = src[0], v1 = src[1];
-    sL[i][p] = ok ? v0 : 0.0;
-    sL[i][p + 1] = ok ? v1 : 0.0;
-  }
-  __syncthreads();
-  // rows 32 b + 16 wy + [0, 16), columns 32 wx + [0, 32): only blocks that reach the lower part
-  const int ib = PR * b + 16 * wy;
-  if (32 * wx > ib + 15) return;
-  f64x4 cc[2];
-  cc[0] = cc[1] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 2
-  for (int kb = 0; kb < 8; ++kb) {
-    double pa[4], pb[2][4];
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      pa[s] = sL[ib + li][16 * kb + 4 * lt + s];
-#pragma unroll
-      for (int c = 0; c < 2; ++c) pb[c][s] = sL[32 * wx + 16 * c + li][16 * kb + 4 * lt + s];
-    }
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-#pragma unroll
-      for (int c = 0; c < 2; ++c) cc[c] = mfma64(pa[s], pb[c][s], cc[c]);
-  }
-#pragma unroll
-  for (int c = 0; c < 2; ++c)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int i = ib + lt + 4 * r, j = 32 * wx + 16 * c + li;
-      const int64_t gi = rb + i, gj = rb + j;
-      if (gi < D && i >= j) A[gi * D + gj] -= cc[c][r];
-    }
-}
-
-// Trailing update A22 -= L21 L21^T on the lower triangle: 128 x 128 tiles,
-// 8 waves of 32 x 64 (2 x 4 MFMA blocks), K = NB in chunks of 32 via LDS with
-// a register double buffer. Each wave loads its entries of the tile before
-// the products, so the read of A22 overlaps them. On a diagonal tile the
-// waves whose block lies above the diagonal only help with the loads.
-// Tile (I, J) of the trailing matrix starts at block row/column k/NB + 1 + I/J.
-constexpr int ST = 128, SKC = 32;
-typedef double SyrkSlab[ST][SKC + 1];
-
-static __device__ __forceinline__ void syrk_tile(double* __restrict__ A, int32_t D, int32_t k,
-                                                 int64_t I, int64_t J, SyrkSlab& sI,
-                                                 SyrkSlab& sJ) {
-  constexpr int T = ST, KC = SKC;
-  const bool diag = (I == J);
-  const int64_t s0 = int64_t(k) + NB;
-  const int64_t I0 = s0 + I * T, J0 = s0 + J * T;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wv = tid >> 6;
-  const int wy = wv >> 1, wx = wv & 1;  // rows [32 wy, +32), columns [64 wx, +64)
-  const bool idle = diag && (32 * wy + 31 < 64 * wx);
-  const int lr = tid >> 2;          // row 0..127 of the slab
-  const int lp = (tid & 3) * 8;     // 8 consecutive k
-  const bool okI = I0 + lr < D, okJ = J0 + lr < D;
-  const double* pI = A + min(I0 + lr, int64_t(D) - 1) * D + k + lp;
-  const double* pJ = A + min(J0 + lr, int64_t(D) - 1) * D + k + lp;
-  double rI[8], rJ[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const double a = pI[q], b = pJ[q];
-    rI[q] = okI ? a : 0.0;
-    rJ[q] = okJ ? b : 0.0;
-  }
-  // this wave's entries of the tile (lower part inside the matrix)
-  double c[2][4][4];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t gi = I0 + wy * 32 + a * 16 + (lane >> 4) + 4 * r;
-        const int64_t gj = J0 + wx * 64 + b * 16 + (lane & 15);
-        const bool ok = !idle && gi < D && gj < D && gi >= gj;
-        c[a][b][r] = ok ? A[gi * D + gj] : 0.0;
-      }
-  f64x4 acc[2][4];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
-  for (int c0 = 0; c0 < NB; c0 += KC) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      sI[lr][lp + q] = rI[q];
-      if (!diag) sJ[lr][lp + q] = rJ[q];
-    }
-    __syncthreads();
-    if (c0 + KC < NB) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const double a = pI[c0 + KC + q], b = pJ[c0 + KC + q];
-        rI[q] = okI ? a : 0.0;
-        rJ[q] = okJ ? b : 0.0;
-      }
-    }
-    const double (*sb)[KC + 1] = diag ? sI : sJ;
-    if (!idle) {
-#pragma unroll
-      for (int kk = 0; kk < KC; kk += 4) {
-        const int p = kk + (lane >> 4);
-        double av[2], bv[4];
-#pragma unroll
-        for (int a = 0; a < 2; ++a) av[a] = sI[wy * 32 + a * 16 + (lane & 15)][p];
-#pragma unroll
-        for (int b = 0; b < 4; ++b) bv[b] = sb[wx * 64 + b * 16 + (lane & 15)][p];
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int b = 0; b < 4; ++b) acc[a][b] = mfma64(av[a], bv[b], acc[a][b]);
-      }
-    }
-    __syncthreads();
-  }
-  if (idle) return;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 4; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t gi = I0 + wy * 32 + a * 16 + (lane >> 4) + 4 * r;
-        const int64_t gj = J0 + wx * 64 + b * 16 + (lane & 15);
-        if (gi < D && gj < D && gi >= gj) A[gi * D + gj] = c[a][b][r] - acc[a][b][r];
-      }
-}
-
-// Rows [RP h, RP h + RP) of tile (I, J), RP = 128 / NP: the same update as
-// syrk_tile with the 8 waves on RP / 16 x 128 / (16 BB) blocks of 16 x 16 (BB
-// MFMA blocks each), so that a tile takes NP workgroups. On a diagonal tile
-// the rows are rows RP h .. of the J slab.
-template <int NP>
-static __device__ __forceinline__ void syrk_part_tile(double* __restrict__ A, int32_t D,
-                                                      int32_t k, int64_t I, int64_t J, int h,
-                                                      SyrkSlab& sI, SyrkSlab& sJ) {
-  constexpr int KC = SKC;
-  constexpr int RP = ST / NP;            // rows of the part
-  constexpr int WYN = RP / 16;           // wave rows
-  constexpr int WC = ST / (8 / WYN);     // columns per wave
-  constexpr int BB = WC / 16;            // MFMA blocks per wave
-  static_assert(WYN >= 1 && WYN <= 8 && BB >= 1, "part shape");
-  const bool diag = (I == J);
-  const int64_t s0 = int64_t(k) + NB;
-  const int64_t J0 = s0 + J * ST, I0 = s0 + I * ST + RP * h;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wv = tid >> 6;
-  const int wy = wv % WYN, wx = wv / WYN;   // rows [16 wy, +16) of the part, columns [WC wx, +WC)
-  const bool idle = diag && (RP * h + 16 * wy + 15 < WC * wx);
-  const int lr = tid >> 2;          // row 0..127 of the J slab (0..RP-1 of the I slab)
-  const int lp = (tid & 3) * 8;     // 8 consecutive k
-  const bool loadI = !diag && lr < RP;
-  const bool okI = I0 + lr < D, okJ = J0 + lr < D;
-  const double* pI = A + min(I0 + (lr % RP), int64_t(D) - 1) * D + k + lp;
-  const double* pJ = A + min(J0 + lr, int64_t(D) - 1) * D + k + lp;
-  double rI[8], rJ[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const double a = pI[q], b = pJ[q];
-    rI[q] = okI ? a : 0.0;
-    rJ[q] = okJ ? b : 0.0;
-  }
-  double c[BB][4];
-#pragma unroll
-  for (int b = 0; b < BB; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t gi = I0 + wy * 16 + (lane >> 4) + 4 * r;
-      const int64_t gj = J0 + wx * WC + b * 16 + (lane & 15);
-      const bool ok = !idle && gi < D && gj < D && gi >= gj;
-      c[b][r] = ok ? A[gi * D + gj] : 0.0;
-    }
-  f64x4 acc[BB];
-#pragma unroll
-  for (int b = 0; b < BB; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
-  // A operand: row 16 wy + (lane & 15) of the I slab, or row RP h + ... of the J slab
-  const double (*sa)[KC + 1] = diag ? sJ : sI;
-  const int ra = (diag ? RP * h : 0) + wy * 16 + (lane & 15);
-  for (int c0 = 0; c0 < NB; c0 += KC) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      if (loadI) sI[lr][lp + q] = rI[q];
-      sJ[lr][lp + q] = rJ[q];
-    }
-    __syncthreads();
-    if (c0 + KC < NB) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const double a = pI[c0 + KC + q], b = pJ[c0 + KC + q];
-        rI[q] = okI ? a : 0.0;
-        rJ[q] = okJ ? b : 0.0;
-      }
-    }
-    if (!idle) {
-#pragma unroll
-      for (int kk = 0; kk < KC; kk += 4) {
-        const int p = kk + (lane >> 4);
-        const double av = sa[ra][p];
-        double bv[BB];
-#pragma unroll
-        for (int b = 0; b < BB; ++b) bv[b] = sJ[wx * WC + b * 16 + (lane & 15)][p];
-#pragma unroll
-        for (int b = 0; b < BB; ++b) acc[b] = mfma64(av, bv[b], acc[b]);
-      }
-    }
-    __syncthreads();
-  }
-  if (idle) return;
-#pragma unroll
-  for (int b = 0; b < BB; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t gi = I0 + wy * 16 + (lane >> 4) + 4 * r;
-      const int64_t gj = J0 + wx * WC + b * 16 + (lane & 15);
-      if (gi < D && gj < D && gi >= gj) A[gi * D + gj] = c[b][r] - acc[b][r];
-    }
+  strip_operand(sP[0][li], lt, av);
+  write_block(A, D, r0, c0, li, lt, c, strip_product(av, bv));
 }
 
 // The part of the trailing update that the next panel reads, fused with the
 // panel rows it needs. Tiles of the trailing matrix's first block column
-// below its diagonal, (I, 0) for I >= 1, each in kNextParts workgroups of
-// RP = 32 rows: a workgroup first forms its 32 panel rows
-// L_I = A_I (L_kk^{-1})^T (K = NB in chunks of 32 through LDS, the same
-// products as the panel kernel), stores them in A and keeps them in LDS, then
-// updates its rows of the tile with C -= L_I L_0^T, L_0 being the next block
-// row that the chain's panel kernel wrote. The last kNextParts workgroups
-// update the diagonal tile (1, 1) of the block after next (the tile (0, 0) is
-// updated by the panel kernel) once the workgroups of tile (1, 0) have
-// published L_1 (flags[4 + h] = epoch): those have lower indices and are
-// dispatched first, so the wait ends; past kPanelWaitTicks it sets *info = -1.
-// Splitting tiles into row parts keeps most compute units busy on these few
-// tiles, and forming the panel rows here saves a launch and a pass over them.
-constexpr int kNextParts = 4;
-constexpr int kNextRows = ST / kNextParts;   // 32
+// below its diagonal, (I, 0) for I >= 1, each in kStrips / NS workgroups: a
+// workgroup forms NS strips of L_I and updates its rows of the tile with
+// C -= L_I L_0^T, L_0 being the next block row that the chain's panel kernel
+// wrote. The last kStrips workgroups update the diagonal tile (1, 1) of the
+// block after next (the tile (0, 0) is updated by the panel kernel) once the
+// workgroups of tile (1, 0) have published L_1 (flags[8 + h] = epoch).
+// NS = 1 while every compute unit takes one workgroup, the shortest chain;
+// above that 2, since a workgroup reads the 256 KB of L_kk^{-1} and L_0
+// whatever its number of strips (63 tiles: 32 us against 39 with NS = 1).
+// Tiles in four parts of 32 rows with operands through LDS took 19.5 us at
+// D = 1000, now 17; at D = 8192 24 on average against 22, the price of one
+// shape for the short steps, where the chain waits for this kernel.
+template <int NS>
 __global__ __launch_bounds__(512) void syrk_next_kernel(double* __restrict__ A, int32_t D,
                                                        int32_t k, int32_t nt,
                                                        const double* __restrict__ Linv,
                                                        int32_t* __restrict__ flags,
                                                        int32_t* __restrict__ info) {
-  __shared__ SyrkSlab sI, sJ;
-  __shared__ double sP[kNextRows][NB + 1];
-  constexpr int KC = SKC, RP = kNextRows, WC = 32, BB = 2;
-  const int64_t t = blockIdx.x / kNextParts;
-  const int h = int(blockIdx.x % kNextParts);
+  __shared__ __attribute__((aligned(16))) StripRows sP[NS];
+  constexpr int kParts = kStrips / NS;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int li = lane & 15, lt = lane >> 4;
+  const int n_first = (nt - 1) * kParts;   // workgroups of the first block column
   const int32_t epoch = k / NB + 1;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  if (t + 1 >= nt) {   // diagonal tile (1, 1): wait for L_1
-    if (tid == 0) {
-      const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-      for (int q = 0; q < kNextParts; ++q) {
-        while (__hip_atomic_load(flags + 4 + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
-               epoch) {
-          if (__builtin_amdgcn_s_memrealtime() - t0 > kPanelWaitTicks) {
-            int32_t expect = 0;
-            __hip_atomic_compare_exchange_strong(info, &expect, -1, __ATOMIC_RELAXED,
-                                                 __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            break;
-          }
-          __builtin_amdgcn_s_sleep(1);
-        }
-      }
-    }
-    __syncthreads();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    syrk_part_tile<kNextParts>(A, D, k, 1, 1, h, sI, sJ);
+  const int64_t s0 = int64_t(k) + NB;
+  double c[NS][4];
+  double2 av[16], bv[16];
+  if (int(blockIdx.x) >= n_first) {   // diagonal tile (1, 1)
+    const int h = int(blockIdx.x) - n_first;
+    if (wv > h) return;
+    const int64_t r0 = s0 + NB + PR * h, c0 = s0 + NB + PR * wv;
+    if (r0 >= D) return;
+    read_block(A, D, r0, c0, li, lt, c[0]);
+    await_strip(flags + 8 + h, epoch, info);
+    strip_operand(A + min(r0 + li, int64_t(D) - 1) * D + k, lt, av);
+    if (wv < h) await_strip(flags + 8 + wv, epoch, info);
+    strip_operand(A + min(c0 + li, int64_t(D) - 1) * D + k, lt, bv);
+    write_block(A, D, r0, c0, li, lt, c[0], strip_product(av, bv));
     return;
   }
-  const int64_t I = t + 1;
-  const int64_t s0 = int64_t(k) + NB;
-  const int64_t R0 = s0 + I * ST + RP * h;   // first row of this part
-  const int wy = wv & 1, wx = wv >> 1;       // rows [16 wy, +16), columns [32 wx, +32)
-  const int lr = tid >> 2;                   // row 0..127 of the J slab (0..31 of the I slab)
-  const int lp = (tid & 3) * 8;              // 8 consecutive k
-  // 1. panel rows: sI <- A rows R0 + lr (columns k ..), sJ <- rows of L_kk^{-1}
-  {
-    const bool okI = R0 + lr < D;
-    const double* pI = A + min(R0 + (lr % RP), int64_t(D) - 1) * D + k + lp;
-    const double* pJ = Linv + int64_t(k / NB) * NB * NB + lr * NB + lp;
-    double rI[8], rJ[8];
+  const int64_t t = blockIdx.x / kParts;
+  const int h = int(blockIdx.x % kParts) * NS;
+  const int64_t r0 = s0 + ST * (t + 1) + PR * h, c0 = s0 + PR * wv;
+  if (r0 >= D) return;   // nobody waits for a strip past the matrix
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const double a = pI[q];
-      rI[q] = okI ? a : 0.0;
-      rJ[q] = pJ[q];
-    }
-    f64x4 acc[BB];
-#pragma unroll
-    for (int b = 0; b < BB; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
-    for (int c0 = 0; c0 < NB; c0 += KC) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        if (lr < RP) sI[lr][lp + q] = rI[q];
-        sJ[lr][lp + q] = rJ[q];
-      }
-      __syncthreads();
-      if (c0 + KC < NB) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const double a = pI[c0 + KC + q];
-          rI[q] = okI ? a : 0.0;
-          rJ[q] = pJ[c0 + KC + q];
-        }
-      }
-#pragma unroll
-      for (int kk = 0; kk < KC; kk += 4) {
-        const int p = kk + (lane >> 4);
-        const double av = sI[wy * 16 + (lane & 15)][p];
-        double bv[BB];
-#pragma unroll
-        for (int b = 0; b < BB; ++b) bv[b] = sJ[wx * WC + b * 16 + (lane & 15)][p];
-#pragma unroll
-        for (int b = 0; b < BB; ++b) acc[b] = mfma64(av, bv[b], acc[b]);
-      }
-      __syncthreads();
-    }
-#pragma unroll
-    for (int b = 0; b < BB; ++b)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int i = wy * 16 + (lane >> 4) + 4 * r, j = wx * WC + b * 16 + (lane & 15);
-        sP[i][j] = acc[b][r];
-        if (R0 + i < D) A[(R0 + i) * D + k + j] = acc[b][r];
-      }
-  }
-  if (I == 1) {   // publish this part of L_1 for the diagonal tile's workgroups
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  for (int j = 0; j < NS; ++j) read_block(A, D, r0 + PR * j, c0, li, lt, c[j]);
+  form_strips<NS>(A, D, k, Linv, r0, sP, wv, li, lt);
+  if (t == 0)
+    publish_strips(flags + 8 + h, NS, epoch);
+  else
     __syncthreads();
-    if (tid == 0) __hip_atomic_store(flags + 4 + h, epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+  strip_operand(A + (c0 + li) * D + k, lt, bv);
+#pragma unroll
+  for (int j = 0; j < NS; ++j) {
+    strip_operand(sP[j][li], lt, av);
+    write_block(A, D, r0 + PR * j, c0, li, lt, c[j], strip_product(av, bv));
   }
-  __syncthreads();
-  if (R0 >= D) return;
-  // 2. C -= L_I L_0^T on rows R0 .., columns J0 .. of the tile (I, 0)
-  const int64_t J0 = s0;
-  const bool okJ = J0 + lr < D;
-  const double* pJ = A + min(J0 + lr, int64_t(D) - 1) * D + k + lp;
-  double rJ[8];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) {
-    const double b = pJ[q];
-    rJ[q] = okJ ? b : 0.0;
-  }
-  double c[BB][4];
-#pragma unroll
-  for (int b = 0; b < BB; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t gi = R0 + wy * 16 + (lane >> 4) + 4 * r;
-      const int64_t gj = J0 + wx * WC + b * 16 + (lane & 15);
-      c[b][r] = gi < D && gj < D ? A[gi * D + gj] : 0.0;
-    }
-  f64x4 acc[BB];
-#pragma unroll
-  for (int b = 0; b < BB; ++b) acc[b] = f64x4{0.0, 0.0, 0.0, 0.0};
-  for (int c0 = 0; c0 < NB; c0 += KC) {
-#pragma unroll
-    for (int q = 0; q < 8; ++q) sJ[lr][lp + q] = rJ[q];
-    __syncthreads();
-    if (c0 + KC < NB) {
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        const double b = pJ[c0 + KC + q];
-        rJ[q] = okJ ? b : 0.0;
-      }
-    }
-#pragma unroll
-    for (int kk = 0; kk < KC; kk += 4) {
-      const int p = kk + (lane >> 4);
-      const double av = sP[wy * 16 + (lane & 15)][c0 + p];
-      double bv[BB];
-#pragma unroll
-      for (int b = 0; b < BB; ++b) bv[b] = sJ[wx * WC + b * 16 + (lane & 15)][p];
-#pragma unroll
-      for (int b = 0; b < BB; ++b) acc[b] = mfma64(av, bv[b], acc[b]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int b = 0; b < BB; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t gi = R0 + wy * 16 + (lane >> 4) + 4 * r;
-      const int64_t gj = J0 + wx * WC + b * 16 + (lane & 15);
-      if (gi < D && gj < D) A[gi * D + gj] = c[b][r] - acc[b][r];
-    }
 }
 
 // The rest of the trailing update, tiles (I, J) with 1 <= J <= I other than
-// (1, 1), in a persistent grid of at most kSyrkGrid workgroups: workgroup w
-// takes the tiles w, w + G, ... of the sub-triangle's row-major order after
-// (1, 1). The grid stays below the number of compute units so that the panel
-// and diagonal kernels of the next steps find free units while it runs.
+// (1, 1). The grid of at most kSyrkGrid workgroups stays below the number of
+// compute units so that the panel and diagonal kernels of the next steps find
+// free units while it runs.
+//
+// A workgroup takes an equal run of the units of 128 rows x 32 columns, in
+// row-major order. Its eight waves keep their 16 panel rows for all of
+// K = NB in registers (64 of them) while the run stays in one block row, and
+// the 32 rows of L_J of one unit after the other come through a ring of
+// kFarRing LDS slots, copied there without registers, kFarRing - 1 units
+// ahead, with one barrier a unit. The entries of the unit are read one unit
+// ahead and written when it ends.
+// Bound by the FP64 matrix cores (4 us a unit at 64 to 67 cycles an MFMA),
+// next by the entries' own traffic (64 KB read and written a unit, 2.3 ms of
+// a solve of D = 8192 at the rate of a copy), which this order spreads
+// evenly: in whole tiles of 128 x 128 every workgroup's 128 KB came and went
+// in the same moment and the matrix cores waited for it. Whole lines of L_J
+// are copied (1 KB a row); 64 consecutive bytes a lane through registers
+// touched 64 cache lines a load. Runs of units leave no round of tiles nearly
+// empty. Sum over a solve of D = 8192: 5.6 ms with tiles through registers,
+// 4.6 with tiles through LDS copies, now 4.4.
+//
+// In an LDS row, pair p of columns sits at p ^ (row % 16): the 16 rows that a
+// group of lanes reads fall on distinct banks, without padding, which a
+// 16-byte copy cannot leave. The MFMA's slot k = lane / 16 of product 2 u + e
+// stands for column 8 u + 2 (lane / 16) + e, for both operands.
+// EVEN: rows of A are 16-byte aligned; else 4-byte copies, four times as many.
+constexpr int kFarCols = 32, kFarRing = 4;
+static __device__ __forceinline__ double& at(double* base, uint32_t bytes) {
+  return *reinterpret_cast<double*>(reinterpret_cast<char*>(base) + bytes);
+}
+static __device__ __forceinline__ void dma16(const void* g, void* lds) {
+  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds, 16, 0, 0);
+}
+static __device__ __forceinline__ void dma4(const void* g, void* lds) {
+  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void*)lds, 4, 0, 0);
+}
+
+// Unit q of block row r of the sub-triangle from tile (1, 1): rows
+// k + NB + ST (r + 1) .., columns k + NB + ST + kFarCols q ..
+struct FarUnit {
+  int64_t r, q;
+  static constexpr int64_t kPerTile = ST / kFarCols;
+  __device__ void set(int64_t u) {   // kPerTile r (r + 1) / 2 units before row r
+    int64_t I, J;
+    tri_tile(u / kPerTile, I, J);
+    r = I;
+    q = J * kPerTile + u % kPerTile;
+  }
+  __device__ void next() {
+    if (++q == kPerTile * (r + 1)) {
+      q = 0;
+      ++r;
+    }
+  }
+};
+
+template <bool EVEN>
 __global__ __launch_bounds__(512) void syrk_far_kernel(double* __restrict__ A, int32_t D,
                                                       int32_t k, int64_t n_sub) {
-  __shared__ SyrkSlab sI, sJ;
-  for (int64_t t = 1 + int64_t(blockIdx.x); t < n_sub; t += gridDim.x) {
-    int64_t I, J;
-    tri_tile(t, I, J);
-    syrk_tile(A, D, k, I + 1, J + 1, sI, sJ);
-    __syncthreads();   // the next tile reuses the LDS slabs
+  constexpr int kRow = NB * 8, kSlot = kFarCols * kRow;   // bytes
+  constexpr int kAhead = kFarRing - 1;
+  __shared__ __attribute__((aligned(16))) char ring[kFarRing][kSlot];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lt = lane >> 4;
+  const int64_t s0 = int64_t(k) + NB + ST;
+  // the workgroups of an XCD (b % 8) take neighbouring runs
+  const int64_t G = gridDim.x, x = blockIdx.x & 7;
+  const int64_t w = x * (G / 8) + min(x, G % 8) + blockIdx.x / 8;
+  const int64_t n_units = (n_sub - 1) * FarUnit::kPerTile;   // all but tile (1, 1), the first
+  const int64_t u0 = n_units * w / G;
+  const int n = int(n_units * (w + 1) / G - u0);
+  if (n == 0) return;
+  FarUnit cur, ahead, copied;
+  cur.set(u0 + FarUnit::kPerTile);
+  ahead = copied = cur;
+
+  // rows 4 wv .. + 3 of a unit's slot; rows past the matrix repeat its last
+  // one: they only reach entries that are not stored
+  uint32_t oS[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int sw = (4 * wv + i) & 15;
+    oS[i] = EVEN ? uint32_t(lane ^ sw) * 16u : uint32_t((lane >> 2) ^ sw) * 16u + (lane & 3) * 4u;
+  }
+  const auto copy = [&](int slot) {
+    const int64_t col0 = s0 + kFarCols * copied.q + 4 * wv;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      double* src = A + min(col0 + i, int64_t(D) - 1) * D + k;
+      char* dst = ring[slot] + (4 * wv + i) * kRow;
+      if constexpr (EVEN) {
+        dma16(&at(src, oS[i]), dst);
+      } else {
+#pragma unroll
+        for (int p = 0; p < 4; ++p) dma4(&at(src, oS[i] + 256u * p), dst + 256 * p);
+      }
+    }
+    copied.next();
+  };
+  // copies and reads of entries (not the stores) issued after a unit's copies
+  // until its barrier, with kAhead == 3
+  constexpr int kLater = 3 * 8 + 2 * (EVEN ? 4 : 16);
+  static_assert(kAhead == 3 && kLater < 64, "vmcnt range");
+
+  double2 ar[16];
+  const auto load_rows = [&]() {
+    const int64_t row = min(s0 + ST * cur.r + 16 * wv + li, int64_t(D) - 1);
+    const double* src = A + row * D + k + 2 * lt;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      if constexpr (EVEN) {
+        ar[u] = *reinterpret_cast<const double2*>(src + 8 * u);
+      } else {
+        ar[u].x = src[8 * u];
+        ar[u].y = src[8 * u + 1];
+      }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0) here, or every unit waits for its successor's loads
+  };
+  double c0[2][4], c1[2][4];
+  const auto load_entries = [&](const FarUnit& f, double (&v)[2][4]) {
+    const int64_t I0 = s0 + ST * f.r, J0 = s0 + kFarCols * f.q;
+    double* pC = A + I0 * D;
+    const int last = int(min(D - I0, int64_t(ST))) - 1;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t o = uint32_t(min(16 * wv + lt + 4 * r, last)) * uint32_t(D) * 8u;
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+        v[b][r] = at(pC, o + uint32_t(min(J0 + 16 * b + li, int64_t(D) - 1)) * 8u);
+    }
+  };
+
+  for (int s = 0; s < kAhead && s < n; ++s) copy(s);
+  load_rows();
+  load_entries(cur, c0);
+  const uint32_t read0 = uint32_t(li * kRow + 16 * (lt ^ li));
+  const auto unit = [&](int s, double (&c)[2][4], double (&cn)[2][4]) {
+    // this wave's copies for the unit have landed; behind the barrier every
+    // wave's have, and every wave has read the slot that is filled next
+    if (s >= 2 && s + 2 < n)
+      asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLater) : "memory");
+    else
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (s + kAhead < n) copy((s + kAhead) % kFarRing);
+    if (s + 1 < n) ahead.next();
+    load_entries(ahead, cn);   // of the last unit again, at the end
+    const int64_t I0 = s0 + ST * cur.r, J0 = s0 + kFarCols * cur.q;
+    const int64_t below = I0 + 16 * wv - J0;   // the wave's first row against the unit's first column
+    f64x4 acc[2];
+    acc[0] = acc[1] = f64x4{0.0, 0.0, 0.0, 0.0};
+    if (below + 15 >= 0) {   // not above the diagonal
+      const char* slot = ring[s % kFarRing];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) {
+        const char* p = slot + (read0 ^ uint32_t(64 * u));
+        const double2 b0 = *reinterpret_cast<const double2*>(p);
+        const double2 b1 = *reinterpret_cast<const double2*>(p + 16 * kRow);
+        acc[0] = mfma64(ar[u].x, b0.x, acc[0]);
+        acc[1] = mfma64(ar[u].x, b1.x, acc[1]);
+        acc[0] = mfma64(ar[u].y, b0.y, acc[0]);
+        acc[1] = mfma64(ar[u].y, b1.y, acc[1]);
+      }
+      double* pC = A + I0 * D;
+      const uint32_t o = uint32_t(16 * wv + lt) * uint32_t(D) * 8u + uint32_t(J0 + li) * 8u;
+      if (below >= kFarCols - 1 && I0 + ST <= D) {   // strictly below the diagonal, inside the matrix
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            at(pC, o + uint32_t(4 * r) * uint32_t(D) * 8u + 128u * b) = c[b][r] - acc[b][r];
+      } else {
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            if (I0 + 16 * wv + lt + 4 * r < D && below + lt + 4 * r >= 16 * b + li)
+              at(pC, o + uint32_t(4 * r) * uint32_t(D) * 8u + 128u * b) = c[b][r] - acc[b][r];
+      }
+    }
+    const int64_t row = cur.r;
+    cur.next();
+    if (cur.r != row && s + 1 < n) load_rows();
+  };
+  for (int s = 0; s < n; s += 2) {   // the entries' registers change places, not values
+    unit(s, c0, c1);
+    if (s + 1 < n) unit(s + 1, c1, c0);
   }
 }
 
@@ -1269,14 +1162,25 @@ static hipError_t launch_solve(int32_t D, const TG* G, const TG* Zty, double lam
         if ((e = hipEventRecord(ev_panel, st)) != hipSuccess) return e;
         if ((e = hipStreamWaitEvent(side, ev_panel, 0)) != hipSuccess) return e;
       }
-      hipLaunchKernelGGL(syrk_next_kernel, dim3(unsigned(kNextParts * nt)), dim3(512), 0, side,
-                         w.A, D, k, int32_t(nt), w.Linv, w.pflags, info);
+      const bool one = (nt - 1) * kStrips <= 256;   // strips against compute units
+      const int64_t parts = (nt - 1) * (one ? kStrips : kStrips / 2) + kStrips;
+      if (one)
+        hipLaunchKernelGGL(syrk_next_kernel<1>, dim3(unsigned(parts)), dim3(512), 0, side, w.A, D,
+                           k, int32_t(nt), w.Linv, w.pflags, info);
+      else
+        hipLaunchKernelGGL(syrk_next_kernel<2>, dim3(unsigned(parts)), dim3(512), 0, side, w.A, D,
+                           k, int32_t(nt), w.Linv, w.pflags, info);
       if (two && (e = hipEventRecord(ev_next, side)) != hipSuccess) return e;
       const int64_t n_sub = (nt - 1) * nt / 2;   // sub-triangle from (1, 1)
       if (n_sub > 1) {
-        const int64_t g = n_sub - 1 < kSyrkGrid ? n_sub - 1 : kSyrkGrid;
-        hipLaunchKernelGGL(syrk_far_kernel, dim3(unsigned(g)), dim3(512), 0, side, w.A, D, k,
-                           n_sub);
+        const int64_t units = (n_sub - 1) * FarUnit::kPerTile;
+        const int64_t g = units < kSyrkGrid ? units : kSyrkGrid;
+        if (D % 2 == 0)
+          hipLaunchKernelGGL(syrk_far_kernel<true>, dim3(unsigned(g)), dim3(512), 0, side, w.A, D,
+                             k, n_sub);
+        else
+          hipLaunchKernelGGL(syrk_far_kernel<false>, dim3(unsigned(g)), dim3(512), 0, side, w.A, D,
+                             k, n_sub);
       }
     }
     hipLaunchKernelGGL(potrf_diag_kernel, dim3(1), dim3(512), 0, st, w.A, D, k + NB, info,
