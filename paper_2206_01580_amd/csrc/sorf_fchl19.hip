@@ -14,14 +14,14 @@
 //                 below r_cut and 0 beyond.
 //
 // Atoms of molecules of up to 64 atoms take one wave each (see
-// fchl19_forward_small_kernel). Larger molecules: one workgroup (4 waves) per atom. The atom's neighbours (same molecule,
+// fchl19_forward_small_kernel). Larger molecules: one workgroup (16 waves) per atom. The atom's neighbours (same molecule,
 // closer than r_cut) are gathered into LDS grouped by element, in atom order
 // inside each group (ballot compaction, no atomics), with their per-neighbour
 // two-body factors. Two-body bins: one thread per (element, bin) sums its
 // element's neighbours in order. Three-body: the unordered pairs are numbered
 // by element pair (X <= Y), then by position; chunks of pairs get their
 // radial-independent weight (xi3, cutoffs, angle) computed by all threads
-// into LDS, and one thread per (element pair, radial bin) sums its pairs of
+// into LDS, and groups of one thread per radial bin sum equal parts of
 // the chunk in order. Every entry of rho is therefore summed in a fixed order.
 #include <cmath>
 
@@ -65,17 +65,30 @@ __device__ __forceinline__ float fchl_rcp(float x) { return __builtin_amdgcn_rcp
 // element pair (a <= b) -> position in the lexicographic list of pairs
 __device__ __forceinline__ int fchl_pair(int a, int b, int E) { return a * E - a * (a - 1) / 2 + (b - a); }
 
-// Atom i of molecule m (atoms a0 .. a1 - 1).
+// Atom i of molecule m (atoms a0 .. a1 - 1), a workgroup of kFchlThreads.
+//
+// Bound by vector issue: the pair weights (about 150 instructions a pair) and
+// the radial bins (an exponential and about ten instructions a pair and bin).
+// What depends on one neighbour alone (1 / r, r^-N3 f_cut) is formed
+// once per neighbour. The bins of a chunk are split over groups of one thread
+// per radial bin, each with an equal part of the chunk's pairs in order; one
+// thread per (element pair, bin) left all but the largest element pair's
+// threads idle (182 us for the 245 atoms of a cluster, now 37).
+constexpr int kFchlThreads = 1024;
+
 __device__ __forceinline__ void fchl19_forward_atom(
     int64_t i, int64_t a0, int64_t a1, const float* __restrict__ R,
     const int32_t* __restrict__ element, int32_t E, const FchlParams& p, int64_t size,
     float* __restrict__ rho) {
+  constexpr int NT = kFchlThreads, NW = NT / 64;
   __shared__ float nx[kFchlMaxNb], ny[kFchlMaxNb], nz[kFchlMaxNb], nr[kFchlMaxNb];
-  __shared__ float c2[kFchlMaxNb], mu2[kFchlMaxNb], inv2s2[kFchlMaxNb];
+  __shared__ float ni[kFchlMaxNb], nw[kFchlMaxNb], c2[kFchlMaxNb], mu2[kFchlMaxNb], inv2s2[kFchlMaxNb];
   __shared__ int32_t grp[kFchlMaxElements + 1];     // neighbour offsets per element
-  __shared__ int32_t wcount[4];
-  __shared__ int64_t seg[kFchlMaxElements * (kFchlMaxElements + 1) / 2 + 1];
-  __shared__ float pw_c[kFchlPairChunk], pw_s[kFchlPairChunk], pmid[kFchlPairChunk];
+  __shared__ int32_t wcount[2][NW];
+  __shared__ int32_t seg[kFchlMaxElements * (kFchlMaxElements + 1) / 2 + 1];
+  __shared__ int32_t pair_xy[kFchlMaxElements * (kFchlMaxElements + 1) / 2];
+  __shared__ float4 pw[kFchlPairChunk];             // w cos, w sin, mean distance
+  __shared__ float2 tail[NT];
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const float rc = p.rcut;
@@ -83,11 +96,10 @@ __device__ __forceinline__ void fchl19_forward_atom(
   float* __restrict__ out = rho + i * size;
 
   // neighbours grouped by element, atom order inside a group
-  int total = 0;
-  bool overflow = false;
+  int total = 0, turn = 0;
   for (int X = 0; X < E; ++X) {
     if (tid == 0) grp[X] = total;
-    for (int64_t j0 = a0; j0 < a1; j0 += 256) {
+    for (int64_t j0 = a0; j0 < a1; j0 += NT, turn ^= 1) {
       const int64_t j = j0 + tid;
       float dx = 0.f, dy = 0.f, dz = 0.f, r = 0.f;
       bool f = false;
@@ -99,41 +111,59 @@ __device__ __forceinline__ void fchl19_forward_atom(
         f = r < rc;
       }
       const uint64_t mask = __ballot(f);
-      const int before = __popcll(mask & ((uint64_t(1) << lane) - 1));
-      if (lane == 0) wcount[wv] = __popcll(mask);
-      __syncthreads();
-      int off = total;
-      for (int w = 0; w < wv; ++w) off += wcount[w];
-      const int chunk = wcount[0] + wcount[1] + wcount[2] + wcount[3];
-      if (f) {
-        const int slot = off + before;
-        if (slot < kFchlMaxNb) {
-          nx[slot] = dx;
-          ny[slot] = dy;
-          nz[slot] = dz;
-          nr[slot] = r;
-          // two-body factors: f_cut r^-N2 / (sigma sqrt(2 pi)), mu, 1 / (2 sigma^2)
-          const float q = 1.0f + p.eta2 / (r * r);
-          const float s2 = logf(q);
-          c2[slot] = fchl_fcut(r, rc) * powf(r, -p.N2) / (sqrtf(s2) * 2.50662827463100f);
-          mu2[slot] = logf(r / sqrtf(q));
-          inv2s2[slot] = 0.5f / s2;
-        }
+      if (lane == 0) wcount[turn][wv] = __popcll(mask);
+      __syncthreads();   // one a pass: the counts alternate between two buffers
+      int off = total, chunk = 0;
+      for (int w = 0; w < NW; ++w) {
+        off += w < wv ? wcount[turn][w] : 0;
+        chunk += wcount[turn][w];
+      }
+      const int slot = off + __popcll(mask & ((uint64_t(1) << lane) - 1));
+      if (f && slot < kFchlMaxNb) {
+        // f_cut as sin^2(pi (r_cut - r) / (2 r_cut)), without the cancellation of
+        // (cos + 1) / 2 near the cutoff
+        const float sc = sinf(1.57079632679490f * ((rc - r) / rc));
+        const float fc = sc * sc;
+        nx[slot] = dx;
+        ny[slot] = dy;
+        nz[slot] = dz;
+        nr[slot] = r;
+        ni[slot] = 1.0f / r;
+        nw[slot] = powf(r, -p.N3) * fc;
+        // two-body factors: f_cut r^-N2 / (sigma sqrt(2 pi)), mu, 1 / (2 sigma^2)
+        const float q = 1.0f + p.eta2 / (r * r);
+        const float s2 = logf(q);
+        c2[slot] = fc * powf(r, -p.N2) / (sqrtf(s2) * 2.50662827463100f);
+        mu2[slot] = logf(r / sqrtf(q));
+        inv2s2[slot] = 0.5f / s2;
       }
       total += chunk;
-      __syncthreads();
     }
   }
   if (tid == 0) grp[E] = total;
-  overflow = total > kFchlMaxNb;
-  if (overflow) {   // more neighbours than the LDS list holds: mark the row, do not guess
-    for (int64_t t = tid; t < size; t += 256) out[t] = __builtin_nanf("");
+  if (total > kFchlMaxNb) {   // more neighbours than the LDS list holds: mark the row, do not guess
+    for (int64_t t = tid; t < size; t += NT) out[t] = __builtin_nanf("");
     return;
   }
   __syncthreads();
 
+  // three-body: pair numbering by element pair X <= Y
+  const int NP = E * (E + 1) / 2;
+  if (tid == 0) {
+    int32_t o = 0;
+    for (int X = 0; X < E; ++X)
+      for (int Y = X; Y < E; ++Y) {
+        const int P = fchl_pair(X, Y, E);
+        seg[P] = o;
+        pair_xy[P] = X | (Y << 8);
+        const int32_t cx = grp[X + 1] - grp[X], cy = grp[Y + 1] - grp[Y];
+        o += X == Y ? cx * (cx - 1) / 2 : cx * cy;
+      }
+    seg[NP] = o;
+  }
+
   // two-body bins
-  for (int t = tid; t < E * p.n2; t += 256) {
+  for (int t = tid; t < E * p.n2; t += NT) {
     const int X = t / p.n2, k = t % p.n2;
     const float Rk = rc * float(k + 1) / float(p.n2);
     const float lnR = logf(Rk);
@@ -144,112 +174,144 @@ __device__ __forceinline__ void fchl19_forward_atom(
     }
     out[t] = acc / Rk;
   }
-
-  // three-body: pair numbering by element pair X <= Y
-  const int NP = E * (E + 1) / 2;
-  if (tid == 0) {
-    int64_t o = 0;
-    for (int X = 0; X < E; ++X)
-      for (int Y = X; Y < E; ++Y) {
-        seg[fchl_pair(X, Y, E)] = o;
-        const int64_t cx = grp[X + 1] - grp[X], cy = grp[Y + 1] - grp[Y];
-        o += X == Y ? cx * (cx - 1) / 2 : cx * cy;
-      }
-    seg[NP] = o;
-  }
   __syncthreads();
-  const int64_t n_pairs = seg[NP];
+  const int32_t n_pairs = seg[NP];
   const float angw = 2.0f * expf(-0.5f * p.zeta * p.zeta) * sqrtf(p.eta3 / 3.14159265358979f);
-  const int nbins = NP * p.n3;
-  // rounds of 512 (element pair, radial bin) outputs, two per thread
-  for (int t0 = 0; t0 < nbins; t0 += 512) {
-    float acc_c[2] = {0.f, 0.f}, acc_s[2] = {0.f, 0.f};
-    for (int64_t q0 = 0; q0 < n_pairs; q0 += kFchlPairChunk) {
-      const int64_t q1 = q0 + kFchlPairChunk < n_pairs ? q0 + kFchlPairChunk : n_pairs;
-      for (int64_t q = q0 + tid; q < q1; q += 256) {
-        // pair q -> element pair P (row X, column Y) -> neighbours (a, b)
-        int P = 0;
-        while (q >= seg[P + 1]) ++P;
-        int X = 0;
-        while (fchl_pair(X, X, E) + (E - X) <= P) ++X;
-        const int Y = X + (P - fchl_pair(X, X, E));
-        const int64_t loc = q - seg[P];
-        int a, b;
-        if (X != Y) {
-          const int cy = grp[Y + 1] - grp[Y];
-          a = grp[X] + int(loc / cy);
-          b = grp[Y] + int(loc % cy);
-        } else {
-          // loc -> (u, v), u < v; row u starts at u (2 cx - u - 1) / 2
-          const int cx = grp[X + 1] - grp[X];
-          const double c2x = 2.0 * cx - 1.0;
-          int u = int((c2x - sqrt(c2x * c2x - 8.0 * double(loc))) * 0.5);
-          if (u < 0) u = 0;
-          while (u > 0 && int64_t(u) * (2 * cx - u - 1) / 2 > loc) --u;
-          while (int64_t(u + 1) * (2 * cx - u - 2) / 2 <= loc) ++u;
-          a = grp[X] + u;
-          b = grp[X] + u + 1 + int(loc - int64_t(u) * (2 * cx - u - 1) / 2);
-        }
-        const float rij = nr[a], rik = nr[b];
-        const float jx = nx[b] - nx[a], jy = ny[b] - ny[a], jz = nz[b] - nz[a];
-        const float rjk = sqrtf(jx * jx + jy * jy + jz * jz);
-        const float cos_i = (nx[a] * nx[b] + ny[a] * ny[b] + nz[a] * nz[b]) / (rij * rik);
-        const float cos_j = -(nx[a] * jx + ny[a] * jy + nz[a] * jz) / (rij * rjk);
-        const float cos_k = (nx[b] * jx + ny[b] * jy + nz[b] * jz) / (rik * rjk);
-        const float sin_i = sqrtf(fmaxf(0.0f, 1.0f - cos_i * cos_i));
-        const float xi3 = p.c3 * (1.0f + 3.0f * cos_i * cos_j * cos_k) / powf(rij * rjk * rik, p.N3);
-        const float w = xi3 * fchl_fcut(rij, rc) * fchl_fcut(rjk, rc) * fchl_fcut(rik, rc) * angw;
-        const int sl = int(q - q0);
-        pw_c[sl] = w * cos_i;
-        pw_s[sl] = w * sin_i;
-        pmid[sl] = 0.5f * (rij + rik);
+  const float c3w = p.c3 * angw;
+  float* __restrict__ out3 = out + int64_t(E) * p.n2;
+  // element pairs without pairs
+  for (int t = tid; t < NP * p.n3; t += NT) {
+    const int P = t / p.n3;
+    if (seg[P] == seg[P + 1]) {
+      out3[2 * t] = 0.0f;
+      out3[2 * t + 1] = 0.0f;
+    }
+  }
+  // G groups of n3 threads, thread kl of a group on radial bin kl; group g
+  // walks the g-th of G equal parts of a chunk. An element pair whose pairs
+  // fall in several parts is finished by the group where it ends, which adds
+  // the earlier groups' partial sums in group order. With more radial bins
+  // than threads the threads of one group loop over them.
+  const int G = p.n3 <= NT ? NT / p.n3 : 1;
+  const int g = p.n3 <= NT ? tid / p.n3 : 0;
+  const int kl = p.n3 <= NT ? tid % p.n3 : tid;
+  const float keta = -p.eta3 * 1.44269504088896341f;
+  int P = 0, Q0 = 0;   // non-decreasing over the chunks
+  for (int32_t q0 = 0; q0 < n_pairs; q0 += kFchlPairChunk) {
+    const int32_t q1 = q0 + kFchlPairChunk < n_pairs ? q0 + kFchlPairChunk : n_pairs;
+    for (int32_t q = q0 + tid; q < q1; q += NT) {
+      // pair q -> element pair P (row X, column Y) -> neighbours (a, b)
+      while (q >= seg[P + 1]) ++P;
+      const int X = pair_xy[P] & 255, Y = pair_xy[P] >> 8;
+      const int32_t loc = q - seg[P];
+      int a, b;
+      if (X != Y) {
+        const int cy = grp[Y + 1] - grp[Y];
+        int u = int(float(loc) * fchl_rcp(float(cy)));   // loc / cy or one beside it
+        u -= u * cy > loc ? 1 : 0;
+        u += (u + 1) * cy <= loc ? 1 : 0;
+        a = grp[X] + u;
+        b = grp[Y] + loc - u * cy;
+      } else {
+        // loc -> (u, v), u < v; row u starts at u (2 cx - u - 1) / 2
+        const int cx = grp[X + 1] - grp[X];
+        const float c2x = 2.0f * float(cx) - 1.0f;
+        int u = int((c2x - __builtin_amdgcn_sqrtf(c2x * c2x - 8.0f * float(loc))) * 0.5f);
+        u = u < 0 ? 0 : u;
+        while (u > 0 && u * (2 * cx - u - 1) / 2 > loc) --u;
+        while ((u + 1) * (2 * cx - u - 2) / 2 <= loc) ++u;
+        a = grp[X] + u;
+        b = grp[X] + u + 1 + (loc - u * (2 * cx - u - 1) / 2);
       }
-      __syncthreads();
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int t = t0 + tid + 256 * h;
-        if (t < nbins) {
-          const int P = t / p.n3, k = t % p.n3;
-          const float Rk = rc * float(k) / float(p.n3 - 1);
-          const int64_t lo = seg[P] > q0 ? seg[P] : q0;
-          const int64_t hi = seg[P + 1] < q1 ? seg[P + 1] : q1;
-          float c = acc_c[h], sn = acc_s[h];
-          for (int64_t q = lo; q < hi; ++q) {
-            const int sl = int(q - q0);
-            const float d = pmid[sl] - Rk;
-            const float g = fchl_exp(-p.eta3 * d * d);
-            c += pw_c[sl] * g;
-            sn += pw_s[sl] * g;
+      const float rij = nr[a], rik = nr[b];
+      const float ax = nx[a], ay = ny[a], az = nz[a], bx = nx[b], by = ny[b], bz = nz[b];
+      const float jx = bx - ax, jy = by - ay, jz = bz - az;
+      const float rjk = sqrtf(jx * jx + jy * jy + jz * jz);
+      float ijk = fchl_rcp(rjk);
+      ijk = __builtin_fmaf(__builtin_fmaf(-rjk, ijk, 1.0f), ijk, ijk);
+      const float iij = ni[a], iik = ni[b];
+      const float cos_i = (ax * bx + ay * by + az * bz) * (iij * iik);
+      const float cos_j = -(ax * jx + ay * jy + az * jz) * (iij * ijk);
+      const float cos_k = (bx * jx + by * jy + bz * jz) * (iik * ijk);
+      const float sin_i = sqrtf(fmaxf(0.0f, 1.0f - cos_i * cos_i));
+      const float w = c3w * (1.0f + 3.0f * cos_i * cos_j * cos_k) * (nw[a] * nw[b]) *
+                      (__builtin_amdgcn_exp2f(-p.N3 * __builtin_amdgcn_logf(rjk)) *
+                       fchl_fcut(rjk, rc));
+      pw[q - q0] = make_float4(w * cos_i, w * sin_i, 0.5f * (rij + rik), 0.0f);
+    }
+    __syncthreads();
+    const int32_t L = q1 - q0;
+    int pend = -1;                      // element pair to finish after the tails are stored
+    float pc = 0.f, ps = 0.f;
+    for (int k = kl; k < p.n3 && g < G; k += NT) {
+      const float Rk = rc * float(k) / float(p.n3 - 1);
+      const int32_t lo = q0 + L * g / G, hi = q0 + L * (g + 1) / G;
+      while (Q0 < NP && seg[Q0 + 1] <= lo) ++Q0;
+      int Q = Q0;
+      bool started = Q < NP && (seg[Q] > q0 ? seg[Q] : q0) >= lo;
+      float c = 0.f, sn = 0.f;
+      for (int32_t q = lo; q < hi;) {
+        const int32_t segend = seg[Q + 1] < q1 ? seg[Q + 1] : q1;
+        const int32_t stop = segend < hi ? segend : hi;
+#pragma unroll 4
+        for (; q < stop; ++q) {
+          const float4 w = pw[q - q0];
+          const float d = w.z - Rk;
+          const float gk = __builtin_amdgcn_exp2f(keta * (d * d));
+          c = __builtin_fmaf(w.x, gk, c);
+          sn = __builtin_fmaf(w.y, gk, sn);
+        }
+        if (q == segend) {              // element pair Q ends in this part
+          if (started) {
+            float* o = out3 + 2 * (int64_t(Q) * p.n3 + k);
+            const bool first = seg[Q] >= q0;
+            o[0] = first ? c : o[0] + c;
+            o[1] = first ? sn : o[1] + sn;
+          } else {
+            pend = Q;
+            pc = c;
+            ps = sn;
           }
-          acc_c[h] = c;
-          acc_s[h] = sn;
+          c = 0.f;
+          sn = 0.f;
+          ++Q;
+          while (Q < NP && seg[Q + 1] <= q) ++Q;
+          started = true;
         }
       }
-      __syncthreads();
+      tail[tid] = make_float2(c, sn);   // open partial at the end of the part (0 if none)
     }
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const int t = t0 + tid + 256 * h;
-      if (t < nbins) {
-        float* o = out + int64_t(E) * p.n2 + 2 * int64_t(t);
-        o[0] = acc_c[h];
-        o[1] = acc_s[h];
+    __syncthreads();
+    if (pend >= 0) {
+      const int32_t st = seg[pend] > q0 ? seg[pend] : q0;
+      int gs = g - 1;                   // the group in whose part the element pair starts
+      while (gs > 0 && q0 + L * gs / G > st) --gs;
+      float sc = 0.f, ss = 0.f;
+      for (int gg = gs; gg < g; ++gg) {
+        sc += tail[gg * p.n3 + kl].x;
+        ss += tail[gg * p.n3 + kl].y;
       }
+      float* o = out3 + 2 * (int64_t(pend) * p.n3 + kl);
+      const bool first = seg[pend] >= q0;
+      o[0] = first ? sc + pc : o[0] + (sc + pc);
+      o[1] = first ? ss + ps : o[1] + (ss + ps);
     }
+    __syncthreads();   // weights and tails are reused, and the next chunk adds to these entries
   }
 }
 
 // Atoms of larger molecules: a persistent grid in which every workgroup reads
-// the molecule sizes 256 at a time (coalesced), collects the molecules above
+// the molecule sizes kFchlThreads at a time (coalesced), collects the molecules above
 // kFchlSmallMol atoms with ballots, and gives a whole workgroup to atom j of
 // such a molecule m when (m + j) mod grid is its own index, so that the atoms
 // of one large molecule spread over consecutive workgroups.
-__global__ __launch_bounds__(256) void fchl19_forward_kernel(
+__global__ __launch_bounds__(kFchlThreads) void fchl19_forward_kernel(
     const float* __restrict__ R, const int32_t* __restrict__ element,
     const int64_t* __restrict__ mol_ptr, int64_t n_mols, int32_t E, FchlParams p,
     int64_t size, float* __restrict__ rho) {
-  __shared__ int32_t big[256];
-  __shared__ int32_t wbig[4];
+  constexpr int NT = kFchlThreads, NW = NT / 64;
+  __shared__ int32_t big[NT];
+  __shared__ int32_t wbig[NW];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int64_t G = gridDim.x, b = blockIdx.x;
   int64_t lo = 0, hi = 0;
@@ -257,19 +319,19 @@ __global__ __launch_bounds__(256) void fchl19_forward_kernel(
     lo = mol_ptr[tid];
     hi = mol_ptr[tid + 1];
   }
-  for (int64_t m0 = 0; m0 < n_mols; m0 += 256) {
+  for (int64_t m0 = 0; m0 < n_mols; m0 += NT) {
     const int64_t m = m0 + tid;
     const bool large = m < n_mols && hi - lo > kFchlSmallMol;
     // next group's sizes in flight while this group is processed
-    if (m + 256 < n_mols) {
-      lo = mol_ptr[m + 256];
-      hi = mol_ptr[m + 257];
+    if (m + NT < n_mols) {
+      lo = mol_ptr[m + NT];
+      hi = mol_ptr[m + NT + 1];
     }
     const uint64_t mask = __ballot(large);
     if (lane == 0) wbig[wv] = __popcll(mask);
     __syncthreads();
     int off = 0, nbig = 0;
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < NW; ++w) {
       off += w < wv ? wbig[w] : 0;
       nbig += wbig[w];
     }
@@ -1050,10 +1112,10 @@ hipError_t sorf_launch_fchl19_forward(const float* R, const int32_t* element,
     if (e != hipSuccess) return e;
   }
   if (n_mols == 0) return hipSuccess;
-  // three workgroups of this kernel fit a compute unit (LDS), 256 units: the
-  // whole grid is resident, so the size scan runs once
-  const int64_t grid = n_atoms < 768 ? n_atoms : 768;
-  hipLaunchKernelGGL(fchl19_forward_kernel, dim3(unsigned(grid)), dim3(256), 0, st, R, element,
+  // one workgroup of this kernel fits a compute unit (registers), 256 units:
+  // the whole grid is resident, so the size scan runs once
+  const int64_t grid = n_atoms < 256 ? n_atoms : 256;
+  hipLaunchKernelGGL(fchl19_forward_kernel, dim3(unsigned(grid)), dim3(kFchlThreads), 0, st, R, element,
                      mol_ptr, n_mols, E, p, size, rho);
   return hipGetLastError();
 }
