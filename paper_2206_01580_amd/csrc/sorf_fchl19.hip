@@ -65,6 +65,24 @@ __device__ __forceinline__ float fchl_rcp(float x) { return __builtin_amdgcn_rcp
 // element pair (a <= b) -> position in the lexicographic list of pairs
 __device__ __forceinline__ int fchl_pair(int a, int b, int E) { return a * E - a * (a - 1) / 2 + (b - a); }
 
+// loc / c for 0 <= loc < 2^18 and c >= 1: the FP32 quotient is off by one at most.
+__device__ __forceinline__ int fchl_div(int loc, int c) {
+  int u = int(float(loc) * fchl_rcp(float(c)));
+  u -= u * c > loc ? 1 : 0;
+  u += (u + 1) * c <= loc ? 1 : 0;
+  return u;
+}
+// Row u of the pairs (u, v), u < v < n, numbered row by row; row u starts at u (2 n - u - 1) / 2.
+// (n at most 512, so the discriminant is exact in FP32)
+__device__ __forceinline__ int fchl_pair_row(int loc, int n) {
+  const float c2n = 2.0f * float(n) - 1.0f;
+  int u = int((c2n - __builtin_amdgcn_sqrtf(c2n * c2n - 8.0f * float(loc))) * 0.5f);
+  u = u < 0 ? 0 : (u > n - 2 ? n - 2 : u);
+  while (u > 0 && u * (2 * n - u - 1) / 2 > loc) --u;
+  while ((u + 1) * (2 * n - u - 2) / 2 <= loc) ++u;
+  return u;
+}
+
 // Atom i of molecule m (atoms a0 .. a1 - 1), a workgroup of kFchlThreads.
 //
 // Bound by vector issue: the pair weights (about 150 instructions a pair) and
@@ -207,19 +225,12 @@ __device__ __forceinline__ void fchl19_forward_atom(
       int a, b;
       if (X != Y) {
         const int cy = grp[Y + 1] - grp[Y];
-        int u = int(float(loc) * fchl_rcp(float(cy)));   // loc / cy or one beside it
-        u -= u * cy > loc ? 1 : 0;
-        u += (u + 1) * cy <= loc ? 1 : 0;
+        const int u = fchl_div(loc, cy);
         a = grp[X] + u;
         b = grp[Y] + loc - u * cy;
       } else {
-        // loc -> (u, v), u < v; row u starts at u (2 cx - u - 1) / 2
         const int cx = grp[X + 1] - grp[X];
-        const float c2x = 2.0f * float(cx) - 1.0f;
-        int u = int((c2x - __builtin_amdgcn_sqrtf(c2x * c2x - 8.0f * float(loc))) * 0.5f);
-        u = u < 0 ? 0 : u;
-        while (u > 0 && u * (2 * cx - u - 1) / 2 > loc) --u;
-        while ((u + 1) * (2 * cx - u - 2) / 2 <= loc) ++u;
+        const int u = fchl_pair_row(loc, cx);
         a = grp[X] + u;
         b = grp[X] + u + 1 + (loc - u * (2 * cx - u - 1) / 2);
       }
@@ -593,16 +604,26 @@ __global__ __launch_bounds__(256) void fchl19_forward_small_kernel(
 // it from every centre, so a single large molecule spreads over the chip.
 // Every gradient entry is summed in a fixed order (deterministic, no atomics).
 // ---------------------------------------------------------------------------
+typedef float FchlPair __attribute__((ext_vector_type(2), aligned(4)));
+
+// What a triple needs of one of its sides.
+struct FchlSide {
+  float r, inv, f, df, pn;   // length, 1 / r, f_cut, d f_cut / dr, r^-N3
+};
+
 // dL/da, dL/db, dL/dc for one centre i and neighbour pair (j, l) with sides
 // a = r_ij, b = r_il, c = r_jl, where L is the pair's three-body terms
 // contracted with the centre's upstream gradient gp (the 2 n3 entries of the
 // pair's element pair, [radial bin][cos, sin]). The cosines are functions of
 // the sides (law of cosines), so this is the whole positional dependence.
-__device__ __forceinline__ void fchl_triple_grad(float a, float b, float c,
+// inv_pn is (a b c)^-N3.
+__device__ __forceinline__ void fchl_triple_grad(const FchlSide& sa, const FchlSide& sb,
+                                                 const FchlSide& sc, float inv_pn,
                                                  const float* __restrict__ gp,
                                                  const FchlParams& p, float angw, float (&dL)[3]) {
   const float rc = p.rcut;
-  const float ia = fchl_rcp(a), ib = fchl_rcp(b), ic = fchl_rcp(c);
+  const float a = sa.r, b = sb.r, c = sc.r;
+  const float ia = sa.inv, ib = sb.inv, ic = sc.inv;
   const float a2 = a * a, b2 = b * b, c2 = c * c;
   const float ci_ = 0.5f * (a2 + b2 - c2) * ia * ib;
   const float cj_ = 0.5f * (a2 + c2 - b2) * ia * ic;
@@ -616,10 +637,10 @@ __device__ __forceinline__ void fchl_triple_grad(float a, float b, float c,
   const float si = sqrtf(fmaxf(0.0f, 1.0f - ci_ * ci_));
   const float dsi_dc = si > 1e-12f ? -ci_ * fchl_rcp(si) : 0.0f;
   const float C = ci_ * cj_ * cl_;
-  const float invP3 = __builtin_amdgcn_exp2f(-p.N3 * __builtin_amdgcn_logf(a * b * c));
+  const float invP3 = inv_pn;
   const float xi3 = p.c3 * (1.0f + 3.0f * C) * invP3;
-  const float fa = fchl_fcut(a, rc), fb = fchl_fcut(b, rc), fcc = fchl_fcut(c, rc);
-  const float dfa = fchl_dfcut(a, rc), dfb = fchl_dfcut(b, rc), dfcc = fchl_dfcut(c, rc);
+  const float fa = sa.f, fb = sb.f, fcc = sc.f;
+  const float dfa = sa.df, dfb = sb.df, dfcc = sc.df;
   const float Fc = fa * fb * fcc;
   const float dF[3] = {dfa * fb * fcc, fa * dfb * fcc, fa * fb * dfcc};
   const float inv_side[3] = {ia, ib, ic};
@@ -627,16 +648,22 @@ __device__ __forceinline__ void fchl_triple_grad(float a, float b, float c,
   const float wc = A * ci_, ws = A * si;
   const float mid = 0.5f * (a + b);
   const float step = rc / float(p.n3 - 1);
+  // radial bins: rad = exp(-eta3 d^2), d rad / d mid = -2 eta3 d rad
+  const float keta = -p.eta3 * 1.44269504088896341f;
   float Gc = 0.f, Gs = 0.f, Gcp = 0.f, Gsp = 0.f;
+#pragma unroll 4
   for (int k = 0; k < p.n3; ++k) {
+    const FchlPair g = *reinterpret_cast<const FchlPair*>(gp + 2 * k);
     const float d = mid - float(k) * step;
-    const float rad = fchl_exp(-p.eta3 * d * d);
-    const float drad = -2.0f * p.eta3 * d * rad;
-    Gc += gp[2 * k] * rad;
-    Gs += gp[2 * k + 1] * rad;
-    Gcp += gp[2 * k] * drad;
-    Gsp += gp[2 * k + 1] * drad;
+    const float rad = __builtin_amdgcn_exp2f(keta * (d * d));
+    const float drad = d * rad;
+    Gc = __builtin_fmaf(g.x, rad, Gc);
+    Gs = __builtin_fmaf(g.y, rad, Gs);
+    Gcp = __builtin_fmaf(g.x, drad, Gcp);
+    Gsp = __builtin_fmaf(g.y, drad, Gsp);
   }
+  Gcp *= -2.0f * p.eta3;
+  Gsp *= -2.0f * p.eta3;
 #pragma unroll
   for (int v = 0; v < 3; ++v) {
     const float dC = dci[v] * cj_ * cl_ + ci_ * dcj[v] * cl_ + ci_ * cj_ * dcl[v];
@@ -647,6 +674,18 @@ __device__ __forceinline__ void fchl_triple_grad(float a, float b, float c,
     const float dmid = v < 2 ? 0.5f : 0.0f;
     dL[v] = Gc * dwc + Gs * dws + (wc * Gcp + ws * Gsp) * dmid;
   }
+}
+
+// The same from the three lengths alone.
+__device__ __forceinline__ FchlSide fchl_side(float r, const FchlParams& p) {
+  return FchlSide{r, fchl_rcp(r), fchl_fcut(r, p.rcut), fchl_dfcut(r, p.rcut), 0.0f};
+}
+__device__ __forceinline__ void fchl_triple_grad(float a, float b, float c,
+                                                 const float* __restrict__ gp,
+                                                 const FchlParams& p, float angw, float (&dL)[3]) {
+  fchl_triple_grad(fchl_side(a, p), fchl_side(b, p), fchl_side(c, p),
+                   __builtin_amdgcn_exp2f(-p.N3 * __builtin_amdgcn_logf(a * b * c)), gp, p, angw,
+                   dL);
 }
 
 // d/dr of the two-body terms of one neighbour at distance r, contracted with
@@ -895,17 +934,26 @@ __global__ __launch_bounds__(256) void fchl19_backward_small_kernel(
 // thousands of terms. Every pair derivative of a centre is evaluated once for
 // each of the pair's atoms (three times over), the price of needing no
 // workspace and no bound on the molecule's size.
+//
+// Bound by vector issue, about 350 instructions a triple, most of them the
+// radial bins. 16 waves to a workgroup, so that a compute unit with one atom
+// has four on each SIMD; what depends on one neighbour alone (1 / r, f_cut
+// and its derivative, r^-N3) is formed once per neighbour. 124 us for the 245
+// atoms of a cluster with four waves and every factor formed per triple, now 47.
 __device__ void fchl19_backward_atom(int64_t t, int64_t a0, int64_t a1,
                                      const float* __restrict__ R,
                                      const int32_t* __restrict__ element, int32_t E,
                                      const FchlParams& p, int64_t size,
                                      const float* __restrict__ g, float* __restrict__ dR) {
+  constexpr int NT = kFchlThreads, NW = NT / 64;
   __shared__ int32_t nidx[kFchlMaxNb];
-  __shared__ float nx[kFchlMaxNb], ny[kFchlMaxNb], nz[kFchlMaxNb], nr[kFchlMaxNb];
+  __shared__ float nx[kFchlMaxNb], ny[kFchlMaxNb], nz[kFchlMaxNb];
+  __shared__ FchlSide ns[kFchlMaxNb];
   __shared__ int32_t grp[kFchlMaxElements + 1];
-  __shared__ int32_t wcount[4];
-  __shared__ int64_t seg[kFchlMaxElements * (kFchlMaxElements + 1) / 2 + 1];
-  __shared__ double red[3][256];
+  __shared__ int32_t wcount[2][NW];
+  __shared__ int32_t seg[kFchlMaxElements * (kFchlMaxElements + 1) / 2 + 1];
+  __shared__ int32_t pair_xy[kFchlMaxElements * (kFchlMaxElements + 1) / 2];
+  __shared__ double red[3][NW];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const float rc = p.rcut;
   const float angw = 2.0f * expf(-0.5f * p.zeta * p.zeta) * sqrtf(p.eta3 / 3.14159265358979f);
@@ -914,10 +962,10 @@ __device__ void fchl19_backward_atom(int64_t t, int64_t a0, int64_t a1,
   const int et = element[t];
 
   // t's neighbours grouped by element, atom order inside a group
-  int total = 0;
+  int total = 0, turn = 0;
   for (int X = 0; X < E; ++X) {
     if (tid == 0) grp[X] = total;
-    for (int64_t j0 = a0; j0 < a1; j0 += 256) {
+    for (int64_t j0 = a0; j0 < a1; j0 += NT, turn ^= 1) {
       const int64_t j = j0 + tid;
       float dx = 0.f, dy = 0.f, dz = 0.f, r = 0.f;
       bool f = false;
@@ -929,22 +977,22 @@ __device__ void fchl19_backward_atom(int64_t t, int64_t a0, int64_t a1,
         f = r < rc;
       }
       const uint64_t mask = __ballot(f);
-      const int before = __popcll(mask & ((uint64_t(1) << lane) - 1));
-      if (lane == 0) wcount[wv] = __popcll(mask);
-      __syncthreads();
-      int off = total;
-      for (int w = 0; w < wv; ++w) off += wcount[w];
-      const int chunk = wcount[0] + wcount[1] + wcount[2] + wcount[3];
-      if (f && off + before < kFchlMaxNb) {
-        const int sl = off + before;
+      if (lane == 0) wcount[turn][wv] = __popcll(mask);
+      __syncthreads();   // one a pass: the counts alternate between two buffers
+      int off = total, chunk = 0;
+      for (int w = 0; w < NW; ++w) {
+        off += w < wv ? wcount[turn][w] : 0;
+        chunk += wcount[turn][w];
+      }
+      const int sl = off + __popcll(mask & ((uint64_t(1) << lane) - 1));
+      if (f && sl < kFchlMaxNb) {
         nidx[sl] = int32_t(j - a0);
         nx[sl] = dx;
         ny[sl] = dy;
         nz[sl] = dz;
-        nr[sl] = r;
+        ns[sl] = FchlSide{r, fchl_rcp(r), fchl_fcut(r, rc), fchl_dfcut(r, rc), powf(r, -p.N3)};
       }
       total += chunk;
-      __syncthreads();
     }
   }
   const bool bad = total > kFchlMaxNb;   // uniform: every thread counted the same chunks
@@ -952,58 +1000,60 @@ __device__ void fchl19_backward_atom(int64_t t, int64_t a0, int64_t a1,
   if (!bad) {
     if (tid == 0) {
       grp[E] = total;
-      int64_t o = 0;
+      int32_t o = 0;
       for (int X = 0; X < E; ++X)
         for (int Y = X; Y < E; ++Y) {
-          seg[fchl_pair(X, Y, E)] = o;
-          const int64_t cxn = grp[X + 1] - grp[X], cyn = grp[Y + 1] - grp[Y];
+          const int P = fchl_pair(X, Y, E);
+          seg[P] = o;
+          pair_xy[P] = X | (Y << 8);
+          const int32_t cxn = grp[X + 1] - grp[X], cyn = grp[Y + 1] - grp[Y];
           o += X == Y ? cxn * (cxn - 1) / 2 : cxn * cyn;
         }
       seg[NP] = o;
     }
     __syncthreads();
     const float* __restrict__ gt = g + t * size;
+    // a triple whose sides a and b end at t and whose third side is new
+    const auto far_side = [&](float r) {
+      return FchlSide{r, fchl_rcp(r), fchl_fcut(r, rc), fchl_dfcut(r, rc),
+                      __builtin_amdgcn_exp2f(-p.N3 * __builtin_amdgcn_logf(r))};
+    };
     // centre t, two-body
-    for (int sl = tid; sl < total; sl += 256) {
+    for (int sl = tid; sl < total; sl += NT) {
       int X = 0;
       while (sl >= grp[X + 1]) ++X;
-      const float r = nr[sl];
-      const float f = fchl_pair_grad(r, gt + X * p.n2, p) / r;
+      const float f = fchl_pair_grad(ns[sl].r, gt + X * p.n2, p) * ns[sl].inv;
       px -= f * nx[sl];
       py -= f * ny[sl];
       pz -= f * nz[sl];
     }
     // centre t, three-body over its unordered neighbour pairs
-    const int64_t n_pairs = seg[NP];
-    for (int64_t q = tid; q < n_pairs; q += 256) {
-      int P = 0;
+    const int32_t n_pairs = seg[NP];
+    int P = 0;   // non-decreasing over this thread's pairs
+    for (int32_t q = tid; q < n_pairs; q += NT) {
       while (q >= seg[P + 1]) ++P;
-      int X = 0;
-      while (fchl_pair(X, X, E) + (E - X) <= P) ++X;
-      const int Y = X + (P - fchl_pair(X, X, E));
-      const int64_t loc = q - seg[P];
+      const int X = pair_xy[P] & 255, Y = pair_xy[P] >> 8;
+      const int32_t loc = q - seg[P];
       int sa, sb;
       if (X != Y) {
         const int cyn = grp[Y + 1] - grp[Y];
-        sa = grp[X] + int(loc / cyn);
-        sb = grp[Y] + int(loc % cyn);
+        const int u = fchl_div(loc, cyn);
+        sa = grp[X] + u;
+        sb = grp[Y] + loc - u * cyn;
       } else {
         const int cxn = grp[X + 1] - grp[X];
-        const double c2x = 2.0 * cxn - 1.0;
-        int u = int((c2x - sqrt(c2x * c2x - 8.0 * double(loc))) * 0.5);
-        if (u < 0) u = 0;
-        while (u > 0 && int64_t(u) * (2 * cxn - u - 1) / 2 > loc) --u;
-        while (int64_t(u + 1) * (2 * cxn - u - 2) / 2 <= loc) ++u;
+        const int u = fchl_pair_row(loc, cxn);
         sa = grp[X] + u;
-        sb = grp[X] + u + 1 + int(loc - int64_t(u) * (2 * cxn - u - 1) / 2);
+        sb = grp[X] + u + 1 + (loc - u * (2 * cxn - u - 1) / 2);
       }
-      const float a = nr[sa], b = nr[sb];
       const float wx = nx[sb] - nx[sa], wy = ny[sb] - ny[sa], wz = nz[sb] - nz[sa];
       const float c = sqrtf(wx * wx + wy * wy + wz * wz);
       if (!(c < rc)) continue;   // f_cut(r_jl) and its derivative vanish
+      const FchlSide A = ns[sa], B = ns[sb], C = far_side(c);
       float dL[3];
-      fchl_triple_grad(a, b, c, gt + int64_t(E) * p.n2 + int64_t(P) * p.n3 * 2, p, angw, dL);
-      const float fa = dL[0] / a, fb = dL[1] / b;
+      fchl_triple_grad(A, B, C, A.pn * B.pn * C.pn,
+                       gt + int64_t(E) * p.n2 + int64_t(P) * p.n3 * 2, p, angw, dL);
+      const float fa = dL[0] * A.inv, fb = dL[1] * B.inv;
       px -= fa * nx[sa] + fb * nx[sb];
       py -= fa * ny[sa] + fb * ny[sb];
       pz -= fa * nz[sa] + fb * nz[sb];
@@ -1012,67 +1062,76 @@ __device__ void fchl19_backward_atom(int64_t t, int64_t a0, int64_t a1,
     // the pairs {t, l} of c. A pair's terms carry f_cut(r_tl), so only the
     // neighbours l of t contribute, and those are in t's list: the pairs
     // (c, l) of t's list with r_cl < r_cut, flattened over the threads
-    const int et = element[t];
-    for (int cs = tid; cs < total; cs += 256) {
+    for (int cs = tid; cs < total; cs += NT) {
       const float* __restrict__ gc = g + (a0 + nidx[cs]) * size;
-      const float rct = nr[cs];
-      const float f = fchl_pair_grad(rct, gc + et * p.n2, p) / rct;
+      const float f = fchl_pair_grad(ns[cs].r, gc + et * p.n2, p) * ns[cs].inv;
       px -= f * nx[cs];   // (R_t - R_c) = -(R_c - R_t)
       py -= f * ny[cs];
       pz -= f * nz[cs];
     }
-    const int64_t n_cl = int64_t(total) * total;
-    for (int64_t q = tid; q < n_cl; q += 256) {
-      const int cs = int(q / total), ls = int(q - int64_t(cs) * total);
+    const int32_t n_cl = total * total;
+    for (int32_t q = tid; q < n_cl; q += NT) {
+      const int cs = fchl_div(q, total), ls = q - cs * total;
       if (ls == cs) continue;
       const float wx = nx[ls] - nx[cs], wy = ny[ls] - ny[cs], wz = nz[ls] - nz[cs];   // R_l - R_c
       const float rcl = sqrtf(wx * wx + wy * wy + wz * wz);
       if (!(rcl < rc)) continue;
       int Y = 0;
       while (ls >= grp[Y + 1]) ++Y;
-      const int P = et <= Y ? fchl_pair(et, Y, E) : fchl_pair(Y, et, E);
+      const int Pc = et <= Y ? fchl_pair(et, Y, E) : fchl_pair(Y, et, E);
       const float* __restrict__ gc = g + (a0 + nidx[cs]) * size;
-      const float rct = nr[cs], rtl = nr[ls];
+      const FchlSide A = ns[cs], B = far_side(rcl), C = ns[ls];
       float dL[3];
-      fchl_triple_grad(rct, rcl, rtl, gc + int64_t(E) * p.n2 + int64_t(P) * p.n3 * 2, p, angw, dL);
+      fchl_triple_grad(A, B, C, A.pn * C.pn * B.pn,
+                       gc + int64_t(E) * p.n2 + int64_t(Pc) * p.n3 * 2, p, angw, dL);
       // dL/da (R_t - R_c) / a + dL/dc (R_t - R_l) / c, with R_x - R_t = n[x]
-      const float fa = dL[0] / rct, fc = dL[2] / rtl;
+      const float fa = dL[0] * A.inv, fc = dL[2] * C.inv;
       px -= fa * nx[cs] + fc * nx[ls];
       py -= fa * ny[cs] + fc * ny[ls];
       pz -= fa * nz[cs] + fc * nz[ls];
     }
   }
-  red[0][tid] = px;
-  red[1][tid] = py;
-  red[2][tid] = pz;
+  // lanes, then waves, in a fixed order
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    px += __shfl_xor(px, o);
+    py += __shfl_xor(py, o);
+    pz += __shfl_xor(pz, o);
+  }
+  if (lane == 0) {
+    red[0][wv] = px;
+    red[1][wv] = py;
+    red[2][wv] = pz;
+  }
   __syncthreads();
   if (tid < 3) {
     double sum = 0.0;
-    for (int k = 0; k < 256; ++k) sum += red[tid][k];
+    for (int k = 0; k < NW; ++k) sum += red[tid][k];
     dR[3 * t + tid] = bad ? __builtin_nanf("") : float(sum);
   }
   __syncthreads();   // red[], the neighbour list and seg[] are rewritten for the next atom
 }
 
-// Molecules above kFchlSmallAtoms atoms: a resident grid (three workgroups
-// per compute unit) deals their atoms out, atom j of molecule m to workgroup
+// Molecules above kFchlSmallAtoms atoms: a resident grid (one workgroup per
+// compute unit) deals their atoms out, atom j of molecule m to workgroup
 // (m + j) mod G, as the forward kernel deals the atoms of large molecules.
-__global__ __launch_bounds__(256) void fchl19_backward_gather_kernel(
+__global__ __launch_bounds__(kFchlThreads) void fchl19_backward_gather_kernel(
     const float* __restrict__ R, const int32_t* __restrict__ element,
     const int64_t* __restrict__ mol_ptr, int64_t n_mols, int32_t E, FchlParams p, int64_t size,
     const float* __restrict__ g, float* __restrict__ dR) {
-  __shared__ int32_t big[256];
-  __shared__ int32_t wbig[4];
+  constexpr int NT = kFchlThreads, NW = NT / 64;
+  __shared__ int32_t big[NT];
+  __shared__ int32_t wbig[NW];
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int64_t G = gridDim.x, b = blockIdx.x;
-  for (int64_t m0 = 0; m0 < n_mols; m0 += 256) {
+  for (int64_t m0 = 0; m0 < n_mols; m0 += NT) {
     const int64_t m = m0 + tid;
     const bool large = m < n_mols && mol_ptr[m + 1] - mol_ptr[m] > kFchlSmallAtoms;
     const uint64_t mask = __ballot(large);
     if (lane == 0) wbig[wv] = __popcll(mask);
     __syncthreads();
     int off = 0, nbig = 0;
-    for (int w = 0; w < 4; ++w) {
+    for (int w = 0; w < NW; ++w) {
       off += w < wv ? wbig[w] : 0;
       nbig += wbig[w];
     }
@@ -1140,7 +1199,7 @@ hipError_t sorf_launch_fchl19_backward(const float* R, const int32_t* element,
     if (e != hipSuccess) return e;
   }
   // molecules above kFchlSmallAtoms atoms: a resident grid, one workgroup per atom
-  hipLaunchKernelGGL(fchl19_backward_gather_kernel, dim3(768u), dim3(256), 0, st, R, element,
+  hipLaunchKernelGGL(fchl19_backward_gather_kernel, dim3(256u), dim3(kFchlThreads), 0, st, R, element,
                      mol_ptr, n_mols, E, p, size, g, dR);
   return hipGetLastError();
 }
