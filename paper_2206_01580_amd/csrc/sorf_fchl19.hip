@@ -718,7 +718,7 @@ __device__ __forceinline__ float fchl_pair_grad(float r, const float* __restrict
 }
 
 // Molecules of at most kFchlSmallAtoms atoms: one workgroup per molecule,
-// its four waves take four centres at a time. For a centre with n
+// its NW waves take NW centres at a time. For a centre with n
 // neighbours, every unordered pair is evaluated once: lanes take the pairs
 // (in chunks of kFchlBwdPairs) and store dL/da, dL/db, dL/dc in the wave's
 // LDS. Then each neighbour s gets H lanes (H = 4, 2, 1 for at most 16, 32,
@@ -727,26 +727,30 @@ __device__ __forceinline__ float fchl_pair_grad(float r, const float* __restrict
 // j, dL/db where it is l, plus its two-body term) and V_s = -sum dL/dc
 // (x_t - x_s) / r_st; the H parts are combined by fixed shuffles. Neighbour s
 // gets T_s u_s + V_s, the centre -sum_s T_s u_s (u_s the unit vector from the
-// centre to s, summed by fixed shuffles), and the four centres' results are
-// merged into the molecule's gradient in centre order.
+// centre to s, summed by fixed shuffles), and the centres' results are
+// merged into the molecule's gradient in centre order, so the bits do not
+// depend on NW. NW = 4 fills the chip with four molecules to a compute unit;
+// up to kFchlFewMols molecules each has a compute unit to itself, and NW = 16
+// shortens its chain (21 atoms: 66 us with four waves, 35 with 16).
 // STAGED: the centre's upstream gradient row (at most kFchlStage entries) is
 // copied into the wave's LDS first, so that the radial-bin loops read LDS.
 constexpr int kFchlSmallAtoms = 64;
+constexpr int kFchlFewMols = 256;   // molecules that take 16 waves each
 constexpr int kFchlStage = 1024;
 constexpr int kFchlBwdPairs = 256;
 
-template <bool STAGED>
-__global__ __launch_bounds__(256) void fchl19_backward_small_kernel(
+template <bool STAGED, int NW>
+__global__ __launch_bounds__(64 * NW) void fchl19_backward_small_kernel(
     const float* __restrict__ R, const int32_t* __restrict__ element,
     const int64_t* __restrict__ mol_ptr, int64_t m0, int64_t n_mols, int32_t E, FchlParams p,
     int64_t size, const float* __restrict__ g, float* __restrict__ dR) {
   __shared__ float ax[kFchlSmallAtoms], ay[kFchlSmallAtoms], az[kFchlSmallAtoms];
   __shared__ int32_t ael[kFchlSmallAtoms];
   __shared__ float gsum[3][kFchlSmallAtoms];
-  __shared__ float res[4][3][kFchlSmallAtoms];
-  __shared__ int32_t nid[4][kFchlSmallAtoms];
-  __shared__ float dls[4][3][kFchlBwdPairs];
-  __shared__ float gst[4][STAGED ? kFchlStage : 1];
+  __shared__ float res[NW][3][kFchlSmallAtoms];
+  __shared__ int32_t nid[NW][kFchlSmallAtoms];
+  __shared__ float dls[NW][3][kFchlBwdPairs];
+  __shared__ float gst[NW][STAGED ? kFchlStage : 1];
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int64_t m = m0 + blockIdx.x;
@@ -765,7 +769,7 @@ __global__ __launch_bounds__(256) void fchl19_backward_small_kernel(
   __syncthreads();
   const float angw = 2.0f * expf(-0.5f * p.zeta * p.zeta) * sqrtf(p.eta3 / 3.14159265358979f);
 
-  for (int c0 = 0; c0 < N; c0 += 4) {
+  for (int c0 = 0; c0 < N; c0 += NW) {
     const int ci = c0 + wv;
     res[wv][0][lane] = res[wv][1][lane] = res[wv][2][lane] = 0.0f;
     if (ci < N) {   // wave-uniform
@@ -896,10 +900,8 @@ __global__ __launch_bounds__(256) void fchl19_backward_small_kernel(
 #pragma unroll
       for (int v = 0; v < 3; ++v) {
         float acc = gsum[v][tid];
-        acc += res[0][v][tid];
-        acc += res[1][v][tid];
-        acc += res[2][v][tid];
-        acc += res[3][v][tid];
+#pragma unroll
+        for (int w = 0; w < NW; ++w) acc += res[w][v][tid];
         gsum[v][tid] = acc;
       }
     }
@@ -1189,12 +1191,19 @@ hipError_t sorf_launch_fchl19_backward(const float* R, const int32_t* element,
   constexpr int64_t kPerLaunch = int64_t(1) << 30;
   for (int64_t m0 = 0; m0 < n_mols; m0 += kPerLaunch) {
     const int64_t cnt = n_mols - m0 < kPerLaunch ? n_mols - m0 : kPerLaunch;
-    if (size <= kFchlStage)
-      hipLaunchKernelGGL(fchl19_backward_small_kernel<true>, dim3(unsigned(cnt)), dim3(256), 0, st,
-                         R, element, mol_ptr, m0, n_mols, E, p, size, g, dR);
+    const auto go = [&](auto kernel, unsigned threads) {
+      hipLaunchKernelGGL(kernel, dim3(unsigned(cnt)), dim3(threads), 0, st, R, element, mol_ptr,
+                         m0, n_mols, E, p, size, g, dR);
+    };
+    const bool few = n_mols <= kFchlFewMols;
+    if (size <= kFchlStage && few)
+      go(fchl19_backward_small_kernel<true, 16>, 1024);
+    else if (size <= kFchlStage)
+      go(fchl19_backward_small_kernel<true, 4>, 256);
+    else if (few)
+      go(fchl19_backward_small_kernel<false, 16>, 1024);
     else
-      hipLaunchKernelGGL(fchl19_backward_small_kernel<false>, dim3(unsigned(cnt)), dim3(256), 0,
-                         st, R, element, mol_ptr, m0, n_mols, E, p, size, g, dR);
+      go(fchl19_backward_small_kernel<false, 4>, 256);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

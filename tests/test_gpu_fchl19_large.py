@@ -33,3 +33,20 @@ def test_large_molecules_match_oracle(case):
     el = rng.integers(0, E, size=sum(sizes)).astype(np.int32)
     ptr = np.r_[0, np.cumsum(sizes)].astype(np.int64)
     print(f"{case}: max row error / row scale {check(R, el, ptr, E, prm):.2e}")
+
+
+@pytest.mark.parametrize("E", [5, 10])   # rows staged in LDS, and above what is staged
+def test_small_molecule_gradients_independent_of_the_wave_count(E):
+    """Up to 256 molecules take 16 waves each, more take four: the same bits."""
+    from test_gpu_fchl19 import F, gpu_grad
+    sizes = ([1, 2, 4, 5, 15, 16, 17, 32, 33, 63, 64] * 24)[:260]
+    rng = np.random.default_rng(E)
+    R = W.host_geometries(sizes, seed=7).astype(np.float32)
+    el = rng.integers(0, E, size=sum(sizes)).astype(np.int32)
+    ptr = np.r_[0, np.cumsum(sizes)].astype(np.int64)
+    g = rng.standard_normal((sum(sizes), F.fchl19_size(E, PRM["n2"], PRM["n3"]))).astype(np.float32)
+    many = gpu_grad(R, el, ptr, E, PRM, g)
+    n = int(ptr[22])
+    few = gpu_grad(R[:n], el[:n], ptr[:23], E, PRM, g[:n])
+    assert np.isfinite(many).all()
+    assert np.array_equal(many[:n], few)
