@@ -65,7 +65,7 @@ __device__ __forceinline__ float fchl_rcp(float x) { return __builtin_amdgcn_rcp
 // element pair (a <= b) -> position in the lexicographic list of pairs
 __device__ __forceinline__ int fchl_pair(int a, int b, int E) { return a * E - a * (a - 1) / 2 + (b - a); }
 
-// loc / c for 0 <= loc < 2^18 and c >= 1: the FP32 quotient is off by one at most.
+// loc / c for 0 <= loc < 2^22 and c >= 1: the FP32 quotient is off by one at most.
 __device__ __forceinline__ int fchl_div(int loc, int c) {
   int u = int(float(loc) * fchl_rcp(float(c)));
   u -= u * c > loc ? 1 : 0;
@@ -370,7 +370,14 @@ __global__ __launch_bounds__(kFchlThreads) void fchl19_forward_kernel(
 // the others idle. Every entry is summed in a fixed order (pairs in the
 // workgroup-per-atom kernel's numbering, parts in group order, chunks in
 // order), so results are deterministic.
-constexpr int kFchlWavePairs = 384;   // covers the 378 pairs of a centre with 28 neighbours
+//
+// Bound by vector issue (2700 instructions an atom of a QM9-sized molecule)
+// and by the waves in flight: 360,000 atoms 1.81 ms, now 1.41. Seven waves a
+// SIMD (registers and LDS held to that; 1.50 with what the compiler chose);
+// what depends on one neighbour alone formed once for all lanes, not in each
+// element's turn; integer divisions by FP32 reciprocals; the molecule
+// searched by the whole wave.
+constexpr int kFchlWavePairs = 192;   // a chunk; more LDS would cost waves in flight
 
 __device__ __forceinline__ void wave_sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -378,22 +385,42 @@ __device__ __forceinline__ void wave_sync_lds() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__global__ __launch_bounds__(256) void fchl19_forward_small_kernel(
+// The molecule of atom i (the last m < n_mols with mol_ptr[m] <= i), searched
+// by a whole wave with 64 probes a round: three dependent loads for 20000
+// molecules, where a binary search's fifteen were a third of the small kernel's time.
+__device__ __forceinline__ int64_t wave_molecule_of(const int64_t* __restrict__ mol_ptr,
+                                                    int64_t n_mols, int64_t i, int lane) {
+  int64_t lo = 0, len = n_mols;   // the answer lies in [lo, lo + len)
+  while (len > 1) {
+    const int64_t step = (len + 63) / 64;
+    const int64_t probe = lo + lane * step;
+    const bool below = lane * step < len && mol_ptr[probe] <= i;
+    const int n = __popcll(__ballot(below));   // at least one: mol_ptr[lo] <= i
+    lo += (n > 0 ? n - 1 : 0) * step;
+    len = step < n_mols - lo ? step : n_mols - lo;
+  }
+  return lo;
+}
+
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7, 7))) void fchl19_forward_small_kernel(
     const float* __restrict__ R, const int32_t* __restrict__ element,
     const int64_t* __restrict__ mol_ptr, int64_t atom0, int64_t n_atoms, int64_t n_mols,
     int32_t E, FchlParams p, int64_t size, float* __restrict__ rho) {
   __shared__ float nx[4][kFchlSmallMol], ny[4][kFchlSmallMol], nz[4][kFchlSmallMol];
-  __shared__ float nr[4][kFchlSmallMol], c2[4][kFchlSmallMol], mu2[4][kFchlSmallMol],
-      inv2s2[4][kFchlSmallMol];
+  __shared__ float nr[4][kFchlSmallMol], ni[4][kFchlSmallMol], nw[4][kFchlSmallMol];
+  __shared__ float c2[4][kFchlSmallMol], mu2[4][kFchlSmallMol], inv2s2[4][kFchlSmallMol];
   __shared__ int32_t grp[4][kFchlMaxElements + 1];
   __shared__ int32_t seg[4][kFchlMaxElements * (kFchlMaxElements + 1) / 2 + 1];
-  __shared__ float pw_c[4][kFchlWavePairs], pw_s[4][kFchlWavePairs], pmid[4][kFchlWavePairs];
+  __shared__ float2 pw[4][kFchlWavePairs];          // w cos, w sin
+  __shared__ float pmid[4][kFchlWavePairs];
   __shared__ float tail[4][64][2];
+  // X | Y << 8 of an element pair, the same for every wave (each stores all of it)
+  __shared__ uint16_t pair_xy[kFchlMaxElements * (kFchlMaxElements + 1) / 2];
 
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t i = atom0 + int64_t(blockIdx.x) * 4 + wv;
   if (i >= n_atoms) return;                   // whole waves leave
-  const int64_t m = molecule_of(mol_ptr, n_mols, i);
+  const int64_t m = wave_molecule_of(mol_ptr, n_mols, i, lane);
   const int64_t a0 = mol_ptr[m];
   const int N = int(mol_ptr[m + 1] - a0);
   if (N > kFchlSmallMol) return;              // fchl19_forward_kernel takes this atom
@@ -413,6 +440,19 @@ __global__ __launch_bounds__(256) void fchl19_forward_small_kernel(
     in = r < rc;
     ej = element[j];
   }
+  // what depends on one neighbour alone: 1 / r, r^-N3 f_cut, and the two-body
+  // factors f_cut r^-N2 / (sigma sqrt(2 pi)), mu, 1 / (2 sigma^2)
+  float inv = 0.f, w3 = 0.f, fc2 = 0.f, fmu = 0.f, fi = 0.f;
+  if (in) {
+    const float fc = fchl_fcut(r, rc);
+    const float q = 1.0f + p.eta2 / (r * r);
+    const float s2 = logf(q);
+    inv = 1.0f / r;
+    w3 = powf(r, -p.N3) * fc;
+    fc2 = fc * powf(r, -p.N2) / (sqrtf(s2) * 2.50662827463100f);
+    fmu = logf(r / sqrtf(q));
+    fi = 0.5f / s2;
+  }
   int n = 0;
   for (int X = 0; X < E; ++X) {
     if (lane == 0) grp[wv][X] = n;
@@ -424,11 +464,11 @@ __global__ __launch_bounds__(256) void fchl19_forward_small_kernel(
       ny[wv][sl] = dy;
       nz[wv][sl] = dz;
       nr[wv][sl] = r;
-      const float q = 1.0f + p.eta2 / (r * r);
-      const float s2 = logf(q);
-      c2[wv][sl] = fchl_fcut(r, rc) * powf(r, -p.N2) / (sqrtf(s2) * 2.50662827463100f);
-      mu2[wv][sl] = logf(r / sqrtf(q));
-      inv2s2[wv][sl] = 0.5f / s2;
+      ni[wv][sl] = inv;
+      nw[wv][sl] = w3;
+      c2[wv][sl] = fc2;
+      mu2[wv][sl] = fmu;
+      inv2s2[wv][sl] = fi;
     }
     n += __popcll(mask);
   }
@@ -437,7 +477,7 @@ __global__ __launch_bounds__(256) void fchl19_forward_small_kernel(
 
   // two-body bins
   for (int t = lane; t < E * p.n2; t += 64) {
-    const int X = t / p.n2, k = t % p.n2;
+    const int X = fchl_div(t, p.n2), k = t - X * p.n2;
     const float Rk = rc * float(k + 1) / float(p.n2);
     const float lnR = logf(Rk);
     float acc = 0.0f;
@@ -451,19 +491,22 @@ __global__ __launch_bounds__(256) void fchl19_forward_small_kernel(
   // three-body: pairs numbered by element pair, then by position (the
   // workgroup-per-atom kernel's numbering)
   const int NP = E * (E + 1) / 2;
-  if (lane == 0) {
-    int32_t o = 0;
-    for (int X = 0; X < E; ++X)
-      for (int Y = X; Y < E; ++Y) {
-        seg[wv][fchl_pair(X, Y, E)] = o;
-        const int32_t cx = grp[wv][X + 1] - grp[wv][X], cy = grp[wv][Y + 1] - grp[wv][Y];
-        o += X == Y ? cx * (cx - 1) / 2 : cx * cy;
-      }
-    seg[wv][NP] = o;
+  for (int P = lane; P < NP; P += 64) {
+    int X = 0;
+    while (fchl_pair(X, X, E) + (E - X) <= P) ++X;
+    const int Y = X + (P - fchl_pair(X, X, E));
+    // pairs whose first neighbour comes before X's, then those of X before Y's
+    const int gX = grp[wv][X], cx = grp[wv][X + 1] - gX;
+    int32_t o = gX * (2 * n - gX - 1) / 2;
+    if (Y > X) o += cx * (cx - 1) / 2 + cx * (grp[wv][Y] - grp[wv][X + 1]);
+    seg[wv][P] = o;
+    pair_xy[P] = uint16_t(X | (Y << 8));
   }
+  if (lane == 0) seg[wv][NP] = n * (n - 1) / 2;
   wave_sync_lds();
   const int32_t n_pairs = seg[wv][NP];
   const float angw = 2.0f * expf(-0.5f * p.zeta * p.zeta) * sqrtf(p.eta3 / 3.14159265358979f);
+  const float c3w = p.c3 * angw, keta = -p.eta3 * 1.44269504088896341f;
   // Bins: G groups of n3 lanes, one lane per radial bin; group g walks the
   // g-th of G equal parts of the chunk's pairs in order. An element pair
   // whose pairs fall in several parts is finished by the group where it ends,
@@ -473,54 +516,49 @@ __global__ __launch_bounds__(256) void fchl19_forward_small_kernel(
   const int g = p.n3 <= 64 ? lane / p.n3 : 0;
   const int kl = p.n3 <= 64 ? lane % p.n3 : lane;
   float* __restrict__ out3 = out + int64_t(E) * p.n2;
-  int P = 0, X = 0;   // decode state: non-decreasing in q, kept across iterations
+  int P = 0;   // decode state: non-decreasing in q, kept across iterations
   for (int32_t q0 = 0; q0 < n_pairs || q0 == 0; q0 += kFchlWavePairs) {
     const int32_t q1 = q0 + kFchlWavePairs < n_pairs ? q0 + kFchlWavePairs : n_pairs;
     for (int32_t q = q0 + lane; q < q1; q += 64) {
       while (q >= seg[wv][P + 1]) ++P;
-      while (fchl_pair(X, X, E) + (E - X) <= P) ++X;
-      const int Y = X + (P - fchl_pair(X, X, E));
+      const int X = pair_xy[P] & 255, Y = pair_xy[P] >> 8;
       const int32_t loc = q - seg[wv][P];
       int a, b;
       if (X != Y) {
         const int cy = grp[wv][Y + 1] - grp[wv][Y];
-        a = grp[wv][X] + loc / cy;
-        b = grp[wv][Y] + loc % cy;
+        const int u = fchl_div(loc, cy);
+        a = grp[wv][X] + u;
+        b = grp[wv][Y] + loc - u * cy;
       } else {
         const int cx = grp[wv][X + 1] - grp[wv][X];
-        const float c2x = 2.0f * float(cx) - 1.0f;
-        int u = int((c2x - sqrtf(c2x * c2x - 8.0f * float(loc))) * 0.5f);
-        if (u < 0) u = 0;
-        while (u > 0 && u * (2 * cx - u - 1) / 2 > loc) --u;
-        while ((u + 1) * (2 * cx - u - 2) / 2 <= loc) ++u;
+        const int u = fchl_pair_row(loc, cx);
         a = grp[wv][X] + u;
         b = grp[wv][X] + u + 1 + (loc - u * (2 * cx - u - 1) / 2);
       }
       const float rij = nr[wv][a], rik = nr[wv][b];
       const float jx = nx[wv][b] - nx[wv][a], jy = ny[wv][b] - ny[wv][a], jz = nz[wv][b] - nz[wv][a];
       const float rjk = sqrtf(jx * jx + jy * jy + jz * jz);
-      const float iij = fchl_rcp(rij), iik = fchl_rcp(rik), ijk = fchl_rcp(rjk);
+      const float iij = ni[wv][a], iik = ni[wv][b], ijk = fchl_rcp(rjk);
       const float cos_i = (nx[wv][a] * nx[wv][b] + ny[wv][a] * ny[wv][b] + nz[wv][a] * nz[wv][b]) * (iij * iik);
       const float cos_j = -(nx[wv][a] * jx + ny[wv][a] * jy + nz[wv][a] * jz) * (iij * ijk);
       const float cos_k = (nx[wv][b] * jx + ny[wv][b] * jy + nz[wv][b] * jz) * (iik * ijk);
       const float sin_i = sqrtf(fmaxf(0.0f, 1.0f - cos_i * cos_i));
-      const float xi3 = p.c3 * (1.0f + 3.0f * cos_i * cos_j * cos_k) *
-                        __builtin_amdgcn_exp2f(-p.N3 * __builtin_amdgcn_logf(rij * rjk * rik));
-      const float w = xi3 * fchl_fcut(rij, rc) * fchl_fcut(rjk, rc) * fchl_fcut(rik, rc) * angw;
+      const float w = c3w * (1.0f + 3.0f * cos_i * cos_j * cos_k) * (nw[wv][a] * nw[wv][b]) *
+                      (__builtin_amdgcn_exp2f(-p.N3 * __builtin_amdgcn_logf(rjk)) *
+                       fchl_fcut(rjk, rc));
       const int sl = q - q0;
-      pw_c[wv][sl] = w * cos_i;
-      pw_s[wv][sl] = w * sin_i;
+      pw[wv][sl] = make_float2(w * cos_i, w * sin_i);
       pmid[wv][sl] = 0.5f * (rij + rik);
     }
     // element pairs without pairs in the first chunk: their bins start at 0
     if (q0 == 0)
-      for (int Q = 0; Q < NP; ++Q) {
+      for (int t = lane; t < NP * p.n3; t += 64) {
+        const int Q = fchl_div(t, p.n3);
         const int32_t s0 = seg[wv][Q], s1 = seg[wv][Q + 1] < q1 ? seg[wv][Q + 1] : q1;
-        if (s1 <= s0)
-          for (int k = lane; k < p.n3; k += 64) {
-            out3[2 * (int64_t(Q) * p.n3 + k)] = 0.0f;
-            out3[2 * (int64_t(Q) * p.n3 + k) + 1] = 0.0f;
-          }
+        if (s1 <= s0) {
+          out3[2 * t] = 0.0f;
+          out3[2 * t + 1] = 0.0f;
+        }
       }
     wave_sync_lds();
     const int32_t L = q1 - q0;
@@ -528,18 +566,19 @@ __global__ __launch_bounds__(256) void fchl19_forward_small_kernel(
     float pc = 0.f, ps = 0.f;
     for (int k = kl; k < p.n3 && g < G; k += 64) {
       const float Rk = rc * float(k) / float(p.n3 - 1);
-      const int32_t lo = q0 + int32_t(int64_t(L) * g / G), hi = q0 + int32_t(int64_t(L) * (g + 1) / G);
+      const int32_t lo = q0 + fchl_div(L * g, G), hi = q0 + fchl_div(L * (g + 1), G);
       int Q = 0;
       while (Q < NP && seg[wv][Q + 1] <= lo) ++Q;
       bool started = Q < NP && (seg[wv][Q] > q0 ? seg[wv][Q] : q0) >= lo;
-      int32_t segend = Q < NP && seg[wv][Q + 1] < q1 ? seg[wv][Q + 1] : q1;
       float c = 0.f, sn = 0.f;
+      int32_t segend = Q < NP && seg[wv][Q + 1] < q1 ? seg[wv][Q + 1] : q1;
+      // one pair a step for every group, whatever their element pairs' ends
       for (int32_t q = lo; q < hi; ++q) {
-        const int sl = q - q0;
-        const float d = pmid[wv][sl] - Rk;
-        const float gk = fchl_exp(-p.eta3 * d * d);
-        c += pw_c[wv][sl] * gk;
-        sn += pw_s[wv][sl] * gk;
+        const float2 w = pw[wv][q - q0];
+        const float d = pmid[wv][q - q0] - Rk;
+        const float gk = __builtin_amdgcn_exp2f(keta * (d * d));
+        c = __builtin_fmaf(w.x, gk, c);
+        sn = __builtin_fmaf(w.y, gk, sn);
         if (q + 1 == segend) {          // element pair Q ends in this part
           if (started) {
             float* o = out3 + 2 * (int64_t(Q) * p.n3 + k);
@@ -558,7 +597,7 @@ __global__ __launch_bounds__(256) void fchl19_forward_small_kernel(
           c = 0.f;
           sn = 0.f;
           ++Q;
-          while (Q < NP && seg[wv][Q + 1] <= q + 1) ++Q;
+          while (Q < NP && seg[wv][Q + 1] <= segend) ++Q;
           started = true;
           segend = Q < NP && seg[wv][Q + 1] < q1 ? seg[wv][Q + 1] : q1;
         }
@@ -569,8 +608,8 @@ __global__ __launch_bounds__(256) void fchl19_forward_small_kernel(
     wave_sync_lds();
     if (pend >= 0) {
       const int32_t st = seg[wv][pend] > q0 ? seg[wv][pend] : q0;
-      int gs = 0;
-      while (q0 + int32_t(int64_t(L) * (gs + 1) / G) <= st) ++gs;
+      int gs = g - 1;                   // the group in whose part the element pair starts
+      while (gs > 0 && q0 + fchl_div(L * gs, G) > st) --gs;
       float sc = 0.f, ss = 0.f;
       for (int gg = gs; gg < g; ++gg) {
         sc += tail[wv][gg * p.n3 + kl][0];
