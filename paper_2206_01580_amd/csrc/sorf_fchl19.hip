@@ -715,16 +715,9 @@ __device__ __forceinline__ void fchl_triple_grad(const FchlSide& sa, const FchlS
   }
 }
 
-// The same from the three lengths alone.
+// A side from its length alone (r^-N3 left out).
 __device__ __forceinline__ FchlSide fchl_side(float r, const FchlParams& p) {
   return FchlSide{r, fchl_rcp(r), fchl_fcut(r, p.rcut), fchl_dfcut(r, p.rcut), 0.0f};
-}
-__device__ __forceinline__ void fchl_triple_grad(float a, float b, float c,
-                                                 const float* __restrict__ gp,
-                                                 const FchlParams& p, float angw, float (&dL)[3]) {
-  fchl_triple_grad(fchl_side(a, p), fchl_side(b, p), fchl_side(c, p),
-                   __builtin_amdgcn_exp2f(-p.N3 * __builtin_amdgcn_logf(a * b * c)), gp, p, angw,
-                   dL);
 }
 
 // d/dr of the two-body terms of one neighbour at distance r, contracted with
@@ -760,7 +753,7 @@ __device__ __forceinline__ float fchl_pair_grad(float r, const float* __restrict
 // its NW waves take NW centres at a time. For a centre with n
 // neighbours, every unordered pair is evaluated once: lanes take the pairs
 // (in chunks of kFchlBwdPairs) and store dL/da, dL/db, dL/dc in the wave's
-// LDS. Then each neighbour s gets H lanes (H = 4, 2, 1 for at most 16, 32,
+// LDS (dL/dc over r_st). Then each neighbour s gets H lanes (H = 4, 2, 1 for at most 16, 32,
 // 63 neighbours); lane h walks the partners t = h, h + H, ... in order (and
 // the two-body bins h, h + H, ...) and sums T_s (dL/da where s is the pair's
 // j, dL/db where it is l, plus its two-body term) and V_s = -sum dL/dc
@@ -790,6 +783,7 @@ __global__ __launch_bounds__(64 * NW) void fchl19_backward_small_kernel(
   __shared__ int32_t nid[NW][kFchlSmallAtoms];
   __shared__ float dls[NW][3][kFchlBwdPairs];
   __shared__ float gst[NW][STAGED ? kFchlStage : 1];
+  __shared__ float4 side[NW][kFchlSmallAtoms];   // r, 1 / r, f_cut, its derivative
 
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   const int64_t m = m0 + blockIdx.x;
@@ -833,6 +827,13 @@ __global__ __launch_bounds__(64 * NW) void fchl19_backward_small_kernel(
         n += __popcll(mask);
       }
       wave_sync_lds();
+      if (lane < n) {   // lane = slot here: what the pairs need of one neighbour alone
+        const int j = nid[wv][lane];
+        const float vx = ax[j] - xi, vy = ay[j] - yi, vz = az[j] - zi;
+        const float r = sqrtf(vx * vx + vy * vy + vz * vz);
+        side[wv][lane] = make_float4(r, fchl_rcp(r), fchl_fcut(r, rc), fchl_dfcut(r, rc));
+      }
+      wave_sync_lds();
       // H lanes per neighbour slot when the neighbours are few: lane (sl, h)
       // takes the two-body bins and the partners h, h + H, ... of slot sl
       const int H = n <= 16 ? 4 : (n <= 32 ? 2 : 1);
@@ -866,18 +867,21 @@ __global__ __launch_bounds__(64 * NW) void fchl19_backward_small_kernel(
           const int ja = nid[wv][s], jb = nid[wv][tt];
           const float vax = ax[ja] - xi, vay = ay[ja] - yi, vaz = az[ja] - zi;
           const float vbx = ax[jb] - xi, vby = ay[jb] - yi, vbz = az[jb] - zi;
-          const float a = sqrtf(vax * vax + vay * vay + vaz * vaz);
-          const float b = sqrtf(vbx * vbx + vby * vby + vbz * vbz);
+          const float4 fa = side[wv][s], fb = side[wv][tt];
           const float wx = vbx - vax, wy = vby - vay, wz = vbz - vaz;
           const float c = sqrtf(wx * wx + wy * wy + wz * wz);
           const int Xa = ael[ja], Xb = ael[jb];
           const int P = fchl_pair(Xa < Xb ? Xa : Xb, Xa < Xb ? Xb : Xa, E);
+          const FchlSide A{fa.x, fa.y, fa.z, fa.w, 0.0f}, B{fb.x, fb.y, fb.z, fb.w, 0.0f};
+          const FchlSide C = fchl_side(c, p);
           float dL[3];
-          fchl_triple_grad(a, b, c, gi + int64_t(E) * p.n2 + int64_t(P) * p.n3 * 2, p, angw, dL);
+          fchl_triple_grad(A, B, C,
+                           __builtin_amdgcn_exp2f(-p.N3 * __builtin_amdgcn_logf(fa.x * fb.x * c)),
+                           gi + int64_t(E) * p.n2 + int64_t(P) * p.n3 * 2, p, angw, dL);
           const int sl = q - q0;
           dls[wv][0][sl] = dL[0];
           dls[wv][1][sl] = dL[1];
-          dls[wv][2][sl] = dL[2];
+          dls[wv][2][sl] = dL[2] * C.inv;
         }
         wave_sync_lds();
         if (sl < n) {
@@ -890,9 +894,8 @@ __global__ __launch_bounds__(64 * NW) void fchl19_backward_small_kernel(
             const int sl = q - q0;
             T += s < u ? dls[wv][0][sl] : dls[wv][1][sl];
             const int ju = nid[wv][u];
-            const float wx = (ax[ju] - xi) - (xs - xi), wy = (ay[ju] - yi) - (ys - yi),
-                        wz = (az[ju] - zi) - (zs - zi);
-            const float f = dls[wv][2][sl] / sqrtf(wx * wx + wy * wy + wz * wz);
+            const float wx = ax[ju] - xs, wy = ay[ju] - ys, wz = az[ju] - zs;
+            const float f = dls[wv][2][sl];
             Vx -= f * wx;
             Vy -= f * wy;
             Vz -= f * wz;
