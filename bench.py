@@ -34,8 +34,20 @@ PEAK_HBM_GBS = 8000.0
 PEAK_MFMA_TFLOPS = {"fp32": 157.3, "bf16": 2500.0, "fp16": 2500.0, "bf16_hilo": 2500.0,
                     "fp16_hilo": 2500.0, "fp64": 78.6, "fp32_kahan": 157.3, "split": 2500.0}
 # matrix-core work per algorithmic product, in units of one 16-bit product: hi+lo runs
-# four fp16/bf16 products; split runs one int8 product (double rate) and three fp16
+# four fp16/bf16 products; split runs one int8 product (double rate) and three fp16; FP32
+# runs six bf16 products of an exact three-part split at the sizes that take it
 MFMA_WORK = {"bf16_hilo": 4.0, "fp16_hilo": 4.0, "split": 3.5}
+FP32_PARTS_WORK = 6.0
+
+
+def gram_peak(mode, M, D):
+    """(ceiling of one algorithmic Gram product, matrix-core work per product, peak of
+    the instructions that run) in TFLOP/s. FP32 at M >= 512, D >= 1024, D % 4 == 0 runs
+    on the bf16 matrix cores, elsewhere on the FP32 ones."""
+    if mode == "fp32" and M >= 512 and D >= 1024 and D % 4 == 0:
+        peak = PEAK_MFMA_TFLOPS["bf16"]
+        return peak / FP32_PARTS_WORK, FP32_PARTS_WORK, peak
+    return PEAK_MFMA_TFLOPS[mode], MFMA_WORK.get(mode, 1.0), PEAK_MFMA_TFLOPS[mode]
 # VALU issue ceiling derived from unit counts: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
 # = 39.3 T lane-instructions/s (packed FP32, which would double it, is disabled by the library's compile flags)
 PEAK_VALU_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
@@ -311,7 +323,7 @@ def force_training_leg(args, dev, log):
                         "slots_per_unit": dz_slots_per_unit(p.d, p.n_transforms),
                         "units_per_launch": units},
         "gram_tflops": gram_tf,
-        "gram_frac": gram_tf / PEAK_MFMA_TFLOPS[args.gram],
+        "gram_frac": gram_tf / gram_peak(args.gram, 3 * A, D)[0],
         "inference": {
             "phase_ms": imed,
             "conformations_per_s": M / (imed["predict_energy_force"] * 1e-3),
@@ -953,12 +965,12 @@ def main():
     bwd_slots = valu_slots_per_feature(p.d, p.n_transforms, backward=True) * af
     bwd_tops = bwd_slots / (med["energy_grad"] * 1e-3) / 1e12
     chol_flop = D ** 3 / 3.0
-    mfma_work = MFMA_WORK.get(args.gram, 1.0)
+    g_peak, mfma_work, g_unit_peak = gram_peak(args.gram, M, D)
     rooflines = {
-        "gram": {"bound": "mfma", "achieved": gram_tf, "peak": PEAK_MFMA_TFLOPS[args.gram],
-                 "unit": "TFLOP/s", "frac": gram_tf / PEAK_MFMA_TFLOPS[args.gram], "traffic": None,
+        "gram": {"bound": "mfma", "achieved": gram_tf, "peak": g_peak,
+                 "unit": "TFLOP/s", "frac": gram_tf / g_peak, "traffic": None,
                  "ms": med["gram"], "mode": args.gram, "mfma_executed_tflops": gram_tf * mfma_work,
-                 "mfma_utilisation": gram_tf * mfma_work / PEAK_MFMA_TFLOPS[args.gram]},
+                 "mfma_utilisation": gram_tf * mfma_work / g_unit_peak},
         "forward": {"bound": "alu", "achieved": fwd_tops, "peak": PEAK_VALU_TOPS,
                     "unit": "T VALU-slots/s", "frac": fwd_tops / PEAK_VALU_TOPS, "traffic": None,
                     "ms": med["forward"]},
@@ -1033,10 +1045,10 @@ def main():
                 ts.append(e0.elapsed_time(e1))
         ms = float(np.median(ts))
         tf = gram_flop / (ms * 1e-3) / 1e12
-        work = MFMA_WORK.get(mode, 1.0)
-        extra[mode] = {"ms": ms, "algorithmic_tflops": tf, "peak": PEAK_MFMA_TFLOPS[mode],
-                       "frac": tf / PEAK_MFMA_TFLOPS[mode], "mfma_executed_tflops": tf * work,
-                       "mfma_utilisation": tf * work / PEAK_MFMA_TFLOPS[mode]}
+        m_peak, work, m_unit_peak = gram_peak(mode, M, D)
+        extra[mode] = {"ms": ms, "algorithmic_tflops": tf, "peak": m_peak,
+                       "frac": tf / m_peak, "mfma_executed_tflops": tf * work,
+                       "mfma_utilisation": tf * work / m_unit_peak}
         del Gm, rm
         log(f"gram {mode}: {ms:.2f} ms")
     out["gram_modes"] = extra
