@@ -50,3 +50,26 @@ def test_small_molecule_gradients_independent_of_the_wave_count(E):
     few = gpu_grad(R[:n], el[:n], ptr[:23], E, PRM, g[:n])
     assert np.isfinite(many).all()
     assert np.array_equal(many[:n], few)
+
+
+@pytest.mark.parametrize("n", [1024, 1025, 1100])
+def test_gather_beyond_one_pass_of_the_workgroup(n):
+    """Molecules around 1024 atoms, one piece of 64 atoms a wave and two: sampled
+    rows against a small molecule that holds the same neighbourhoods (a
+    stretched chain: atom i sees atoms i - 3 .. i + 3). The chain's triples are
+    nearly collinear, where a gradient in FP32 has no 1e-5 to hold; the
+    gradient's gather is the same code, and the 1260-atom test holds it."""
+    from test_gpu_fchl19 import F, gpu_rho
+    rng = np.random.default_rng(n)
+    step = PRM["rcut"] / 3.4
+    R = np.zeros((n, 3))
+    R[:, 0] = np.arange(n) * step
+    R += rng.uniform(-0.1, 0.1, size=R.shape)
+    R = R.astype(np.float32)
+    el = rng.integers(0, 3, size=n).astype(np.int32)
+    rho = gpu_rho(R, el, np.array([0, n]), 3, PRM)
+    for i in (0, 5, 63, 64, 127, 128, n // 2, 1000, n - 1):
+        a, b = max(0, i - 8), min(n, i + 9)
+        ref, _ = F.fchl19(R[a:b].astype(np.float64), el[a:b], np.array([0, b - a]), 3, PRM)
+        ref = ref.numpy()[i - a]
+        assert np.abs(rho[i] - ref).max() <= 2e-5 * np.abs(ref).max(), i
