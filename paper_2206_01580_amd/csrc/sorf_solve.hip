@@ -17,6 +17,7 @@
 // Triangular solves use the inverted diagonal blocks: one launch per sweep,
 // one workgroup per block row, each waiting for the solved values it needs.
 #include <cmath>
+#include <type_traits>
 
 #include "sorf_internal.h"
 
@@ -623,7 +624,8 @@ __global__ __launch_bounds__(512) void syrk_next_kernel(double* __restrict__ A, 
 // are copied (1 KB a row); 64 consecutive bytes a lane through registers
 // touched 64 cache lines a load. Runs of units leave no round of tiles nearly
 // empty. Sum over a solve of D = 8192: 5.6 ms with tiles through registers,
-// 4.6 with tiles through LDS copies, now 4.4.
+// 4.6 with tiles through LDS copies, now 3.9 (4.3 when every unit also waited
+// for the copies in flight).
 //
 // In an LDS row, pair p of columns sits at p ^ (row % 16): the 16 rows that a
 // group of lanes reads fall on distinct banks, without padding, which a
@@ -689,6 +691,9 @@ __global__ __launch_bounds__(512) void syrk_far_kernel(double* __restrict__ A, i
     const int sw = (4 * wv + i) & 15;
     oS[i] = EVEN ? uint32_t(lane ^ sw) * 16u : uint32_t((lane >> 2) ^ sw) * 16u + (lane & 3) * 4u;
   }
+  // every unit starts one copy and one read of entries, past the last unit
+  // those of the last one again: the waits below count on it
+  int left = n - 1;   // units after `copied`
   const auto copy = [&](int slot) {
     const int64_t col0 = s0 + kFarCols * copied.q + 4 * wv;
 #pragma unroll
@@ -702,7 +707,8 @@ __global__ __launch_bounds__(512) void syrk_far_kernel(double* __restrict__ A, i
         for (int p = 0; p < 4; ++p) dma4(&at(src, oS[i] + 256u * p), dst + 256 * p);
       }
     }
-    copied.next();
+    if (left > 0) copied.next();
+    --left;
   };
   // copies and reads of entries (not the stores) issued after a unit's copies
   // until its barrier, with kAhead == 3
@@ -738,21 +744,27 @@ __global__ __launch_bounds__(512) void syrk_far_kernel(double* __restrict__ A, i
     }
   };
 
-  for (int s = 0; s < kAhead && s < n; ++s) copy(s);
+#pragma unroll
+  for (int s = 0; s < kAhead; ++s) copy(s);
   load_rows();
   load_entries(cur, c0);
   const uint32_t read0 = uint32_t(li * kRow + 16 * (lt ^ li));
-  const auto unit = [&](int s, double (&c)[2][4], double (&cn)[2][4]) {
+  // SLOT = s % kFarRing as a constant. (The operands are read as 8-byte pairs,
+  // which become 16-byte reads: read as double2 the compiler makes each wait for
+  // every copy in flight, whatever its slot.)
+  const auto unit = [&](int s, auto kSlotOf, double (&c)[2][4], double (&cn)[2][4]) {
+    constexpr int SLOT = decltype(kSlotOf)::value;
     // this wave's copies for the unit have landed; behind the barrier every
     // wave's have, and every wave has read the slot that is filled next
-    if (s >= 2 && s + 2 < n)
+    if (s >= 2)
       asm volatile("s_waitcnt vmcnt(%0)" ::"n"(kLater) : "memory");
     else
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (s + kAhead < n) copy((s + kAhead) % kFarRing);
+    copy((SLOT + kAhead) % kFarRing);
+    asm volatile("" ::: "memory");   // kLater counts the reads below as issued after the copies
     if (s + 1 < n) ahead.next();
     load_entries(ahead, cn);   // of the last unit again, at the end
     const int64_t I0 = s0 + ST * cur.r, J0 = s0 + kFarCols * cur.q;
@@ -760,17 +772,21 @@ __global__ __launch_bounds__(512) void syrk_far_kernel(double* __restrict__ A, i
     f64x4 acc[2];
     acc[0] = acc[1] = f64x4{0.0, 0.0, 0.0, 0.0};
     if (below + 15 >= 0) {   // not above the diagonal
-      const char* slot = ring[s % kFarRing];
+      const char* slot = ring[SLOT];
 #pragma unroll
       for (int u = 0; u < 16; ++u) {
         const char* p = slot + (read0 ^ uint32_t(64 * u));
-        const double2 b0 = *reinterpret_cast<const double2*>(p);
-        const double2 b1 = *reinterpret_cast<const double2*>(p + 16 * kRow);
+        const double* q0 = reinterpret_cast<const double*>(p);
+        const double* q1 = reinterpret_cast<const double*>(p + 16 * kRow);
+        const double2 b0 = make_double2(q0[0], q0[1]), b1 = make_double2(q1[0], q1[1]);
         acc[0] = mfma64(ar[u].x, b0.x, acc[0]);
         acc[1] = mfma64(ar[u].x, b1.x, acc[1]);
         acc[0] = mfma64(ar[u].y, b0.y, acc[0]);
         acc[1] = mfma64(ar[u].y, b1.y, acc[1]);
       }
+      // vmcnt(12) with 16-byte copies, (24) without: c's reads are older than this
+      // unit's copies and reads, which the compiler would also wait for
+      __builtin_amdgcn_s_waitcnt(EVEN ? 0x0f7c : 0x4f78);
       double* pC = A + I0 * D;
       const uint32_t o = uint32_t(16 * wv + lt) * uint32_t(D) * 8u + uint32_t(J0 + li) * 8u;
       if (below >= kFarCols - 1 && I0 + ST <= D) {   // strictly below the diagonal, inside the matrix
@@ -792,10 +808,14 @@ __global__ __launch_bounds__(512) void syrk_far_kernel(double* __restrict__ A, i
     cur.next();
     if (cur.r != row && s + 1 < n) load_rows();
   };
-  for (int s = 0; s < n; s += 2) {   // the entries' registers change places, not values
-    unit(s, c0, c1);
-    if (s + 1 < n) unit(s + 1, c1, c0);
+  static_assert(kFarRing == 4, "units in turn");
+  for (int s = 0; s < n; s += 4) {   // the entries' registers change places, not values
+    unit(s, std::integral_constant<int, 0>(), c0, c1);
+    if (s + 1 < n) unit(s + 1, std::integral_constant<int, 1>(), c1, c0);
+    if (s + 2 < n) unit(s + 2, std::integral_constant<int, 2>(), c0, c1);
+    if (s + 3 < n) unit(s + 3, std::integral_constant<int, 3>(), c1, c0);
   }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // no copy outlives the workgroup's LDS
 }
 
 // ---------------------------------------------------------------------------
