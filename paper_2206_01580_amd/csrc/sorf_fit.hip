@@ -41,6 +41,11 @@ constexpr double kFitEps = 2.220446049250313e-16;
 // orthogonal to eps / kFitCluster = 2e-8 by themselves, below the rounding of
 // the FP32 output.
 constexpr double kFitCluster = 1e-8;
+// Squared length below which a column counts as reduced already. G's entries are
+// sums of products of FP32 numbers, so a G that is not zero has a norm of 1e-90
+// or more and 1e-140 is far below its rounding; the squares above it are far
+// from the end of the FP64 range.
+constexpr double kFitNothing = 1e-280;
 
 template <int CTRL>
 __device__ __forceinline__ double dpp_add(double v) {
@@ -84,8 +89,8 @@ __global__ __launch_bounds__(256) void fit_init_kernel(const double* __restrict_
 }
 
 // Column k of the reduction. In: A with the updates of columns < k - 1, the
-// reflector v of column k - 1 (H = I - tau v v^T, entries >= k), tau and
-// p = A v. Every workgroup forms, from row k of A and these vectors,
+// reflector v of column k - 1 (H = I - tau v v^T, entries >= k, the first one 1,
+// so that 1 <= tau <= 2 however small the column was), tau and p = A v. Every workgroup forms, from row k of A and these vectors,
 //   w = tau p - (tau^2 / 2) (v . p) v,   column k of A - v w^T - w v^T,
 // the diagonal entry, the subdiagonal entry and the next reflector; then it
 // updates its own rows i > k and multiplies them by the new reflector. Row k
@@ -138,13 +143,14 @@ __global__ __launch_bounds__(kFitThreads) void fit_column_kernel(
   const double dk = sn[k];
   const double x0 = k + 1 < n ? sn[k + 1] : 0.0;
   double t = 0.0, alpha = x0;
-  if (x2 > 0.0) {
+  if (x2 > kFitNothing) {
     const double norm = sqrt(fma(x0, x0, x2));
     alpha = x0 > 0.0 ? -norm : norm;
-    const double head = x0 - alpha;             // v = (head, x_1, ...), |head| >= norm
-    t = 2.0 / fma(head, head, x2);
+    const double head = x0 - alpha, h2 = head * head;   // |head| >= norm
+    t = 2.0 * h2 / (h2 + x2);
     __syncthreads();                            // x0 has been read by every thread
-    if (tid == 0) sn[k + 1] = head;
+    const double scale = 1.0 / head;
+    for (int j = k + 1 + tid; j < n; j += kFitThreads) sn[j] = j > k + 1 ? sn[j] * scale : 1.0;
   } else if (x2 != x2) {
     t = x2;                                     // not a number: carried into the result
   }
