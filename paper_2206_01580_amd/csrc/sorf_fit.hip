@@ -17,8 +17,8 @@
 //                the rounding of T;
 //   vectors      inverse iteration on T (LU with partial pivoting), one wave
 //                per vector;
-//   clusters     eigenvalues closer than kFitCluster ||T|| share a workgroup
-//                that orthonormalises their vectors in order; their inverse
+//   clusters     vectors of eigenvalues closer than kFitCluster ||T|| are
+//                orthonormalised in order, one workgroup per 16; their inverse
 //                iteration is repeated from the orthonormal vectors;
 //   back         the reflectors are applied to the wanted vectors only.
 //
@@ -269,8 +269,10 @@ __global__ __launch_bounds__(kFitThreads) void fit_bisect_kernel(
 // start[r] = the first index of r's cluster of close eigenvalues.
 __global__ __launch_bounds__(256) void fit_clusters_kernel(const double* __restrict__ lam,
                                                            const double* __restrict__ norm,
-                                                           int n_pca, int32_t* __restrict__ start) {
+                                                           int n_pca, int32_t* __restrict__ start,
+                                                           int32_t* __restrict__ flags) {
   __shared__ int32_t s[256];
+  for (int r = threadIdx.x; r < n_pca; r += 256) flags[r] = 0;   // of the panels below
   const double tol = kFitCluster * norm[0];
   int first = 0;
   for (int r0 = 0; r0 < n_pca; r0 += 256) {
@@ -386,46 +388,153 @@ __global__ __launch_bounds__(64) void fit_vectors_kernel(
   }
 }
 
-// Orthonormalises the rows of Z of every cluster of two or more, in order:
-// each is freed of the earlier ones twice (the second time removes what
-// rounding left of the first) and scaled to length one. One workgroup per
-// cluster.
-__global__ __launch_bounds__(kFitThreads) void fit_orthogonal_kernel(
-    double* __restrict__ Z, int n, int n_pca, const int32_t* __restrict__ start) {
-  __shared__ double y[4096], coef[4096];
-  __shared__ double red[4];
-  const int first = blockIdx.x;
-  if (start[first] != first) return;
-  int last = first;
-  while (last + 1 < n_pca && start[last + 1] == first) ++last;
-  if (last == first) return;
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  for (int j = first; j <= last; ++j) {
-    double* __restrict__ zj = Z + int64_t(j) * n;
-    for (int i = tid; i < n; i += kFitThreads) y[i] = zj[i];
-    __syncthreads();
-    for (int pass = 0; pass < 2; ++pass) {
-      for (int q = first + wv; q < j; q += kFitThreads / 64) {
-        const double* zq = Z + int64_t(q) * n;
+// Orthonormalises the rows of Z of every cluster of two or more, in order. A
+// workgroup owns a panel of 16 rows. It frees them of the earlier panels of
+// their cluster, panel by panel (16 x 16 coefficients and the update on FP64
+// matrix cores), then of each other, and scales them to length one; all that
+// twice (the second time removes what rounding left of the first). A panel is
+// published when it is finished (flags[P] = epoch); a workgroup waits for panels
+// with a lower index only, which are dispatched first, so the waits end. Past
+// kFitWaitTicks of the 100 MHz counter it makes its rows NaN and goes on.
+//
+// Bound by the chain of panels: 16 dependent rows inside each, and the earlier
+// panels again in the second pass. One workgroup for a cluster, row after row,
+// took 748 ms for n = n_pca = 720 and rank 100 (a cluster of 620; Jacobi 112 ms),
+// now 44, and 4.0 ms for 128 of 168 vectors of a decaying spectrum, now 2.2.
+// LDS: the panel in LDS (n <= kFitPanelN), else in place in Z.
+typedef double fit_f64x4 __attribute__((ext_vector_type(4)));
+constexpr int kFitPanel = 16, kFitPanelN = 1024, kFitPanelThreads = 512;
+constexpr uint64_t kFitWaitTicks = uint64_t(1) << 30;   // about 10.7 s
+
+template <bool LDS>
+__global__ __launch_bounds__(kFitPanelThreads) void fit_orthogonal_kernel(
+    double* Z, int n, int n_pca, const int32_t* __restrict__ start, int32_t* flags,
+    int32_t epoch) {
+  constexpr int PW = kFitPanel, NT = kFitPanelThreads, NW = NT / 64;
+  __shared__ double rows[LDS ? PW * (kFitPanelN + 1) : 1];
+  __shared__ double part[NW][PW * PW], coef[PW * PW];
+  __shared__ int32_t first[PW];   // start of each row's cluster
+  __shared__ int32_t s_failed;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int li = lane & 15, lt = lane >> 4;
+  const int p0 = int(blockIdx.x) * PW;
+  const int np = n_pca - p0 < PW ? n_pca - p0 : PW;   // rows of this panel
+  bool cluster = false;
+  if (lane < np) {
+    const int j = p0 + lane;
+    const int32_t s = start[j];
+    if (wv == 0) first[lane] = s;
+    cluster = s != j || (j + 1 < n_pca && start[j + 1] == s);
+  }
+  if (!__any(cluster)) return;   // the same in every wave
+  const int ld = LDS ? (n | 1) : n;
+  double* const P = LDS ? rows : Z + int64_t(p0) * n;
+  if (tid == 0) s_failed = 0;
+  if constexpr (LDS) {
+    for (int j = wv; j < PW; j += NW)
+      for (int i = lane; i < n; i += 64) P[j * ld + i] = j < np ? Z[int64_t(p0 + j) * n + i] : 0.0;
+  }
+  __syncthreads();
+  const int C = first[0];
+  int joined = 0;   // rows of the cluster that the earlier panels belong to
+  while (joined < np && first[joined] == C) ++joined;
+  const int groups = (n + 15) / 16;
+
+  for (int pass = 0; pass < 2; ++pass) {
+    for (int q0 = C / PW * PW; q0 < p0; q0 += PW) {
+      if (pass == 0) {
+        if (tid == 0) {
+          const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+          while (!s_failed && __hip_atomic_load(&flags[q0 / PW], __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT) < epoch) {
+            if (__builtin_amdgcn_s_memrealtime() - t0 > kFitWaitTicks) s_failed = 1;
+            __builtin_amdgcn_s_sleep(2);
+          }
+          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        }
+        __syncthreads();
+      }
+      const double* Q = Z + int64_t(q0) * n;
+      // coefficients Q P^T: slot k = lt of product e stands for column 16 u + 4 lt + e
+      fit_f64x4 acc = {0.0, 0.0, 0.0, 0.0};
+      const double* pj = P + (LDS || li < np ? li : np - 1) * ld;
+      for (int u = wv; u < groups; u += NW) {
+        double a[4], b[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int c = 16 * u + 4 * lt + e, cc = c < n ? c : n - 1;
+          a[e] = Q[int64_t(li) * n + cc];
+          b[e] = pj[cc];
+          if (c >= n) a[e] = b[e] = 0.0;
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(a[e], b[e], acc, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) part[wv][(lt + 4 * r) * PW + li] = acc[r];
+      __syncthreads();
+      if (tid < PW * PW) {
         double s = 0.0;
-        for (int i = lane; i < n; i += 64) s = fma(zq[i], y[i], s);
-        s = wave_sum(s);
-        if (lane == 0) coef[q - first] = s;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) s += part[w][tid];
+        coef[tid] = q0 + tid / PW >= C && tid % PW < joined ? s : 0.0;
       }
       __syncthreads();
-      for (int i = tid; i < n; i += kFitThreads) {
-        double v = y[i];
-        for (int q = first; q < j; ++q) v = fma(-coef[q - first], Z[int64_t(q) * n + i], v);
-        y[i] = v;
+      for (int u = wv; u < groups; u += NW) {
+        const int c = 16 * u + li, cc = c < n ? c : n - 1;
+        fit_f64x4 d = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+          d = __builtin_amdgcn_mfma_f64_16x16x4f64(coef[(4 * s + lt) * PW + li],
+                                                   Q[int64_t(4 * s + lt) * n + cc], d, 0, 0, 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (lt + 4 * r < np && c < n) P[(lt + 4 * r) * ld + c] -= d[r];
       }
       __syncthreads();
     }
-    double n2 = 0.0;
-    for (int i = tid; i < n; i += kFitThreads) n2 = fma(y[i], y[i], n2);
-    const double scale = 1.0 / sqrt(block_sum(n2, red));
-    for (int i = tid; i < n; i += kFitThreads) zj[i] = y[i] * scale;
-    __syncthreads();
+    for (int j = 0; j < np; ++j) {
+      const int lo = first[j] > p0 ? first[j] - p0 : 0;
+      if (first[j] == p0 + j) continue;   // the first of its cluster stays as it is
+      double* pj = P + j * ld;
+      for (int again = 0; again < 2; ++again) {
+        for (int q = lo + wv; q < j; q += NW) {
+          double s = 0.0;
+          for (int i = lane; i < n; i += 64) s = fma(P[q * ld + i], pj[i], s);
+          s = wave_sum(s);
+          if (lane == 0) coef[q] = s;
+        }
+        __syncthreads();
+        for (int i = tid; i < n; i += NT) {
+          double v = pj[i];
+          for (int q = lo; q < j; ++q) v = fma(-coef[q], P[q * ld + i], v);
+          pj[i] = v;
+        }
+        __syncthreads();
+      }
+      double n2 = 0.0;
+      for (int i = tid; i < n; i += NT) n2 = fma(pj[i], pj[i], n2);
+      n2 = wave_sum(n2);
+      if (lane == 0) part[0][wv] = n2;
+      __syncthreads();
+      n2 = 0.0;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) n2 += part[0][w];
+      const double scale = 1.0 / sqrt(n2);
+      for (int i = tid; i < n; i += NT) pj[i] *= scale;
+      __syncthreads();
+    }
   }
+  if (LDS || s_failed)
+    for (int j = wv; j < np; j += NW)
+      for (int i = lane; i < n; i += 64)
+        Z[int64_t(p0 + j) * n + i] = s_failed ? __builtin_nan("") : P[j * ld + i];
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __syncthreads();
+  if (tid == 0)
+    __hip_atomic_store(&flags[blockIdx.x], epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Column r of U = H_0 H_1 ... H_{n-2} applied to row r of Z, its sign fixed by
@@ -533,7 +642,7 @@ static size_t fit_g_bytes(size_t n) {
 size_t sorf_fit_ws_bytes(int32_t d_rep) {
   const size_t n = size_t(d_rep);
   return fit_g_bytes(n) + 3 * fit_align(8 * n * n) + 6 * fit_align(8 * n) + fit_align(8) +
-         fit_align(4 * n);
+         2 * fit_align(4 * n);
 }
 
 hipError_t sorf_launch_projection_fit(int64_t n_samples, int32_t d_rep, const float* sample,
@@ -560,6 +669,7 @@ hipError_t sorf_launch_projection_fit(int64_t n_samples, int32_t d_rep, const fl
   double* lam = reinterpret_cast<double*>(part(vec));
   double* norm = reinterpret_cast<double*>(part(8));
   int32_t* start = reinterpret_cast<int32_t*>(part(4 * size_t(n)));
+  int32_t* flags = reinterpret_cast<int32_t*>(part(4 * size_t(n)));
 
   hipError_t err = sorf_launch_fill(reinterpret_cast<float*>(G), 2 * int64_t(n) * n, 0.0f, st);
   if (err != hipSuccess) return err;
@@ -585,7 +695,7 @@ hipError_t sorf_launch_projection_fit(int64_t n_samples, int32_t d_rep, const fl
   else
     hipLaunchKernelGGL(fit_bisect_kernel<4096>, each, dim3(kFitThreads), 0, st, diag, sub, n,
                        n_pca, lam, norm);
-  hipLaunchKernelGGL(fit_clusters_kernel, dim3(1), dim3(256), 0, st, lam, norm, n_pca, start);
+  hipLaunchKernelGGL(fit_clusters_kernel, dim3(1), dim3(256), 0, st, lam, norm, n_pca, start, flags);
   // once for every vector, twice more for the vectors of clusters
   for (int round = 0; round < 3; ++round) {
     if (n <= kFitLdsN)
@@ -596,7 +706,13 @@ hipError_t sorf_launch_projection_fit(int64_t n_samples, int32_t d_rep, const fl
                          dim3(unsigned(n_pca < kFitScratchGroups ? n_pca : kFitScratchGroups)),
                          dim3(64), 0, st, diag, sub, n, n_pca, lam, norm, start, int(round > 0),
                          G, Z);
-    hipLaunchKernelGGL(fit_orthogonal_kernel, each, dim3(kFitThreads), 0, st, Z, n, n_pca, start);
+    const dim3 panels{unsigned((n_pca + kFitPanel - 1) / kFitPanel)}, threads{kFitPanelThreads};
+    if (n <= kFitPanelN)
+      hipLaunchKernelGGL(fit_orthogonal_kernel<true>, panels, threads, 0, st, Z, n, n_pca, start,
+                         flags, round + 1);
+    else
+      hipLaunchKernelGGL(fit_orthogonal_kernel<false>, panels, threads, 0, st, Z, n, n_pca, start,
+                         flags, round + 1);
   }
   if (n <= 1024)
     hipLaunchKernelGGL(fit_back_kernel<1>, each, dim3(64), 0, st, Z, Vh, tau, lam, n, n_pca, U, sv);
