@@ -203,6 +203,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
 // at a time. Exchanges that keep the step are dearer: ds_swizzle 4600 cycles,
 // v_permlane swaps 4400, transposes through LDS 3480.
 constexpr int kLockWaves = 8;
+// Workgroups of one launch: HIP refuses 2^32 threads or more.
+constexpr int64_t kLockMaxBlocks = int64_t(1) << 22;
 // Direct global -> LDS copies: lane i's 4 or 16 bytes land at lds + 4 i or 16 i
 // (lds is the same in every lane); they are waited for with vmcnt.
 __device__ __forceinline__ void dma4(const void* g, void* lds) {
@@ -292,7 +294,8 @@ void forward_lock_kernel(const float* __restrict__ x, const int32_t* __restrict_
                          const int64_t* __restrict__ mol_ptr, const uint32_t* __restrict__ signs,
                          const float* __restrict__ bias, float* __restrict__ Z,
                          const float* __restrict__ alpha, const int64_t* __restrict__ chunk_ptr,
-                         int64_t n_mols, int32_t S, int32_t T, float c_rev, float out_scale) {
+                         int64_t n_mols, int32_t S, int32_t T, float c_rev, float out_scale,
+                         int64_t block0) {
   using L = LockLayout<LOG_D>;
   constexpr int DV = L::DV, EPL = L::EPL, LOGK = L::LOGK, VPW = L::VPW, W = L::W;
   constexpr int XR = DV / 64;                // 256-byte pieces of a row
@@ -306,7 +309,7 @@ void forward_lock_kernel(const float* __restrict__ x, const int32_t* __restrict_
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
   const int half = wv / HALF;
   const int64_t per = S / VPW;               // items per molecule or chunk, a multiple of HALF
-  const int64_t item0 = int64_t(blockIdx.x) * HALF;   // the workgroup's first item
+  const int64_t item0 = (block0 + blockIdx.x) * HALF;   // the workgroup's first item
   const int64_t c = item0 / per;
   const int32_t s0 = int32_t(item0 - c * per + wv % HALF) * VPW;   // the wave's first stack
   const int32_t s = s0 + int32_t(grp);
@@ -744,15 +747,16 @@ __device__ __forceinline__ void adjoint_atom(const AdjointArgs& g, int64_t a, in
   __syncthreads();   // the shared sums are rewritten for the next atom
 }
 
-// 8 / nw atoms per workgroup. dE: upstream weights of the molecules, or null.
+// 8 / nw atoms per workgroup, from atom0 on. dE: upstream weights of the molecules, or null.
 template <int LOG_D, bool WANT_E>
 __global__ __launch_bounds__(64 * kLockWaves) __attribute__((amdgpu_waves_per_eu(LOG_D < 9 ? 4 : 2)))
 void adjoint_lock_kernel(AdjointArgs g, const int64_t* __restrict__ mol_ptr,
-                         const float* __restrict__ dE, int64_t n_atoms, int64_t n_mols, int nw) {
+                         const float* __restrict__ dE, int64_t atom0, int64_t n_atoms,
+                         int64_t n_mols, int nw) {
   __shared__ AdjointShared<LOG_D> sh;
   const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
   const int per = kLockWaves / nw;
-  int64_t a = wv < per * nw ? int64_t(blockIdx.x) * per + wv / nw : -1;
+  int64_t a = wv < per * nw ? atom0 + int64_t(blockIdx.x) * per + wv / nw : -1;
   if (a >= n_atoms) a = -1;
   float scale = g.g_scale;
   if (!WANT_E && dE != nullptr && a >= 0) scale *= dE[wave_segment(mol_ptr, n_mols, a)];
@@ -1234,18 +1238,21 @@ static hipError_t forward_dispatch(const SorfFeatureArgs& a, float* Z, const flo
   if constexpr (kCanShare) {
     if (share && per % (kLockWaves / 2) == 0) {
       const int64_t rows = alpha == nullptr ? a.n_mols : energy_chunk_bound(a.n_atoms, a.n_mols);
-      const dim3 grid{unsigned(rows * (per / (kLockWaves / 2)))};
-      if (alpha == nullptr)
-        hipLaunchKernelGGL((forward_lock_kernel<LOG_D, false>), grid,
-                           dim3(64 * kLockWaves), 0, st, a.x, a.element, a.mol_ptr, a.signs,
-                           a.bias, Z, alpha, chunk_ptr, a.n_mols, a.n_stacks, a.n_transforms,
-                           c_rev, scale);
-      else
-        hipLaunchKernelGGL((forward_lock_kernel<LOG_D, true>), grid,
-                           dim3(64 * kLockWaves), 0, st, a.x, a.element, a.mol_ptr, a.signs,
-                           a.bias, Z, alpha, chunk_ptr, a.n_mols, a.n_stacks, a.n_transforms,
-                           c_rev, scale);
-      return hipGetLastError();
+      const int64_t blocks = rows * (per / (kLockWaves / 2));
+      for (int64_t b0 = 0; b0 < blocks; b0 += kLockMaxBlocks) {
+        const dim3 grid{unsigned(blocks - b0 < kLockMaxBlocks ? blocks - b0 : kLockMaxBlocks)};
+        if (alpha == nullptr)
+          hipLaunchKernelGGL((forward_lock_kernel<LOG_D, false>), grid, dim3(64 * kLockWaves), 0, st,
+                             a.x, a.element, a.mol_ptr, a.signs, a.bias, Z, alpha, chunk_ptr,
+                             a.n_mols, a.n_stacks, a.n_transforms, c_rev, scale, b0);
+        else
+          hipLaunchKernelGGL((forward_lock_kernel<LOG_D, true>), grid, dim3(64 * kLockWaves), 0, st,
+                             a.x, a.element, a.mol_ptr, a.signs, a.bias, Z, alpha, chunk_ptr,
+                             a.n_mols, a.n_stacks, a.n_transforms, c_rev, scale, b0);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+      }
+      return hipSuccess;
     }
   }
 #define SORF_FWD(DOTV, SH)                                                                     \
@@ -1283,15 +1290,20 @@ static hipError_t adjoint_dispatch(const SorfFeatureArgs& a, const float* alpha,
     const int64_t passes = (int64_t(a.n_stacks) + VPW - 1) / VPW;
     const int nw = passes <= kAdjMaxWaves && a.n_atoms >= kAdjBulkAtoms ? 1 : waves;
     const int64_t per = kLockWaves / nw;
-    const dim3 grid{unsigned((a.n_atoms + per - 1) / per)}, block{64 * kLockWaves};
     const AdjointArgs g{a.x, a.element, a.signs, a.bias, alpha, grad_x, e_atom, a.n_stacks,
                         a.n_transforms, c_rev, g_scale, e_scale};
-    if (e_atom != nullptr)
-      hipLaunchKernelGGL((adjoint_lock_kernel<LOG_D, true>), grid, block, 0, st, g, a.mol_ptr, dE,
-                         a.n_atoms, a.n_mols, nw);
-    else
-      hipLaunchKernelGGL((adjoint_lock_kernel<LOG_D, false>), grid, block, 0, st, g, a.mol_ptr, dE,
-                         a.n_atoms, a.n_mols, nw);
+    for (int64_t a0 = 0; a0 < a.n_atoms; a0 += kLockMaxBlocks * per) {
+      const int64_t blocks = (a.n_atoms - a0 + per - 1) / per;
+      const dim3 grid{unsigned(blocks < kLockMaxBlocks ? blocks : kLockMaxBlocks)};
+      if (e_atom != nullptr)
+        hipLaunchKernelGGL((adjoint_lock_kernel<LOG_D, true>), grid, dim3(64 * kLockWaves), 0, st, g,
+                           a.mol_ptr, dE, a0, a.n_atoms, a.n_mols, nw);
+      else
+        hipLaunchKernelGGL((adjoint_lock_kernel<LOG_D, false>), grid, dim3(64 * kLockWaves), 0, st, g,
+                           a.mol_ptr, dE, a0, a.n_atoms, a.n_mols, nw);
+      const hipError_t e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   } else {
     constexpr int LOG_EPL = default_log_epl<LOG_D>();
     const dim3 grid{unsigned((a.n_atoms + 3) / 4)}, block{256};
