@@ -554,6 +554,36 @@ __device__ __forceinline__ int64_t wave_segment(const int64_t* __restrict__ ptr,
   return lo;
 }
 
+// The gradient row of an atom from its lane sums in LDS (eight blocks of 64 float4,
+// AdjointShared's BLOCK floats apart): the lane groups, first and second half, each in order.
+template <int LOG_D>
+__device__ __forceinline__ void adjoint_row(const float* lane_sums, float* __restrict__ row,
+                                            uint32_t lane, float scale) {
+  using L = LockLayout<LOG_D>;
+  constexpr int VPW = L::VPW, BLOCK = AdjointShared<LOG_D>::BLOCK;
+  for (int u = int(lane); u < L::DV / 4; u += 64) {      // entries 4 u .. 4 u + 3
+    const int i = (4 * u) / (8 * L::K), rem = (4 * u) % (8 * L::K);
+    const float* src = lane_sums + (2 * i + (rem >> 2 & 1)) * BLOCK + 4 * (rem >> 3);
+    float4 h[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      float4 t = *reinterpret_cast<const float4*>(src + 4 * L::K * (k * (VPW / 2)));
+#pragma unroll
+      for (int j = 1; j < VPW / 2; ++j) {
+        const float4 o = *reinterpret_cast<const float4*>(src + 4 * L::K * (k * (VPW / 2) + j));
+        t.x += o.x;
+        t.y += o.y;
+        t.z += o.z;
+        t.w += o.w;
+      }
+      h[k] = t;
+    }
+    *reinterpret_cast<float4*>(row + 4 * u) =
+        make_float4((h[0].x + h[1].x) * scale, (h[0].y + h[1].y) * scale,
+                    (h[0].z + h[1].z) * scale, (h[0].w + h[1].w) * scale);
+  }
+}
+
 // Atom `a` (< 0: none) by waves wv - part .. wv - part + nw - 1 of the workgroup;
 // every wave of the workgroup calls it, with the same nw. scale multiplies the
 // gradient.
@@ -713,27 +743,7 @@ __device__ __forceinline__ void adjoint_atom(const AdjointArgs& g, int64_t a, in
     lds_wave_sync();
   }
   if (part == 0 && live) {
-    for (int u = int(lane); u < DV / 4; u += 64) {       // entries 4 u .. 4 u + 3
-      const int i = (4 * u) / (8 * L::K), rem = (4 * u) % (8 * L::K);
-      const float* src = &sh.part[wv][(2 * i + (rem >> 2 & 1)) * BLOCK + 4 * (rem >> 3)];
-      float4 h[2];
-#pragma unroll
-      for (int k = 0; k < 2; ++k) {
-        float4 t = *reinterpret_cast<const float4*>(src + 4 * L::K * (k * (VPW / 2)));
-#pragma unroll
-        for (int j = 1; j < VPW / 2; ++j) {
-          const float4 o = *reinterpret_cast<const float4*>(src + 4 * L::K * (k * (VPW / 2) + j));
-          t.x += o.x;
-          t.y += o.y;
-          t.z += o.z;
-          t.w += o.w;
-        }
-        h[k] = t;
-      }
-      *reinterpret_cast<float4*>(g.grad_x + a * DV + 4 * u) =
-          make_float4((h[0].x + h[1].x) * scale, (h[0].y + h[1].y) * scale,
-                      (h[0].z + h[1].z) * scale, (h[0].w + h[1].w) * scale);
-    }
+    adjoint_row<LOG_D>(&sh.part[wv][0], g.grad_x + a * DV, lane, scale);
     if constexpr (WANT_E) {
       eacc += lane_xor<0>(eacc);
       eacc += lane_xor<1>(eacc);
@@ -761,6 +771,128 @@ void adjoint_lock_kernel(AdjointArgs g, const int64_t* __restrict__ mol_ptr,
   float scale = g.g_scale;
   if (!WANT_E && dE != nullptr && a >= 0) scale *= dE[wave_segment(mol_ptr, n_mols, a)];
   adjoint_atom<LOG_D, WANT_E>(g, a, wv % nw, nw, scale, sh);
+}
+
+// One wave per atom without the step: the same sums in the same order as
+// adjoint_atom, so the same bits, with phases, rows and signs read from memory
+// when they are needed. For calls whose workgroups in step would leave waves
+// idle or compute units half filled (see adjoint_dispatch). With more than eight
+// passes of stacks the eight chunks are summed one after the other, through LDS.
+template <int LOG_D, bool WANT_E>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void adjoint_wave_kernel(AdjointArgs g,
+                                                           const int64_t* __restrict__ mol_ptr,
+                                                           const float* __restrict__ dE,
+                                                           int64_t atom0, int64_t n_atoms,
+                                                           int64_t n_mols) {
+  // products stay products: the kernel in step has a barrier between them and the sums
+#pragma clang fp contract(off)
+  using L = LockLayout<LOG_D>;
+  constexpr int DV = L::DV, EPL = L::EPL, LOGK = L::LOGK, VPW = L::VPW, W = L::W;
+  constexpr int BLOCK = AdjointShared<LOG_D>::BLOCK, CH = 8;
+  __shared__ __attribute__((aligned(16))) float lane_sums[4][8 * BLOCK];
+  const uint32_t lane = lane_id();
+  const uint32_t q = lane & (L::K - 1u);
+  const uint32_t grp = lane >> LOGK;
+  const int wv = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+  const int64_t a = atom0 + int64_t(blockIdx.x) * 4 + wv;
+  if (a >= n_atoms) return;   // whole waves
+  float scale = g.g_scale;
+  if (!WANT_E && dE != nullptr) scale *= dE[wave_segment(mol_ptr, n_mols, a)];
+  const int32_t S = g.S, T = g.T;
+  const int passes = (S + VPW - 1) / VPW;
+  const bool oddq = (__builtin_popcount(q) & 1) != 0;
+  const uint32_t flip = oddq ? 0xFFFFFFFFu : 0u;
+  const float c_lane = oddq ? -g.c_rev : g.c_rev;
+  const int64_t tstride = int64_t(S) * W;
+  const int32_t e = __builtin_amdgcn_readfirstlane(g.element[a]);
+  const uint32_t* signs_e = g.signs + int64_t(e) * T * S * W;
+  const float* bias_e = g.bias + int64_t(e) * S * DV + 8 * q;
+  const float* row = g.x + a * DV + 8 * q;
+  float* mine = &lane_sums[wv][4 * lane];
+
+  float acc[EPL];
+  float eacc = 0.0f, esum = 0.0f;
+#pragma unroll
+  for (int r = 0; r < EPL; ++r) acc[r] = 0.0f;
+  const int step = passes > kAdjMaxWaves ? kAdjMaxWaves : 1;   // one chunk, or eight
+  for (int chunk = 0; chunk < step; ++chunk) {
+    for (int p = chunk; p < passes; p += step) {
+      const bool partial = (p + 1) * VPW > S;              // the last pass may be
+      const bool inside = p * VPW + int(grp) < S;
+      const int32_t s = inside ? p * VPW + int(grp) : S - 1;
+      const uint32_t* sv = signs_e + int64_t(s) * W;
+      uint32_t raw[3][L::RAW], sg[3];   // transforms past T repeat the last one's signs
+#pragma unroll
+      for (int t = 0; t < 3; ++t) L::load_raw(raw[t], sv + (t < T ? t : T - 1) * tstride, q);
+      float v[EPL];
+#pragma unroll
+      for (int i = 0; i < EPL / CH; ++i) {
+        float x[CH];
+        load_vec<CH>(x, row + 8 * L::K * i);
+#pragma unroll
+        for (int r = 0; r < CH; ++r) v[CH * i + r] = x[r];
+      }
+#pragma unroll
+      for (int t = 0; t < 3; ++t) sg[t] = L::sign_word(raw[t], q);
+#pragma unroll 1
+      for (int t = 0; t < T; ++t) {
+        const uint32_t w[1] = {t == 0 ? sg[0] : (t == 1 ? sg[1] : sg[2]) ^ flip};
+        apply_signs<EPL>(v, w);
+        fwht_ahead<LOGK, EPL>(v, q);
+      }
+      float ep = 0.0f;
+#pragma unroll
+      for (int i = 0; i < EPL / CH; ++i) {
+        float b[CH], al[CH];
+        load_vec<CH>(b, bias_e + int64_t(s) * DV + 8 * L::K * i);
+        load_vec<CH>(al, g.alpha + int64_t(s) * DV + 8 * q + 8 * L::K * i);
+        if (partial) {
+#pragma unroll
+          for (int r = 0; r < CH; ++r) al[r] = inside ? al[r] : 0.0f;
+        }
+#pragma unroll
+        for (int r = 0; r < CH; ++r) {
+          const float wt = al[r];
+          const float u = __builtin_fmaf(v[CH * i + r], c_lane, b[r] * kInv2Pi);
+          if constexpr (WANT_E) ep = __builtin_fmaf(wt, __builtin_amdgcn_cosf(u), ep);
+          v[CH * i + r] = wt * __builtin_amdgcn_sinf(u);
+        }
+      }
+#pragma unroll 1
+      for (int t = T - 1; t >= 0; --t) {
+        fwht_ahead<LOGK, EPL>(v, q);
+        const uint32_t w[1] = {(t == 0 ? sg[0] : t == 1 ? sg[1] : sg[2]) ^ flip};
+        apply_signs<EPL>(v, w);
+      }
+#pragma unroll
+      for (int r = 0; r < EPL; ++r) acc[r] += v[r];
+      eacc += ep;
+    }
+#pragma unroll
+    for (int r = 0; r < EPL; r += 4) {
+      float4* at = reinterpret_cast<float4*>(mine + (r / 4) * BLOCK);
+      float4 t = make_float4(acc[r], acc[r + 1], acc[r + 2], acc[r + 3]);
+      if (chunk > 0) {
+        const float4 o = *at;
+        t = make_float4(o.x + t.x, o.y + t.y, o.z + t.z, o.w + t.w);
+      }
+      *at = t;
+      acc[r] = acc[r + 1] = acc[r + 2] = acc[r + 3] = 0.0f;
+    }
+    esum = chunk > 0 ? esum + eacc : eacc;
+    eacc = 0.0f;
+  }
+  lds_wave_sync();
+  adjoint_row<LOG_D>(&lane_sums[wv][0], g.grad_x + a * DV, lane, scale);
+  if constexpr (WANT_E) {
+    esum += lane_xor<0>(esum);
+    esum += lane_xor<1>(esum);
+    esum += lane_xor<2>(esum);
+    esum += lane_xor<3>(esum);
+    esum += lane_xor<4>(esum);
+    esum += lane_xor<5>(esum);
+    if (lane == 0) g.e_atom[a] = esum * g.e_scale;
+  }
 }
 
 // Below d = 64 a vector lies in one lane, there is no exchange, and the transforms are short:
@@ -1272,11 +1404,23 @@ static hipError_t forward_dispatch(const SorfFeatureArgs& a, float* Z, const flo
 
 // Gradients (and the atoms' energy shares when e_atom is given; then dE is
 // null). latency: below d = 64, several waves per atom.
-// From d = 64 on both work splits of adjoint_lock_kernel give the same bits.
-// One wave per atom saves the sums over waves, several fill the chip evenly:
-// 21,000 atoms with 64 stacks take 383 us with one and 390 with four (the whole
-// prediction), 360,149 atoms 8.87 and 9.29 ms (energies and forces from
-// coordinates), but 8400 atoms 181 and 172, and with 128 stacks 287 and 263.
+//
+// From d = 64 on three forms give the same bits (us, energies and gradients,
+// T = 3): several waves per atom in step (N), one wave per atom in step (1),
+// one wave per atom out of step (adjoint_wave_kernel, W).
+//  - Below d = 512 and up to eight passes, N or 1 by the number of atoms: one wave
+//    saves the sums over waves, several fill the chip evenly. 21,000 atoms with 64
+//    stacks take 383 us with one and 390 with four (the whole prediction), 360,149
+//    atoms 8.87 and 9.29 ms (energies and forces from coordinates), but 8400 atoms
+//    181 and 172, and with 128 stacks 287 and 263.
+//  - More passes: N, or W where its last round leaves too many waves idle. 16,000
+//    atoms, d = 128, 9 passes N 574, W 444; 13 686, 638; 16 697, 777; d = 256, 13
+//    passes 788, 658; 16 807, 804. Up to 2000 atoms W has too few waves in flight
+//    (1000 atoms, 13 passes: N 54, W 65).
+//  - From d = 512 on a workgroup in step fills a compute unit's LDS with two
+//    waves a SIMD, and W has three: N for few atoms only. d = 512, 4 passes: 500
+//    atoms N 18, W 33, 1000 31 and 34, 2000 47 and 42, 40,000 990 (1: 836) and
+//    550; one pass, 21 atoms 16.3 and 16.4, 40,000 245 and 158.
 constexpr int64_t kAdjBulkAtoms = 16384;
 template <int LOG_D>
 static hipError_t adjoint_dispatch(const SorfFeatureArgs& a, const float* alpha, const float* dE,
@@ -1287,20 +1431,35 @@ static hipError_t adjoint_dispatch(const SorfFeatureArgs& a, const float* alpha,
   if constexpr (LOG_D >= 6) {
     (void)latency;
     constexpr int VPW = LockLayout<LOG_D>::VPW;
-    const int64_t passes = (int64_t(a.n_stacks) + VPW - 1) / VPW;
-    const int nw = passes <= kAdjMaxWaves && a.n_atoms >= kAdjBulkAtoms ? 1 : waves;
-    const int64_t per = kLockWaves / nw;
+    const int64_t passes = (int64_t(a.n_stacks) + VPW - 1) / VPW, A = a.n_atoms;
+    const auto blocks = [&](int64_t per) { return (A + per - 1) / per; };
+    const int per_n = kLockWaves / waves;   // atoms per workgroup with N
+    // busy waves of a workgroup with N, on average
+    const double busy = passes <= kAdjMaxWaves
+                            ? double(per_n * waves)
+                            : double(passes) / double((passes + kAdjMaxWaves - 1) / kAdjMaxWaves);
+    const bool out_of_step = LOG_D >= 9 ? passes == 1 || double(A) > 192.0 * busy
+                                        : passes > kAdjMaxWaves && busy < 6.8 && A > 2048;
+    const bool one = passes <= kAdjMaxWaves && A >= kAdjBulkAtoms;
+    const int nw = one ? 1 : waves;
+    const int64_t per = out_of_step ? 4 : kLockWaves / nw;
     const AdjointArgs g{a.x, a.element, a.signs, a.bias, alpha, grad_x, e_atom, a.n_stacks,
                         a.n_transforms, c_rev, g_scale, e_scale};
-    for (int64_t a0 = 0; a0 < a.n_atoms; a0 += kLockMaxBlocks * per) {
-      const int64_t blocks = (a.n_atoms - a0 + per - 1) / per;
-      const dim3 grid{unsigned(blocks < kLockMaxBlocks ? blocks : kLockMaxBlocks)};
-      if (e_atom != nullptr)
+    for (int64_t a0 = 0; a0 < A; a0 += kLockMaxBlocks * per) {
+      const int64_t left = blocks(per) - a0 / per;
+      const dim3 grid{unsigned(left < kLockMaxBlocks ? left : kLockMaxBlocks)};
+      if (out_of_step && e_atom != nullptr)
+        hipLaunchKernelGGL((adjoint_wave_kernel<LOG_D, true>), grid, dim3(256), 0, st, g, a.mol_ptr,
+                           dE, a0, A, a.n_mols);
+      else if (out_of_step)
+        hipLaunchKernelGGL((adjoint_wave_kernel<LOG_D, false>), grid, dim3(256), 0, st, g, a.mol_ptr,
+                           dE, a0, A, a.n_mols);
+      else if (e_atom != nullptr)
         hipLaunchKernelGGL((adjoint_lock_kernel<LOG_D, true>), grid, dim3(64 * kLockWaves), 0, st, g,
-                           a.mol_ptr, dE, a0, a.n_atoms, a.n_mols, nw);
+                           a.mol_ptr, dE, a0, A, a.n_mols, nw);
       else
         hipLaunchKernelGGL((adjoint_lock_kernel<LOG_D, false>), grid, dim3(64 * kLockWaves), 0, st, g,
-                           a.mol_ptr, dE, a0, a.n_atoms, a.n_mols, nw);
+                           a.mol_ptr, dE, a0, A, a.n_mols, nw);
       const hipError_t e = hipGetLastError();
       if (e != hipSuccess) return e;
     }

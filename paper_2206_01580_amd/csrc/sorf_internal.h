@@ -114,6 +114,33 @@ __device__ __forceinline__ void fwht(float (&v)[EPL], uint32_t q) {
   fwht_across_lanes<0, LOGK, EPL>(v, q);
 }
 
+// The same with the exchanges beyond a quad requested 16 at a time, where the
+// compiler would wait for each of them before it requests the next.
+template <int BIT, int LOGK, int EPL>
+__device__ __forceinline__ void fwht_far_lanes(float (&v)[EPL], uint32_t q) {
+  if constexpr (BIT < LOGK) {
+    const float m = ((q >> BIT) & 1u) ? -1.0f : 1.0f;
+#pragma unroll
+    for (int r0 = 0; r0 < EPL; r0 += 16) {
+      float t[16];
+#pragma unroll
+      for (int r = 0; r < 16; ++r) t[r] = lane_xor<BIT>(v[r0 + r]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) v[r0 + r] = __builtin_fmaf(m, t[r], v[r0 + r]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    fwht_far_lanes<BIT + 1, LOGK, EPL>(v, q);
+  }
+}
+template <int LOGK, int EPL>
+__device__ __forceinline__ void fwht_ahead(float (&v)[EPL], uint32_t q) {
+  static_assert(EPL % 16 == 0, "batches");
+  fwht_in_lane<EPL>(v);
+  fwht_across_lanes<0, (LOGK < 2 ? LOGK : 2), EPL>(v, q);
+  fwht_far_lanes<2, LOGK, EPL>(v, q);
+}
+
 // Multiply entry r by -1 when bit r of the lane's sign words is set.
 template <int EPL>
 __device__ __forceinline__ void apply_signs(float (&v)[EPL], const uint32_t* w) {
