@@ -1408,11 +1408,11 @@ static hipError_t forward_dispatch(const SorfFeatureArgs& a, float* Z, const flo
 // From d = 64 on three forms give the same bits (us, energies and gradients,
 // T = 3): several waves per atom in step (N), one wave per atom in step (1),
 // one wave per atom out of step (adjoint_wave_kernel, W).
-//  - Below d = 512 and up to eight passes, N or 1 by the number of atoms: one wave
-//    saves the sums over waves, several fill the chip evenly. 21,000 atoms with 64
-//    stacks take 383 us with one and 390 with four (the whole prediction), 360,149
-//    atoms 8.87 and 9.29 ms (energies and forces from coordinates), but 8400 atoms
-//    181 and 172, and with 128 stacks 287 and 263.
+//  - Below d = 512 and up to eight passes, N or 1 by the rounds they take: one
+//    of 256 workgroups, one per compute unit, takes 5.7 us for one pass of each
+//    of its waves with N and 5.4 a pass with 1, but N leaves 8 mod passes of
+//    eight waves idle. 64 stacks of 128 (4 passes): 5000 atoms N 68, 1 74, 16,000
+//    194 and 182; 65 stacks (5 passes): 113 and 91, 337 and 222.
 //  - More passes: N, or W where its last round leaves too many waves idle. 16,000
 //    atoms, d = 128, 9 passes N 574, W 444; 13 686, 638; 16 697, 777; d = 256, 13
 //    passes 788, 658; 16 807, 804. Up to 2000 atoms W has too few waves in flight
@@ -1421,7 +1421,6 @@ static hipError_t forward_dispatch(const SorfFeatureArgs& a, float* Z, const flo
 //    waves a SIMD, and W has three: N for few atoms only. d = 512, 4 passes: 500
 //    atoms N 18, W 33, 1000 31 and 34, 2000 47 and 42, 40,000 990 (1: 836) and
 //    550; one pass, 21 atoms 16.3 and 16.4, 40,000 245 and 158.
-constexpr int64_t kAdjBulkAtoms = 16384;
 template <int LOG_D>
 static hipError_t adjoint_dispatch(const SorfFeatureArgs& a, const float* alpha, const float* dE,
                                    float* grad_x, float* e_atom, bool latency, hipStream_t st) {
@@ -1433,6 +1432,7 @@ static hipError_t adjoint_dispatch(const SorfFeatureArgs& a, const float* alpha,
     constexpr int VPW = LockLayout<LOG_D>::VPW;
     const int64_t passes = (int64_t(a.n_stacks) + VPW - 1) / VPW, A = a.n_atoms;
     const auto blocks = [&](int64_t per) { return (A + per - 1) / per; };
+    const auto cu_rounds = [&](int64_t per) { return (blocks(per) + 255) / 256; };
     const int per_n = kLockWaves / waves;   // atoms per workgroup with N
     // busy waves of a workgroup with N, on average
     const double busy = passes <= kAdjMaxWaves
@@ -1440,7 +1440,8 @@ static hipError_t adjoint_dispatch(const SorfFeatureArgs& a, const float* alpha,
                             : double(passes) / double((passes + kAdjMaxWaves - 1) / kAdjMaxWaves);
     const bool out_of_step = LOG_D >= 9 ? passes == 1 || double(A) > 192.0 * busy
                                         : passes > kAdjMaxWaves && busy < 6.8 && A > 2048;
-    const bool one = passes <= kAdjMaxWaves && A >= kAdjBulkAtoms;
+    const bool one = passes <= kAdjMaxWaves &&
+                     54 * passes * cu_rounds(kLockWaves) <= 57 * cu_rounds(per_n);
     const int nw = one ? 1 : waves;
     const int64_t per = out_of_step ? 4 : kLockWaves / nw;
     const AdjointArgs g{a.x, a.element, a.signs, a.bias, alpha, grad_x, e_atom, a.n_stacks,
