@@ -30,6 +30,21 @@ __device__ __forceinline__ void lds_wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Largest m with ptr[m] <= v (ptr[0] <= v < ptr[n]) by the 64 lanes of a wave.
+__device__ __forceinline__ int64_t wave_segment(const int64_t* __restrict__ ptr, int64_t n,
+                                                int64_t v) {
+  int64_t lo = 0, hi = n;
+  while (hi - lo > 1) {
+    const int64_t step = (hi - lo + 63) / 64;
+    const int64_t i = lo + (int64_t(lane_id()) + 1) * step;
+    const int64_t at = ptr[i < hi ? i : hi - 1];
+    const int64_t under = __popcll(__ballot(i < hi && at <= v));
+    lo += under * step;
+    hi = lo + step < hi ? lo + step : hi;
+  }
+  return lo;
+}
+
 // ---------------------------------------------------------------------------
 // Forward features
 // ---------------------------------------------------------------------------
@@ -316,13 +331,7 @@ void forward_lock_kernel(const float* __restrict__ x, const int32_t* __restrict_
   int64_t m = c, a0, a1;
   if constexpr (DOT) {
     if (c >= chunk_ptr[n_mols]) return;      // whole workgroups leave
-    int64_t lo = 0, hi = n_mols;             // chunk_ptr[m] <= c < chunk_ptr[m + 1]
-    while (hi - lo > 1) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (chunk_ptr[mid] <= c) lo = mid;
-      else hi = mid;
-    }
-    m = lo;
+    m = wave_segment(chunk_ptr, n_mols, c);  // chunk_ptr[m] <= c < chunk_ptr[m + 1]
     const int64_t m1 = mol_ptr[m + 1];
     a0 = mol_ptr[m] + (c - chunk_ptr[m]) * kEnergyChunkAtoms;
     a1 = a0 + kEnergyChunkAtoms < m1 ? a0 + kEnergyChunkAtoms : m1;
@@ -344,8 +353,10 @@ void forward_lock_kernel(const float* __restrict__ x, const int32_t* __restrict_
 #pragma unroll
   for (int r = 0; r < EPL; ++r) acc[r] = 0.0f;
 
-  // this wave's atom of step i, or the workgroup's last one when it has none
-  auto atom = [&](int64_t i) { return a0 + 2 * i + half < a1 ? a0 + 2 * i + half : a1 - 1; };
+  // whether this wave has an atom in step i (the odd one has none in the last step of an
+  // odd number of atoms: then it only keeps the barriers), and that atom
+  auto has = [&](int64_t i) { return a0 + 2 * i + half < a1; };
+  auto atom = [&](int64_t i) { return a0 + 2 * i + half; };
   uint32_t raw[3][L::RAW];
   auto request = [&](int64_t a, int32_t e, int buf) {   // row and sign words of an atom
 #pragma unroll
@@ -356,36 +367,39 @@ void forward_lock_kernel(const float* __restrict__ x, const int32_t* __restrict_
       if (t < T) L::load_raw(raw[t], sv + t * tstride, q);
   };
   int32_t e = 0, e_next = 0;
-  if (trips > 0) {
+  if (has(0)) {
     e = element[atom(0)];
-    e_next = element[atom(trips > 1 ? 1 : 0)];
+    e_next = element[atom(has(1) ? 1 : 0)];
     request(atom(0), e, 0);
   }
   for (int64_t i = 0; i < trips; ++i) {
-    const bool mine = a0 + 2 * i + half < a1;   // false for the odd wave's last step only
-    const bool more = i + 1 < trips;
+    const bool mine = has(i), more = has(i + 1);
     const int buf = int(i) & 1;
     float v[EPL];
     wait_loads<0>();   // row and sign words have landed
+    if (mine) {
 #pragma unroll
-    for (int r = 0; r < EPL; r += 4) {
-      const float4 t = *reinterpret_cast<const float4*>(&xrow[wv][buf][L::entry(r, q)]);
-      v[r] = t.x;
-      v[r + 1] = t.y;
-      v[r + 2] = t.z;
-      v[r + 3] = t.w;
+      for (int r = 0; r < EPL; r += 4) {
+        const float4 t = *reinterpret_cast<const float4*>(&xrow[wv][buf][L::entry(r, q)]);
+        v[r] = t.x;
+        v[r + 1] = t.y;
+        v[r + 2] = t.z;
+        v[r + 3] = t.w;
+      }
+      const float* bp = bias + int64_t(e) * Dtot + int64_t(s0) * DV + 4 * lane;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) dma16(bp + 256 * j, &phase[wv][phase_piece<LOG_D>(j)]);
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     }
-    const float* bp = bias + int64_t(e) * Dtot + int64_t(s0) * DV + 4 * lane;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) dma16(bp + 256 * j, &phase[wv][phase_piece<LOG_D>(j)]);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     lock_step();
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
       if (t < T) {
-        const uint32_t w[1] = {L::sign_word(raw[t], q) ^ (t > 0 ? flip : 0u)};
-        apply_signs<EPL>(v, w);
-        fwht<LOGK, EPL>(v, q);
+        if (mine) {
+          const uint32_t w[1] = {L::sign_word(raw[t], q) ^ (t > 0 ? flip : 0u)};
+          apply_signs<EPL>(v, w);
+          fwht<LOGK, EPL>(v, q);
+        }
         if (t < T - 1) lock_step();
       }
     }
@@ -393,7 +407,7 @@ void forward_lock_kernel(const float* __restrict__ x, const int32_t* __restrict_
     if (more) {
       e = e_next;
       request(atom(i + 1), e, buf ^ 1);
-      e_next = element[atom(i + 2 < trips ? i + 2 : i + 1)];
+      e_next = element[atom(has(i + 2) ? i + 2 : i + 1)];
     }
     if (mine) {
 #pragma unroll
@@ -538,21 +552,6 @@ struct AdjointArgs {
   int32_t S, T;
   float c_rev, g_scale, e_scale;
 };
-
-// Largest m with ptr[m] <= v (ptr[0] <= v < ptr[n]) by the 64 lanes of a wave.
-__device__ __forceinline__ int64_t wave_segment(const int64_t* __restrict__ ptr, int64_t n,
-                                                int64_t v) {
-  int64_t lo = 0, hi = n;
-  while (hi - lo > 1) {
-    const int64_t step = (hi - lo + 63) / 64;
-    const int64_t i = lo + (int64_t(lane_id()) + 1) * step;
-    const int64_t at = ptr[i < hi ? i : hi - 1];
-    const int64_t under = __popcll(__ballot(i < hi && at <= v));
-    lo += under * step;
-    hi = lo + step < hi ? lo + step : hi;
-  }
-  return lo;
-}
 
 // The gradient row of an atom from its lane sums in LDS (eight blocks of 64 float4,
 // AdjointShared's BLOCK floats apart): the lane groups, first and second half, each in order.
