@@ -313,8 +313,11 @@ hipError_t sorf_launch_project(int64_t n_atoms, int32_t d_rep, const float* rho,
     const dim3 grid(unsigned(max_tiles), unsigned((d + cols - 1) / cols));
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, st, rho, d_rep, U, d, E, off, tiles, perm, x);
   };
-  // fewer large tiles than compute units: the small ones
-  if (max_tiles * ((d + kProjCols - 1) / kProjCols) < 256)
+  // The small tiles while two rounds of them (one fills a compute unit's LDS) cover the
+  // call: a round takes 35 us at d_rep = 720, one round of large tiles 75. d = 128: 15,700
+  // atoms 69 us against 76, 20,000 (three rounds) 98 against 77; d = 64: 32,000 atoms 71
+  // against 100.
+  if (max_tiles * ((d + 31) / 32) <= 512)
     vec4 ? go(proj_gemm_kernel<true, 32, 64>, 32) : go(proj_gemm_kernel<false, 32, 64>, 32);
   else
     vec4 ? go(proj_gemm_kernel<true, kProjCols, kProjK>, kProjCols)
