@@ -232,7 +232,7 @@ sorf_status sorf_fchl19_backward(const float* R, const int32_t* element, const i
     return SORF_ERR_INVALID_ARG;
   const FchlParamsHost p{params->n2, params->n3, params->eta2, params->eta3, params->N2,
                          params->N3, params->c3, params->zeta, params->rcut};
-  return dev(sorf_launch_fchl19_backward(R, element, mol_ptr, n_mols, n_elements, p, g, dR,
+  return dev(sorf_launch_fchl19_backward(R, element, mol_ptr, n_atoms, n_mols, n_elements, p, g, dR,
                                          hipStream_t(stream)));
 }
 

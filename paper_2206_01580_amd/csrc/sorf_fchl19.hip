@@ -98,16 +98,17 @@ constexpr int kFchlThreads = 1024;   // workgroup of the kernels for large molec
 // two barriers for any molecule, where a pass per element and 1024 atoms had
 // one each and formed the neighbours' factors anew in each (1260 atoms: the
 // forward 173 us, now 133, the backward 167, now 132).
+template <int NT>
 struct FchlGather {
-  int32_t first[kFchlMaxElements][kFchlThreads / 64];
+  int32_t first[kFchlMaxElements][NT / 64];
   int32_t grp[kFchlMaxElements + 1];
 };
-template <typename Store>
+template <int NT, typename Store>
 __device__ __forceinline__ int fchl_gather(int64_t i, int64_t a0, int64_t a1,
                                            const float* __restrict__ R,
                                            const int32_t* __restrict__ element, int32_t E,
-                                           float rc, FchlGather& sh, Store store) {
-  constexpr int NW = kFchlThreads / 64;
+                                           float rc, FchlGather<NT>& sh, Store store) {
+  constexpr int NW = NT / 64;
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const float xi = R[3 * i], yi = R[3 * i + 1], zi = R[3 * i + 2];
   const int64_t pieces = (a1 - a0 + 64 * NW - 1) / (64 * NW);   // of 64 atoms, per wave
@@ -175,7 +176,29 @@ __device__ __forceinline__ int fchl_gather(int64_t i, int64_t a0, int64_t a1,
   return sh.grp[E];
 }
 
-// Atom i of molecule m (atoms a0 .. a1 - 1), a workgroup of kFchlThreads.
+// Pairs of neighbours numbered by element pair X <= Y, then by position: seg[P] the
+// first of element pair P, seg[NP] their number, xy[P] = X | Y << 8. One thread per
+// element pair (one thread for all took a third of the time of an atom with few
+// neighbours and 16 elements).
+template <int NT>
+__device__ __forceinline__ void fchl_segments(const int32_t* grp, int E, int32_t* seg, int32_t* xy) {
+  const int NP = E * (E + 1) / 2, n = grp[E];
+  for (int P = threadIdx.x; P < NP; P += NT) {
+    int X = 0;
+    while (fchl_pair(X, X, E) + (E - X) <= P) ++X;
+    const int Y = X + (P - fchl_pair(X, X, E));
+    // pairs whose first neighbour comes before X's, then those of X before Y's
+    const int gX = grp[X], cx = grp[X + 1] - gX;
+    int32_t o = gX * (2 * n - gX - 1) / 2;
+    if (Y > X) o += cx * (cx - 1) / 2 + cx * (grp[Y] - grp[X + 1]);
+    seg[P] = o;
+    xy[P] = X | (Y << 8);
+  }
+  if (threadIdx.x == 0) seg[NP] = n * (n - 1) / 2;
+}
+
+// Atom i of molecule m (atoms a0 .. a1 - 1), a workgroup of NT threads. The sums
+// are those of kFchlThreads threads with either NT, so the bits are the same.
 //
 // Bound by vector issue: the pair weights (about 150 instructions a pair) and
 // the radial bins (an exponential and about ten instructions a pair and bin).
@@ -184,24 +207,26 @@ __device__ __forceinline__ int fchl_gather(int64_t i, int64_t a0, int64_t a1,
 // per radial bin, each with an equal part of the chunk's pairs in order; one
 // thread per (element pair, bin) left all but the largest element pair's
 // threads idle (182 us for the 245 atoms of a cluster, now 37).
+template <int NT>
 __device__ __forceinline__ void fchl19_forward_atom(
     int64_t i, int64_t a0, int64_t a1, const float* __restrict__ R,
     const int32_t* __restrict__ element, int32_t E, const FchlParams& p, int64_t size,
     float* __restrict__ rho) {
-  constexpr int NT = kFchlThreads;
+  constexpr int VT = kFchlThreads;
   __shared__ float nx[kFchlMaxNb], ny[kFchlMaxNb], nz[kFchlMaxNb], nr[kFchlMaxNb];
   __shared__ float ni[kFchlMaxNb], nw[kFchlMaxNb], c2[kFchlMaxNb], mu2[kFchlMaxNb], inv2s2[kFchlMaxNb];
-  __shared__ FchlGather gathered;
+  __shared__ FchlGather<NT> gathered;
   __shared__ int32_t seg[kFchlMaxElements * (kFchlMaxElements + 1) / 2 + 1];
   __shared__ int32_t pair_xy[kFchlMaxElements * (kFchlMaxElements + 1) / 2];
   __shared__ float4 pw[kFchlPairChunk];             // w cos, w sin, mean distance
-  __shared__ float2 tail[NT];
+  __shared__ float2 tail[VT], head[NT < VT ? VT : 1];
+  __shared__ int32_t ends[NT < VT ? VT / 2 : 1];    // n3 >= 2
 
   const int tid = threadIdx.x;
   const float rc = p.rcut;
   float* __restrict__ out = rho + i * size;
   const int32_t* const grp = gathered.grp;          // neighbour offsets per element
-  const int total = fchl_gather(
+  const int total = fchl_gather<NT>(
       i, a0, a1, R, element, E, rc, gathered,
       [&](int slot, int64_t, float dx, float dy, float dz, float r) {
         // f_cut as sin^2(pi (r_cut - r) / (2 r_cut)), without the cancellation of
@@ -229,18 +254,7 @@ __device__ __forceinline__ void fchl19_forward_atom(
 
   // three-body: pair numbering by element pair X <= Y
   const int NP = E * (E + 1) / 2;
-  if (tid == 0) {
-    int32_t o = 0;
-    for (int X = 0; X < E; ++X)
-      for (int Y = X; Y < E; ++Y) {
-        const int P = fchl_pair(X, Y, E);
-        seg[P] = o;
-        pair_xy[P] = X | (Y << 8);
-        const int32_t cx = grp[X + 1] - grp[X], cy = grp[Y + 1] - grp[Y];
-        o += X == Y ? cx * (cx - 1) / 2 : cx * cy;
-      }
-    seg[NP] = o;
-  }
+  fchl_segments<NT>(grp, E, seg, pair_xy);
 
   // two-body bins
   for (int t = tid; t < E * p.n2; t += NT) {
@@ -268,12 +282,14 @@ __device__ __forceinline__ void fchl19_forward_atom(
     }
   }
   // G groups of n3 threads, thread kl of a group on radial bin kl; group g
-  // walks the g-th of G equal parts of a chunk, of kFchlPartPairs pairs at least. An element pair whose pairs
-  // fall in several parts is finished by the group where it ends, which adds
-  // the earlier groups' partial sums in group order. With more radial bins
-  // than threads the threads of one group loop over them.
-  const int most = p.n3 <= NT ? NT / p.n3 : 1;
-  const int g = p.n3 <= NT ? tid / p.n3 : 0;
+  // walks the g-th of G equal parts of a chunk, of kFchlPartPairs pairs at least. An
+  // element pair whose pairs fall in several parts is finished by the group where it
+  // ends, which adds the earlier groups' partial sums in group order. With more radial
+  // bins than threads the threads of one group loop over them. With fewer than VT
+  // threads (n3 <= NT then) each group of threads takes every step-th group.
+  const int most = p.n3 <= VT ? VT / p.n3 : 1;
+  const int step = NT < VT ? NT / p.n3 : most;
+  const int g0 = p.n3 <= NT ? tid / p.n3 : 0;
   const int kl = p.n3 <= NT ? tid % p.n3 : tid;
   const float keta = -p.eta3 * 1.44269504088896341f;
   int P = 0, Q0 = 0;   // non-decreasing over the chunks
@@ -315,9 +331,11 @@ __device__ __forceinline__ void fchl19_forward_atom(
     __syncthreads();
     const int32_t L = q1 - q0;
     const int G = min(most, (L + kFchlPartPairs - 1) / kFchlPartPairs);
-    int pend = -1;                      // element pair to finish after the tails are stored
-    float pc = 0.f, ps = 0.f;
-    for (int k = kl; k < p.n3 && g < G; k += NT) {
+    // Radial bin k of group g's part: adds up the element pairs that begin and end in it,
+    // returns the one (or -1) that only ends in it with its sums (pc, ps), and leaves
+    // the sums of the one that is open at the part's end in tail.
+    const auto part = [&](int g, int k, int& Q0, float& pc, float& ps) {
+      int pend = -1;
       const float Rk = rc * float(k) / float(p.n3 - 1);
       const int32_t lo = q0 + L * g / G, hi = q0 + L * (g + 1) / G;
       while (Q0 < NP && seg[Q0 + 1] <= lo) ++Q0;
@@ -353,74 +371,117 @@ __device__ __forceinline__ void fchl19_forward_atom(
           started = true;
         }
       }
-      tail[tid] = make_float2(c, sn);   // open partial at the end of the part (0 if none)
-    }
-    __syncthreads();
-    if (pend >= 0) {
-      const int32_t st = seg[pend] > q0 ? seg[pend] : q0;
+      tail[g * p.n3 + (p.n3 <= VT ? k : tid)] = make_float2(c, sn);   // 0 if none is open
+      return pend;
+    };
+    // Element pair Q, which ends in group g's part with the sums (pc, ps) and began earlier.
+    const auto finish = [&](int g, int k, int Q, float pc, float ps) {
+      const int32_t st = seg[Q] > q0 ? seg[Q] : q0;
       int gs = g - 1;                   // the group in whose part the element pair starts
       while (gs > 0 && q0 + L * gs / G > st) --gs;
       float sc = 0.f, ss = 0.f;
       for (int gg = gs; gg < g; ++gg) {
-        sc += tail[gg * p.n3 + kl].x;
-        ss += tail[gg * p.n3 + kl].y;
+        sc += tail[gg * p.n3 + k].x;
+        ss += tail[gg * p.n3 + k].y;
       }
-      float* o = out3 + 2 * (int64_t(pend) * p.n3 + kl);
-      const bool first = seg[pend] >= q0;
+      float* o = out3 + 2 * (int64_t(Q) * p.n3 + k);
+      const bool first = seg[Q] >= q0;
       o[0] = first ? sc + pc : o[0] + (sc + pc);
       o[1] = first ? ss + ps : o[1] + (ss + ps);
+    };
+    if constexpr (NT == VT) {
+      int pend = -1;
+      float pc = 0.f, ps = 0.f;
+      for (int k = kl; k < p.n3 && g0 < G; k += NT) pend = part(g0, k, Q0, pc, ps);
+      __syncthreads();
+      if (pend >= 0) finish(g0, kl, pend, pc, ps);
+    } else {
+      int Qg = Q0;
+      for (int g = g0; g < G && g0 < step; g += step) {
+        float pc = 0.f, ps = 0.f;
+        const int pend = part(g, kl, Qg, pc, ps);
+        head[g * p.n3 + kl] = make_float2(pc, ps);
+        if (kl == 0) ends[g] = pend;
+        if (g == g0) Q0 = Qg;
+      }
+      __syncthreads();
+      for (int g = g0; g < G && g0 < step; g += step)
+        if (ends[g] >= 0) {
+          const float2 h = head[g * p.n3 + kl];
+          finish(g, kl, ends[g], h.x, h.y);
+        }
     }
     __syncthreads();   // weights and tails are reused, and the next chunk adds to these entries
   }
 }
 
 // Atoms of larger molecules: a persistent grid in which every workgroup reads
-// the molecule sizes kFchlThreads at a time (coalesced), collects the molecules above
-// kFchlSmallMol atoms with ballots, and gives a whole workgroup to atom j of
-// such a molecule m when (m + j) mod grid is its own index, so that the atoms
-// of one large molecule spread over consecutive workgroups.
-__global__ __launch_bounds__(kFchlThreads) void fchl19_forward_kernel(
-    const float* __restrict__ R, const int32_t* __restrict__ element,
-    const int64_t* __restrict__ mol_ptr, int64_t n_mols, int32_t E, FchlParams p,
-    int64_t size, float* __restrict__ rho) {
-  constexpr int NT = kFchlThreads, NW = NT / 64;
-  __shared__ int32_t big[NT];
-  __shared__ int32_t wbig[NW];
+// the molecule sizes NT at a time (coalesced), collects the molecules above
+// kFchlSmallMol atoms with ballots, and takes those of their atoms whose index in
+// the batch is its own modulo the grid, so that the atoms of one large molecule and
+// of several spread evenly (from (m + j) mod grid on for atom j of molecule m, a
+// hundred molecules of 65 atoms shared a quarter of the workgroups). What the walk
+// over the molecules needs is in LDS.
+template <int NT>
+struct FchlDeal {
+  int64_t a0[NT], n[NT];   // first atom, atoms
+  int32_t shift[NT];       // first atom mod grid
+  int32_t per_wave[NT / 64];
+};
+template <int NT, typename Atom>
+__device__ __forceinline__ void fchl_deal(const int64_t* __restrict__ mol_ptr, int64_t n_mols,
+                                          int small, FchlDeal<NT>& sh, Atom atom) {
+  constexpr int NW = NT / 64;
   const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int64_t G = gridDim.x, b = blockIdx.x;
+  const int32_t G = int32_t(gridDim.x), b = int32_t(blockIdx.x);
   int64_t lo = 0, hi = 0;
   if (tid < n_mols) {
     lo = mol_ptr[tid];
     hi = mol_ptr[tid + 1];
   }
   for (int64_t m0 = 0; m0 < n_mols; m0 += NT) {
-    const int64_t m = m0 + tid;
-    const bool large = m < n_mols && hi - lo > kFchlSmallMol;
+    const int64_t m = m0 + tid, a0 = lo, n = hi - lo;
+    const bool large = m < n_mols && n > small;
     // next group's sizes in flight while this group is processed
     if (m + NT < n_mols) {
       lo = mol_ptr[m + NT];
       hi = mol_ptr[m + NT + 1];
     }
     const uint64_t mask = __ballot(large);
-    if (lane == 0) wbig[wv] = __popcll(mask);
+    if (lane == 0) sh.per_wave[wv] = __popcll(mask);
     __syncthreads();
     int off = 0, nbig = 0;
     for (int w = 0; w < NW; ++w) {
-      off += w < wv ? wbig[w] : 0;
-      nbig += wbig[w];
+      off += w < wv ? sh.per_wave[w] : 0;
+      nbig += sh.per_wave[w];
     }
-    if (large) big[off + __popcll(mask & ((uint64_t(1) << lane) - 1))] = tid;
+    if (large) {
+      const int t = off + __popcll(mask & ((uint64_t(1) << lane) - 1));
+      sh.a0[t] = a0;
+      sh.n[t] = n;
+      sh.shift[t] = int32_t(uint64_t(a0) % uint32_t(G));
+    }
     __syncthreads();
     for (int t = 0; t < nbig; ++t) {
-      const int64_t mm = m0 + big[t];
-      const int64_t a0 = mol_ptr[mm], a1 = mol_ptr[mm + 1];
-      for (int64_t j = ((b - mm) % G + G) % G; j < a1 - a0; j += G) {
-        fchl19_forward_atom(a0 + j, a0, a1, R, element, E, p, size, rho);
-        __syncthreads();   // the next atom reuses the LDS
-      }
+      const int32_t j0 = b - sh.shift[t];
+      const int64_t n_t = sh.n[t];
+      for (int64_t j = j0 < 0 ? j0 + G : j0; j < n_t; j += G)
+        atom(sh.a0[t] + j, sh.a0[t], sh.a0[t] + n_t);
     }
-    __syncthreads();   // big[] and wbig[] are rewritten by the next group
+    __syncthreads();   // the list is rewritten by the next group
   }
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void fchl19_forward_kernel(
+    const float* __restrict__ R, const int32_t* __restrict__ element,
+    const int64_t* __restrict__ mol_ptr, int64_t n_mols, int32_t E, FchlParams p,
+    int64_t size, float* __restrict__ rho) {
+  __shared__ FchlDeal<NT> deal;
+  fchl_deal<NT>(mol_ptr, n_mols, kFchlSmallMol, deal, [&](int64_t i, int64_t a0, int64_t a1) {
+    fchl19_forward_atom<NT>(i, a0, a1, R, element, E, p, size, rho);
+    __syncthreads();   // the next atom reuses the LDS
+  });
 }
 
 // Atoms of molecules of at most kFchlSmallMol atoms: one wave per atom, four
@@ -1047,26 +1108,27 @@ __global__ __launch_bounds__(64 * NW) void fchl19_backward_small_kernel(
 // has four on each SIMD; what depends on one neighbour alone (1 / r, f_cut
 // and its derivative, r^-N3) is formed once per neighbour. 124 us for the 245
 // atoms of a cluster with four waves and every factor formed per triple, now 47.
-__device__ void fchl19_backward_atom(int64_t t, int64_t a0, int64_t a1,
+template <int NT>
+__device__ __forceinline__ void fchl19_backward_atom(int64_t t, int64_t a0, int64_t a1,
                                      const float* __restrict__ R,
                                      const int32_t* __restrict__ element, int32_t E,
                                      const FchlParams& p, int64_t size,
                                      const float* __restrict__ g, float* __restrict__ dR) {
-  constexpr int NT = kFchlThreads, NW = NT / 64;
+  constexpr int VT = kFchlThreads, NW = VT / 64;   // sums of VT threads, whatever NT
   __shared__ int32_t nidx[kFchlMaxNb];
   __shared__ float nx[kFchlMaxNb], ny[kFchlMaxNb], nz[kFchlMaxNb];
   __shared__ FchlSide ns[kFchlMaxNb];
-  __shared__ FchlGather gathered;
+  __shared__ FchlGather<NT> gathered;
   __shared__ int32_t seg[kFchlMaxElements * (kFchlMaxElements + 1) / 2 + 1];
   __shared__ int32_t pair_xy[kFchlMaxElements * (kFchlMaxElements + 1) / 2];
   __shared__ double red[3][NW];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
   const float rc = p.rcut;
   const float angw = 2.0f * expf(-0.5f * p.zeta * p.zeta) * sqrtf(p.eta3 / 3.14159265358979f);
   const int NP = E * (E + 1) / 2;
   const int et = element[t];
   const int32_t* const grp = gathered.grp;
-  const int total = fchl_gather(
+  const int total = fchl_gather<NT>(
       t, a0, a1, R, element, E, rc, gathered,
       [&](int sl, int64_t j, float dx, float dy, float dz, float r) {
         nidx[sl] = int32_t(j - a0);
@@ -1076,20 +1138,8 @@ __device__ void fchl19_backward_atom(int64_t t, int64_t a0, int64_t a1,
         ns[sl] = FchlSide{r, fchl_rcp(r), fchl_fcut(r, rc), fchl_dfcut(r, rc), powf(r, -p.N3)};
       });
   const bool bad = total > kFchlMaxNb;   // uniform: every thread counted the same chunks
-  double px = 0.0, py = 0.0, pz = 0.0;   // FP64 sums: a large centre adds thousands of terms
   if (!bad) {
-    if (tid == 0) {
-      int32_t o = 0;
-      for (int X = 0; X < E; ++X)
-        for (int Y = X; Y < E; ++Y) {
-          const int P = fchl_pair(X, Y, E);
-          seg[P] = o;
-          pair_xy[P] = X | (Y << 8);
-          const int32_t cxn = grp[X + 1] - grp[X], cyn = grp[Y + 1] - grp[Y];
-          o += X == Y ? cxn * (cxn - 1) / 2 : cxn * cyn;
-        }
-      seg[NP] = o;
-    }
+    fchl_segments<NT>(grp, E, seg, pair_xy);
     __syncthreads();
     const float* __restrict__ gt = g + t * size;
     // a triple whose sides a and b end at t and whose third side is new
@@ -1097,90 +1147,94 @@ __device__ void fchl19_backward_atom(int64_t t, int64_t a0, int64_t a1,
       return FchlSide{r, fchl_rcp(r), fchl_fcut(r, rc), fchl_dfcut(r, rc),
                       __builtin_amdgcn_exp2f(-p.N3 * __builtin_amdgcn_logf(r))};
     };
-    // centre t, two-body
-    for (int sl = tid; sl < total; sl += NT) {
-      int X = 0;
-      while (sl >= grp[X + 1]) ++X;
-      const float f = fchl_pair_grad(ns[sl].r, gt + X * p.n2, p) * ns[sl].inv;
-      px -= f * nx[sl];
-      py -= f * ny[sl];
-      pz -= f * nz[sl];
-    }
-    // centre t, three-body over its unordered neighbour pairs
-    const int32_t n_pairs = seg[NP];
-    int P = 0;   // non-decreasing over this thread's pairs
-    for (int32_t q = tid; q < n_pairs; q += NT) {
-      while (q >= seg[P + 1]) ++P;
-      const int X = pair_xy[P] & 255, Y = pair_xy[P] >> 8;
-      const int32_t loc = q - seg[P];
-      int sa, sb;
-      if (X != Y) {
-        const int cyn = grp[Y + 1] - grp[Y];
-        const int u = fchl_div(loc, cyn);
-        sa = grp[X] + u;
-        sb = grp[Y] + loc - u * cyn;
-      } else {
-        const int cxn = grp[X + 1] - grp[X];
-        const int u = fchl_pair_row(loc, cxn);
-        sa = grp[X] + u;
-        sb = grp[X] + u + 1 + (loc - u * (2 * cxn - u - 1) / 2);
-      }
-      const float wx = nx[sb] - nx[sa], wy = ny[sb] - ny[sa], wz = nz[sb] - nz[sa];
-      const float c = sqrtf(wx * wx + wy * wy + wz * wz);
-      if (!(c < rc)) continue;   // f_cut(r_jl) and its derivative vanish
-      const FchlSide A = ns[sa], B = ns[sb], C = far_side(c);
-      float dL[3];
-      fchl_triple_grad(A, B, C, A.pn * B.pn * C.pn,
-                       gt + int64_t(E) * p.n2 + int64_t(P) * p.n3 * 2, p, angw, dL);
-      const float fa = dL[0] * A.inv, fb = dL[1] * B.inv;
-      px -= fa * nx[sa] + fb * nx[sb];
-      py -= fa * ny[sa] + fb * ny[sb];
-      pz -= fa * nz[sa] + fb * nz[sb];
-    }
-    // each neighbour c of t as a centre: t's two-body term in c's row, and
-    // the pairs {t, l} of c. A pair's terms carry f_cut(r_tl), so only the
-    // neighbours l of t contribute, and those are in t's list: the pairs
-    // (c, l) of t's list with r_cl < r_cut, flattened over the threads
-    for (int cs = tid; cs < total; cs += NT) {
-      const float* __restrict__ gc = g + (a0 + nidx[cs]) * size;
-      const float f = fchl_pair_grad(ns[cs].r, gc + et * p.n2, p) * ns[cs].inv;
-      px -= f * nx[cs];   // (R_t - R_c) = -(R_c - R_t)
-      py -= f * ny[cs];
-      pz -= f * nz[cs];
-    }
-    const int32_t n_cl = total * total;
-    for (int32_t q = tid; q < n_cl; q += NT) {
-      const int cs = fchl_div(q, total), ls = q - cs * total;
-      if (ls == cs) continue;
-      const float wx = nx[ls] - nx[cs], wy = ny[ls] - ny[cs], wz = nz[ls] - nz[cs];   // R_l - R_c
-      const float rcl = sqrtf(wx * wx + wy * wy + wz * wz);
-      if (!(rcl < rc)) continue;
-      int Y = 0;
-      while (ls >= grp[Y + 1]) ++Y;
-      const int Pc = et <= Y ? fchl_pair(et, Y, E) : fchl_pair(Y, et, E);
-      const float* __restrict__ gc = g + (a0 + nidx[cs]) * size;
-      const FchlSide A = ns[cs], B = far_side(rcl), C = ns[ls];
-      float dL[3];
-      fchl_triple_grad(A, B, C, A.pn * C.pn * B.pn,
-                       gc + int64_t(E) * p.n2 + int64_t(Pc) * p.n3 * 2, p, angw, dL);
-      // dL/da (R_t - R_c) / a + dL/dc (R_t - R_l) / c, with R_x - R_t = n[x]
-      const float fa = dL[0] * A.inv, fc = dL[2] * C.inv;
-      px -= fa * nx[cs] + fc * nx[ls];
-      py -= fa * ny[cs] + fc * ny[ls];
-      pz -= fa * nz[cs] + fc * nz[ls];
-    }
-  }
-  // lanes, then waves, in a fixed order
+    const int32_t n_pairs = seg[NP], n_cl = total * total;
+    for (int vt = tid; vt < VT; vt += NT) {
+      double px = 0.0, py = 0.0, pz = 0.0;   // FP64 sums: a large centre adds thousands of terms
+      if (vt - lane < max(n_pairs, n_cl)) {  // a wave with terms
+        // centre t, two-body
+        for (int sl = vt; sl < total; sl += VT) {
+          int X = 0;
+          while (sl >= grp[X + 1]) ++X;
+          const float f = fchl_pair_grad(ns[sl].r, gt + X * p.n2, p) * ns[sl].inv;
+          px -= f * nx[sl];
+          py -= f * ny[sl];
+          pz -= f * nz[sl];
+        }
+        // centre t, three-body over its unordered neighbour pairs
+        int P = 0;   // non-decreasing over this thread's pairs
+        for (int32_t q = vt; q < n_pairs; q += VT) {
+          while (q >= seg[P + 1]) ++P;
+          const int X = pair_xy[P] & 255, Y = pair_xy[P] >> 8;
+          const int32_t loc = q - seg[P];
+          int sa, sb;
+          if (X != Y) {
+            const int cyn = grp[Y + 1] - grp[Y];
+            const int u = fchl_div(loc, cyn);
+            sa = grp[X] + u;
+            sb = grp[Y] + loc - u * cyn;
+          } else {
+            const int cxn = grp[X + 1] - grp[X];
+            const int u = fchl_pair_row(loc, cxn);
+            sa = grp[X] + u;
+            sb = grp[X] + u + 1 + (loc - u * (2 * cxn - u - 1) / 2);
+          }
+          const float wx = nx[sb] - nx[sa], wy = ny[sb] - ny[sa], wz = nz[sb] - nz[sa];
+          const float c = sqrtf(wx * wx + wy * wy + wz * wz);
+          if (!(c < rc)) continue;   // f_cut(r_jl) and its derivative vanish
+          const FchlSide A = ns[sa], B = ns[sb], C = far_side(c);
+          float dL[3];
+          fchl_triple_grad(A, B, C, A.pn * B.pn * C.pn,
+                           gt + int64_t(E) * p.n2 + int64_t(P) * p.n3 * 2, p, angw, dL);
+          const float fa = dL[0] * A.inv, fb = dL[1] * B.inv;
+          px -= fa * nx[sa] + fb * nx[sb];
+          py -= fa * ny[sa] + fb * ny[sb];
+          pz -= fa * nz[sa] + fb * nz[sb];
+        }
+        // each neighbour c of t as a centre: t's two-body term in c's row, and
+        // the pairs {t, l} of c. A pair's terms carry f_cut(r_tl), so only the
+        // neighbours l of t contribute, and those are in t's list: the pairs
+        // (c, l) of t's list with r_cl < r_cut, flattened over the threads
+        for (int cs = vt; cs < total; cs += VT) {
+          const float* __restrict__ gc = g + (a0 + nidx[cs]) * size;
+          const float f = fchl_pair_grad(ns[cs].r, gc + et * p.n2, p) * ns[cs].inv;
+          px -= f * nx[cs];   // (R_t - R_c) = -(R_c - R_t)
+          py -= f * ny[cs];
+          pz -= f * nz[cs];
+        }
+        for (int32_t q = vt; q < n_cl; q += VT) {
+          const int cs = fchl_div(q, total), ls = q - cs * total;
+          if (ls == cs) continue;
+          const float wx = nx[ls] - nx[cs], wy = ny[ls] - ny[cs], wz = nz[ls] - nz[cs];   // R_l - R_c
+          const float rcl = sqrtf(wx * wx + wy * wy + wz * wz);
+          if (!(rcl < rc)) continue;
+          int Y = 0;
+          while (ls >= grp[Y + 1]) ++Y;
+          const int Pc = et <= Y ? fchl_pair(et, Y, E) : fchl_pair(Y, et, E);
+          const float* __restrict__ gc = g + (a0 + nidx[cs]) * size;
+          const FchlSide A = ns[cs], B = far_side(rcl), C = ns[ls];
+          float dL[3];
+          fchl_triple_grad(A, B, C, A.pn * C.pn * B.pn,
+                           gc + int64_t(E) * p.n2 + int64_t(Pc) * p.n3 * 2, p, angw, dL);
+          // dL/da (R_t - R_c) / a + dL/dc (R_t - R_l) / c, with R_x - R_t = n[x]
+          const float fa = dL[0] * A.inv, fc = dL[2] * C.inv;
+          px -= fa * nx[cs] + fc * nx[ls];
+          py -= fa * ny[cs] + fc * ny[ls];
+          pz -= fa * nz[cs] + fc * nz[ls];
+        }
+        // lanes in a fixed order
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    px += __shfl_xor(px, o);
-    py += __shfl_xor(py, o);
-    pz += __shfl_xor(pz, o);
-  }
-  if (lane == 0) {
-    red[0][wv] = px;
-    red[1][wv] = py;
-    red[2][wv] = pz;
+        for (int o = 32; o > 0; o >>= 1) {
+          px += __shfl_xor(px, o);
+          py += __shfl_xor(py, o);
+          pz += __shfl_xor(pz, o);
+        }
+      }
+      if (lane == 0) {
+        red[0][vt >> 6] = px;
+        red[1][vt >> 6] = py;
+        red[2][vt >> 6] = pz;
+      }
+    }
   }
   __syncthreads();
   if (tid < 3) {
@@ -1191,39 +1245,16 @@ __device__ void fchl19_backward_atom(int64_t t, int64_t a0, int64_t a1,
   __syncthreads();   // red[], the neighbour list and seg[] are rewritten for the next atom
 }
 
-// Molecules above kFchlSmallAtoms atoms: a resident grid (one workgroup per
-// compute unit) deals their atoms out, atom j of molecule m to workgroup
-// (m + j) mod G, as the forward kernel deals the atoms of large molecules.
-__global__ __launch_bounds__(kFchlThreads) void fchl19_backward_gather_kernel(
+// Molecules above kFchlSmallAtoms atoms, dealt out as the forward kernel deals them.
+template <int NT>
+__global__ __launch_bounds__(NT) void fchl19_backward_gather_kernel(
     const float* __restrict__ R, const int32_t* __restrict__ element,
     const int64_t* __restrict__ mol_ptr, int64_t n_mols, int32_t E, FchlParams p, int64_t size,
     const float* __restrict__ g, float* __restrict__ dR) {
-  constexpr int NT = kFchlThreads, NW = NT / 64;
-  __shared__ int32_t big[NT];
-  __shared__ int32_t wbig[NW];
-  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-  const int64_t G = gridDim.x, b = blockIdx.x;
-  for (int64_t m0 = 0; m0 < n_mols; m0 += NT) {
-    const int64_t m = m0 + tid;
-    const bool large = m < n_mols && mol_ptr[m + 1] - mol_ptr[m] > kFchlSmallAtoms;
-    const uint64_t mask = __ballot(large);
-    if (lane == 0) wbig[wv] = __popcll(mask);
-    __syncthreads();
-    int off = 0, nbig = 0;
-    for (int w = 0; w < NW; ++w) {
-      off += w < wv ? wbig[w] : 0;
-      nbig += wbig[w];
-    }
-    if (large) big[off + __popcll(mask & ((uint64_t(1) << lane) - 1))] = tid;
-    __syncthreads();
-    for (int k = 0; k < nbig; ++k) {
-      const int64_t mm = m0 + big[k];
-      const int64_t a0 = mol_ptr[mm], a1 = mol_ptr[mm + 1];
-      for (int64_t j = ((b - mm) % G + G) % G; j < a1 - a0; j += G)
-        fchl19_backward_atom(a0 + j, a0, a1, R, element, E, p, size, g, dR);
-    }
-    __syncthreads();   // big[] and wbig[] are rewritten by the next group of molecules
-  }
+  __shared__ FchlDeal<NT> deal;
+  fchl_deal<NT>(mol_ptr, n_mols, kFchlSmallAtoms, deal, [&](int64_t t, int64_t a0, int64_t a1) {
+    fchl19_backward_atom<NT>(t, a0, a1, R, element, E, p, size, g, dR);
+  });
 }
 
 }  // namespace sorf
@@ -1232,6 +1263,17 @@ using namespace sorf;
 
 int64_t sorf_fchl19_len(int32_t E, int32_t n2, int32_t n3) {
   return int64_t(E) * n2 + int64_t(E) * (E + 1) / 2 * n3 * 2;
+}
+
+// Workgroups of the kernels for large molecules, all resident so that the size scan runs
+// once: of kFchlThreads threads and one per compute unit (registers) while every atom has
+// one to itself, of half as many and two per unit (LDS) for more atoms, which hide one's
+// barriers and loads behind the other's work (forward and backward, us): 245 atoms with 46
+// neighbours 41 and 54, with the halves 52 and 59; 1260 atoms 122 and 151, halves 99 and
+// 131; 1000 molecules of 65 atoms with eight neighbours 2376 and 4132, halves 1360 and 2083.
+constexpr int64_t kFchlUnits = 256;
+static bool fchl_few_atoms(int64_t n_atoms, int32_t n3) {
+  return n_atoms <= kFchlUnits || n3 > kFchlThreads / 2;
 }
 
 hipError_t sorf_launch_fchl19_forward(const float* R, const int32_t* element,
@@ -1250,17 +1292,20 @@ hipError_t sorf_launch_fchl19_forward(const float* R, const int32_t* element,
     if (e != hipSuccess) return e;
   }
   if (n_mols == 0) return hipSuccess;
-  // one workgroup of this kernel fits a compute unit (registers), 256 units:
-  // the whole grid is resident, so the size scan runs once
-  const int64_t grid = n_atoms < 256 ? n_atoms : 256;
-  hipLaunchKernelGGL(fchl19_forward_kernel, dim3(unsigned(grid)), dim3(kFchlThreads), 0, st, R, element,
-                     mol_ptr, n_mols, E, p, size, rho);
+  const auto go = [&](auto kernel, int threads, int64_t most) {
+    hipLaunchKernelGGL(kernel, dim3(unsigned(n_atoms < most ? n_atoms : most)), dim3(unsigned(threads)),
+                       0, st, R, element, mol_ptr, n_mols, E, p, size, rho);
+  };
+  if (fchl_few_atoms(n_atoms, ph.n3))
+    go(fchl19_forward_kernel<kFchlThreads>, kFchlThreads, kFchlUnits);
+  else
+    go(fchl19_forward_kernel<kFchlThreads / 2>, kFchlThreads / 2, 2 * kFchlUnits);
   return hipGetLastError();
 }
 
 hipError_t sorf_launch_fchl19_backward(const float* R, const int32_t* element,
-                                       const int64_t* mol_ptr, int64_t n_mols, int32_t E,
-                                       const FchlParamsHost& ph, const float* g, float* dR,
+                                       const int64_t* mol_ptr, int64_t n_atoms, int64_t n_mols,
+                                       int32_t E, const FchlParamsHost& ph, const float* g, float* dR,
                                        hipStream_t st) {
   if (n_mols == 0) return hipSuccess;
   const FchlParams p{ph.n2, ph.n3, ph.eta2, ph.eta3, ph.N2, ph.N3, ph.c3, ph.zeta, ph.rcut};
@@ -1284,8 +1329,14 @@ hipError_t sorf_launch_fchl19_backward(const float* R, const int32_t* element,
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  // molecules above kFchlSmallAtoms atoms: a resident grid, one workgroup per atom
-  hipLaunchKernelGGL(fchl19_backward_gather_kernel, dim3(256u), dim3(kFchlThreads), 0, st, R, element,
-                     mol_ptr, n_mols, E, p, size, g, dR);
+  // molecules above kFchlSmallAtoms atoms
+  const auto go = [&](auto kernel, int threads, int64_t most) {
+    hipLaunchKernelGGL(kernel, dim3(unsigned(n_atoms < most ? n_atoms : most)), dim3(unsigned(threads)),
+                       0, st, R, element, mol_ptr, n_mols, E, p, size, g, dR);
+  };
+  if (fchl_few_atoms(n_atoms, ph.n3))
+    go(fchl19_backward_gather_kernel<kFchlThreads>, kFchlThreads, kFchlUnits);
+  else
+    go(fchl19_backward_gather_kernel<kFchlThreads / 2>, kFchlThreads / 2, 2 * kFchlUnits);
   return hipGetLastError();
 }
