@@ -635,8 +635,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7, 7))) voi
   // g-th of G equal parts of the chunk's pairs in order. An element pair
   // whose pairs fall in several parts is finished by the group where it ends,
   // which adds the partial sums of the earlier groups in group order. With
-  // more than 64 radial bins one group's lanes loop over them.
-  const int G = p.n3 <= 64 ? 64 / p.n3 : 1;
+  // more than 64 radial bins one group's lanes loop over them. At most 12 groups (16
+  // pairs of a full chunk each): with 32 of two radial bins the sums over groups took
+  // longer than the pairs (256 molecules of 64 atoms 219 us, now 181).
+  const int G = p.n3 <= 64 ? min(64 / p.n3, 12) : 1;
   const int g = p.n3 <= 64 ? lane / p.n3 : 0;
   const int kl = p.n3 <= 64 ? lane % p.n3 : lane;
   float* __restrict__ out3 = out + int64_t(E) * p.n2;
