@@ -79,6 +79,13 @@ __device__ __forceinline__ double block_sum(double v, double* red) {
   return v;
 }
 
+// 1 / q to rounding (the hardware's approximation, two Newton steps).
+__device__ __forceinline__ double fit_rcp(double q) {
+  double r = __builtin_amdgcn_rcp(q);
+  r = fma(r, fma(-q, r, 1.0), r);
+  return fma(r, fma(-q, r, 1.0), r);
+}
+
 // A (n x n, full) = the symmetric matrix whose lower triangle is G.
 __global__ __launch_bounds__(256) void fit_init_kernel(const double* __restrict__ G, int n,
                                                        double* __restrict__ A) {
@@ -142,21 +149,22 @@ __global__ __launch_bounds__(kFitThreads) void fit_column_kernel(
   x2 = block_sum(x2, red);
   const double dk = sn[k];
   const double x0 = k + 1 < n ? sn[k + 1] : 0.0;
-  double t = 0.0, alpha = x0;
+  // sn: the reflector times its head; the scale is put into what leaves the kernel
+  double t = 0.0, alpha = x0, scale = 1.0;
   if (x2 > kFitNothing) {
     const double norm = sqrt(fma(x0, x0, x2));
     alpha = x0 > 0.0 ? -norm : norm;
     const double head = x0 - alpha, h2 = head * head;   // |head| >= norm
-    t = 2.0 * h2 / (h2 + x2);
+    t = 2.0 * h2 * fit_rcp(h2 + x2);
+    scale = fit_rcp(head);
     __syncthreads();                            // x0 has been read by every thread
-    const double scale = 1.0 / head;
-    for (int j = k + 1 + tid; j < n; j += kFitThreads) sn[j] = j > k + 1 ? sn[j] * scale : 1.0;
+    if (tid == 0) sn[k + 1] = head;
   } else if (x2 != x2) {
     t = x2;                                     // not a number: carried into the result
   }
   __syncthreads();
   if (blockIdx.x == 0) {
-    for (int j = k + 1 + tid; j < n; j += kFitThreads) Vh[int64_t(k) * n + j] = sn[j];
+    for (int j = k + 1 + tid; j < n; j += kFitThreads) Vh[int64_t(k) * n + j] = sn[j] * scale;
     if (tid == 0) {
       tau[k] = t;
       diag[k] = dk;
@@ -184,14 +192,7 @@ __global__ __launch_bounds__(kFitThreads) void fit_column_kernel(
     }
   }
   s = wave_sum(s);
-  if (lane == 0) p_out[i] = s;
-}
-
-// 1 / q to rounding (the hardware's approximation, two Newton steps).
-__device__ __forceinline__ double fit_rcp(double q) {
-  double r = __builtin_amdgcn_rcp(q);
-  r = fma(r, fma(-q, r, 1.0), r);
-  return fma(r, fma(-q, r, 1.0), r);
+  if (lane == 0) p_out[i] = s * scale;
 }
 
 // lam[r] = the r-th largest eigenvalue of T; norm[0] = a bound on ||T||. One
