@@ -426,7 +426,7 @@ template <int NT>
 struct FchlDeal {
   int64_t a0[NT], n[NT];   // first atom, atoms
   int32_t shift[NT];       // first atom mod grid
-  int32_t per_wave[NT / 64];
+  int32_t per_wave[2][NT / 64];   // of this group of molecules and the next
 };
 template <int NT, typename Atom>
 __device__ __forceinline__ void fchl_deal(const int64_t* __restrict__ mol_ptr, int64_t n_mols,
@@ -439,7 +439,8 @@ __device__ __forceinline__ void fchl_deal(const int64_t* __restrict__ mol_ptr, i
     lo = mol_ptr[tid];
     hi = mol_ptr[tid + 1];
   }
-  for (int64_t m0 = 0; m0 < n_mols; m0 += NT) {
+  int buf = 0;
+  for (int64_t m0 = 0; m0 < n_mols; m0 += NT, buf ^= 1) {
     const int64_t m = m0 + tid, a0 = lo, n = hi - lo;
     const bool large = m < n_mols && n > small;
     // next group's sizes in flight while this group is processed
@@ -448,13 +449,14 @@ __device__ __forceinline__ void fchl_deal(const int64_t* __restrict__ mol_ptr, i
       hi = mol_ptr[m + NT + 1];
     }
     const uint64_t mask = __ballot(large);
-    if (lane == 0) sh.per_wave[wv] = __popcll(mask);
+    if (lane == 0) sh.per_wave[buf][wv] = __popcll(mask);
     __syncthreads();
     int off = 0, nbig = 0;
     for (int w = 0; w < NW; ++w) {
-      off += w < wv ? sh.per_wave[w] : 0;
-      nbig += sh.per_wave[w];
+      off += w < wv ? sh.per_wave[buf][w] : 0;
+      nbig += sh.per_wave[buf][w];
     }
+    if (nbig == 0) continue;   // one barrier a group of small molecules
     if (large) {
       const int t = off + __popcll(mask & ((uint64_t(1) << lane) - 1));
       sh.a0[t] = a0;
