@@ -1150,7 +1150,7 @@ static hipError_t launch_solve(int32_t D, const TG* G, const TG* Zty, double lam
                      w.A, info, w.y, w.pflags);
   // Right-looking blocked Cholesky with lookahead over two streams. Caller's
   // stream (the chain of dependent steps): the panel rows of the next block
-  // row, fused with the update of the next diagonal tile (4 workgroups), then
+  // row, fused with the update of the next diagonal tile (8 workgroups), then
   // the factorisation of that block. Second stream: the other panel rows, the
   // trailing tiles the next panel reads (first block column and the next
   // diagonal tile but one), then the rest of the trailing update in a
