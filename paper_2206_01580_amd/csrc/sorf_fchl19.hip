@@ -14,9 +14,10 @@
 //                 below r_cut and 0 beyond.
 //
 // Atoms of molecules of up to 64 atoms take one wave each (see
-// fchl19_forward_small_kernel). Larger molecules: one workgroup (16 waves) per atom. The atom's neighbours (same molecule,
-// closer than r_cut) are gathered into LDS grouped by element, in atom order
-// inside each group (ballot compaction, no atomics), with their per-neighbour
+// fchl19_forward_small_kernel). Larger molecules: one workgroup per atom, of 16
+// waves, or of 8 from 257 atoms in the batch on (fchl_few_atoms). The atom's
+// neighbours (same molecule, closer than r_cut) are gathered into LDS grouped by
+// element, in atom order inside each group (ballot compaction, no atomics), with their per-neighbour
 // two-body factors. Two-body bins: one thread per (element, bin) sums its
 // element's neighbours in order. Three-body: the unordered pairs are numbered
 // by element pair (X <= Y), then by position; chunks of pairs get their
@@ -96,8 +97,8 @@ constexpr int kFchlThreads = 1024;   // workgroup of the kernels for large molec
 // neighbours per element with ballots (lane X keeps element X's count), one
 // wave turns the counts into first slots, and each wave hands out its own:
 // two barriers for any molecule, where a pass per element and 1024 atoms had
-// one each and formed the neighbours' factors anew in each (1260 atoms: the
-// forward 173 us, now 133, the backward 167, now 132).
+// one each and formed the neighbours' factors anew in each (1260 atoms, 16
+// waves: the forward 173 us, now 133, the backward 167, now 132).
 template <int NT>
 struct FchlGather {
   int32_t first[kFchlMaxElements][NT / 64];

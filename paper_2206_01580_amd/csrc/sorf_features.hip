@@ -211,7 +211,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) void f
 // every transform and after the cosines. The odd atoms' sums are added to the
 // even ones' through LDS. Barriers are bracketed for the scheduler, which
 // would otherwise move the butterflies across them.
-// 20,000 molecules, D = 8192, T = 3 (T = 1): 1.95 (1.07) ms against 2.31 (1.49)
+// 20,000 molecules, D = 8192, T = 3 (T = 1): 1.93 (1.07) ms against 2.31 (1.49)
 // with one wave per item and no barriers; 2.24 ms in this form without the
 // barriers. In a register-only copy of the loop body an atom and wave take 3020
 // cycles instead of 3970, and 2500 without the DPP stages, which run one wave

@@ -19,13 +19,16 @@
 //                per vector;
 //   clusters     vectors of eigenvalues closer than kFitCluster ||T|| are
 //                orthonormalised in order, one workgroup per 16; their inverse
-//                iteration is repeated from the orthonormal vectors;
+//                iteration is repeated from the orthonormal vectors. Nothing to
+//                do where the wanted spectrum decays slowly; for n_pca above the
+//                rank of the sample it is most of the call (44 ms at n = n_pca =
+//                720 and rank 100);
 //   back         the reflectors are applied to the wanted vectors only.
 //
 // What bounds it: the chain of n dependent columns, each a launch of about six
 // microseconds (launch, two workgroup sums, one pass over L2; the arithmetic is
 // under 2 % of that). At n = 720, n_pca = 128 (1000 samples) the call takes
-// 5.5 ms: columns 4.2, vectors 0.54, back 0.46, bisection 0.29, Gram 0.13. The
+// 5.4 ms: columns 4.2, vectors 0.54, back 0.46, bisection 0.29, Gram 0.05. The
 // cyclic Jacobi method that stood here before took 112 ms (15 sweeps of 719
 // launches, all n eigenvectors rotated at every one of them; with blocks of 16
 // indices it needs as many sweeps, so fewer launches alone would not do).
@@ -97,7 +100,8 @@ __global__ __launch_bounds__(256) void fit_init_kernel(const double* __restrict_
 
 // Column k of the reduction. In: A with the updates of columns < k - 1, the
 // reflector v of column k - 1 (H = I - tau v v^T, entries >= k, the first one 1,
-// so that 1 <= tau <= 2 however small the column was), tau and p = A v. Every workgroup forms, from row k of A and these vectors,
+// so that 1 <= tau <= 2 however small the column was), tau and p = A v. Every
+// workgroup forms, from row k of A and these vectors,
 //   w = tau p - (tau^2 / 2) (v . p) v,   column k of A - v w^T - w v^T,
 // the diagonal entry, the subdiagonal entry and the next reflector; then it
 // updates its own rows i > k and multiplies them by the new reflector. Row k

@@ -702,9 +702,9 @@ void gram_packed_kernel(const u16x8* __restrict__ hi, const u16x8* __restrict__ 
 
 // ------------------------------------------------ FP32 mode on bf16 matrix cores
 // Every FP32 entry is the exact sum of three bf16 parts, z = h + m + l (split3),
-// |m| <= 2^-8 |z| and |l| <= 2^-16 |z|. G takes the six products h h, h m, m h,
-// m m, h l and l h; the three left out are below 2^-23 |z z'| together, one FP32
-// rounding of the product. The sums are the FP32 mode's: 256 rows in a fresh
+// |m| <= 2^-8 |z| and |l| <= 2^-17 |z|. G takes the six products h h, h m, m h,
+// m m, h l and l h; the three left out are at most (2^-24 + 2^-34) |z z'| together,
+// one FP32 rounding of the product. The sums are the FP32 mode's: 256 rows in a fresh
 // matrix-core accumulator, block sums added in FP32, row slices combined in
 // order. Against FP64 the result is closer than the FP32 matrix cores' (relative
 // Frobenius error at 700 x 1024 1.08e-7 against 1.38e-7, at 3000 x 2048 6.7e-8
@@ -2000,7 +2000,9 @@ static size_t slice_partial_bytes(const SlicePlan& p, int32_t D) {
 // 1024 columns on. Below that the products are too few to pay for packing the
 // parts: 512 x 1024 takes 86 us against 102 on the FP32 matrix cores and 1024
 // x 1024 118 against 124, but 512 x 512 73 against 64 and 200 x 1024 54
-// against 53.
+// against 53. (With Zty, whose sums the packing pass takes along; without it
+// 512 to 530 rows are up to 5 % slower in parts. An entry outside the parts'
+// range costs the packing on top: 512 x 1024 115 us against 101.)
 static bool use_parts(int64_t M, int32_t D, int mode) {
   return mode == kFP32 && D % 4 == 0 && M >= kPartsMinRows && D >= kPartsMinCols;
 }
